@@ -224,9 +224,10 @@ int64_t lb_time(const lb_ctx *ctx);
    when its count is set to the checkpoint's lb_time before stepping.  LB_EINVAL for t < 0. */
 int lb_set_time(lb_ctx *ctx, int64_t t);
 
-/* Launch shape of the step kernel: strip width tx in {64, 128, 256} columns (one workgroup
-   thread per column) and sy >= 1 rows per workgroup.  Any shape gives bitwise identical
-   results.  Host call. */
+/* Launch shape of the row-marching kernels: strip width tx in {64, 128, 256} columns (one
+   workgroup thread per column) and sy >= 1 rows per workgroup.  lb_step advances in rectangular
+   tiles, up to three steps per launch, until a shape is set here; from then on it marches rows in
+   that shape, one step per launch.  Any shape gives bitwise identical results.  Host call. */
 int lb_set_tile(lb_ctx *ctx, int32_t tx, int32_t sy);
 int lb_get_tile(const lb_ctx *ctx, int32_t *tx, int32_t *sy);
 
@@ -254,19 +255,22 @@ int lb_set_rounding(lb_ctx *ctx, int32_t mode);
    `rows` rows (0: the default, sized so the whole grid is resident), recomputing the overlaps.
    The per-site arithmetic and the rounding of the intermediate to the storage format are those
    of two single steps: results are bitwise identical to LB_TWO_STEP_OFF (also with stochastic
-   BF16 rounding and under graph replay).  LB_TWO_STEP_AUTO (the default) pairs the steps where
-   they measured faster, for lattices whose two population buffers exceed the 256 MiB Infinity
-   Cache: walled FP32 and periodic FP64 lattices.  LB_EINVAL for rows < 0.  Host call. */
+   BF16 rounding and under graph replay).  LB_TWO_STEP_OFF launches every step by itself.
+   LB_TWO_STEP_AUTO (the default) takes the tile step, which advances two or three steps per
+   launch (one launch per step once lb_set_tile has set a shape, except for walled FP32 and
+   periodic FP64 lattices whose two buffers exceed the 256 MiB Infinity Cache, whose steps then go
+   in pairs).  LB_EINVAL for rows < 0.  Host call. */
 enum lb_two_step { LB_TWO_STEP_OFF = 0, LB_TWO_STEP_ON = 1, LB_TWO_STEP_AUTO = 2 };
 int lb_set_two_step(lb_ctx *ctx, int32_t enable, int32_t rows);
 
-/* 1 if lb_step currently advances plain steps in pairs (lb_set_two_step and the reduction
-   setting), 0 if one per launch, -1 for a NULL context.  Pure host call. */
+/* 1 if the two-step rule (lb_set_two_step and the reduction setting) pairs this lattice's plain
+   steps, 0 if not, -1 for a NULL context.  It does not count the steps per launch of the tile
+   step.  Pure host call. */
 int lb_two_step_active(const lb_ctx *ctx);
 
 /* Replay plain steps from captured HIP graphs: with steps > 0 (even) and no reductions
-   (lb_set_reduce_every k = 0), lb_step runs whole groups of `steps` launches as one graph
-   launch on the context's stream and the remainder one by one.  Graphs are captured on first
+   (lb_set_reduce_every k = 0), lb_step runs whole groups of `steps` steps as one graph
+   launch on the context's stream and the remainder as it would without graphs.  Graphs are captured on first
    use on a private stream and rebuilt after lb_set_tile / lb_autotune.  steps = 0 turns
    graphs off.  Host call; results are bitwise those of individual launches. */
 int lb_set_graph(lb_ctx *ctx, int32_t steps);
@@ -274,7 +278,8 @@ int lb_set_graph(lb_ctx *ctx, int32_t steps);
 /* Autotuner: time trial_steps launches of each candidate launch shape (tx in {64, 128, 256},
    sy from 1 to 64, and the current shape) with HIP events on the context's stream, keep the
    fastest and return it in *tx, *sy and its time per step in milliseconds in *ms (any
-   output may be NULL).  Trial launches read the current state and write the other
+   output may be NULL).  The tile step competes: where it is faster, lb_step takes it, *ms is its
+   time, and *tx, *sy the fastest shape of the row-marching kernels.  Trial launches read the current state and write the other
    population buffer, so the state is unchanged.  Synchronises. */
 int lb_autotune(lb_ctx *ctx, int32_t trial_steps, int32_t *tx, int32_t *sy, double *ms);
 

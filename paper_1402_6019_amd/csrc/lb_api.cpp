@@ -38,6 +38,7 @@ struct lb_ctx {
   int pitch = 0;
   long long plane = 0;
   int tx = 256, sy = 16;
+  bool shape_set = false;  // lb_set_tile, or an autotuner that found no tile step faster: row-marching steps
   int n_cu = 256;  // compute units of the device the context runs on
   int device = 0;  // device current at lb_init
   int reduce_every = 0;
@@ -174,6 +175,62 @@ bool pairs_on(const lb_ctx *c) {
     return (c->lat.storage == LB_F32 && c->lat.walls) || (c->lat.storage == LB_F64 && !c->lat.walls);
   }
   return c->two_step == LB_TWO_STEP_ON;
+}
+
+// Whether plain and reducing steps run in tiles (lb_tile.hpp), several per launch; else in marched
+// rows of the launch shape that lb_set_tile or the autotuner set, or in the pairs that
+// lb_set_two_step forces.  The tile launch finds a workgroup's tile by a multiplication that is
+// exact while tiles per row times tiles stay below 2^32 (any lattice of fewer than 30 M columns).
+bool tiles_on(const lb_ctx *c);
+
+// Tile shape: the smallest whose tiles fit the compute units one each.  A launch lasts as long as
+// its busiest compute unit, so up to that point a larger tile only adds work, and beyond it a
+// smaller one only adds overlap: per step of 188 x 168 FP64 sites (one species) 16 x 8 tiles
+// took 2.7 us, 8 x 8 3.5 and 16 x 16 3.4; of a 512 x 512 FP32 channel 32 x 16 tiles 7.4 us,
+// 16 x 16 8.1.
+int tile_shape(const lb_ctx *c) {
+  for (int k = 0; k < kTileShapes - 1; ++k)
+    if ((int64_t)((c->lat.lx + kTileX[k] - 1) / kTileX[k]) * ((c->lat.ly + kTileY[k] - 1) / kTileY[k]) <= c->n_cu)
+      return k;
+  return kTileShapes - 1;
+}
+
+int tile_blocks(const lb_ctx *c, int shape) {
+  return ((c->lat.lx + kTileX[shape] - 1) / kTileX[shape]) * ((c->lat.ly + kTileY[shape] - 1) / kTileY[shape]);
+}
+
+bool tiles_on(const lb_ctx *c) {
+  if (c->shape_set || c->two_step == LB_TWO_STEP_ON) return false;
+  const int s = kTileShapes - 1;
+  const uint64_t ntx = (uint64_t)((c->lat.lx + kTileX[s] - 1) / kTileX[s]);
+  return ntx * ntx * (uint64_t)((c->lat.ly + kTileY[s] - 1) / kTileY[s]) < (1ull << 32);
+}
+
+// Steps of the next tile launch with n left: as many as the shape takes, but no single step at
+// the end where two launches of two do (3 + 1 = 2 + 2); one with two steps per launch turned off.
+int tile_steps(const lb_ctx *c, int shape, int64_t n) {
+  const int most = c->two_step == LB_TWO_STEP_OFF ? 1 : kTileSteps[shape];
+  if (most == 3 && n == 4) return 2;
+  return (int)std::min<int64_t>(most, n);
+}
+
+// n steps of the tile kernel in one launch (time steps t_step .. t_step + n - 1) from buffer
+// `from` to the other one.  Streaming stores where the buffers exceed the Infinity Cache, as for
+// the row-marching step, but not in FP32 and BF16 with two steps per launch: 4096 x 512 FP32
+// 45.9 us per step written through, 46.7 streaming; 1024^2 FP64 51.4 and 50.1.
+hipError_t launch_tile_steps(const lb_ctx *c, int shape, int n, int from, int what, uint32_t red_mask, hipStream_t st,
+                             uint32_t t_step, const double *t_base) {
+  StepArgs a;
+  fill_step_args(c, a);
+  if (c->store_policy == LB_STORES_AUTO && n > 1 && c->lat.storage != LB_F64) a.stream_stores = 0;
+  a.src = c->pop[from];
+  a.dst = c->pop[from ^ 1];
+  a.accrows = c->d_accrows;
+  a.t_step = t_step;
+  a.t_base = t_base;
+  TileOpts o;
+  o.red_mask = red_mask;
+  return launch_tile(step_mode(c), c->lat.n_species, c->lat.walls, what, shape, n, a, o, st);
 }
 
 // Two plain steps in one launch (time steps t_step and t_step + 1) from buffer `from` to the
@@ -436,10 +493,24 @@ int lb_step(lb_ctx *c, int64_t n) {
       hipGraphExec_t g = nullptr;
       const int from = c->cur;
       const double *tb = c->rounding == LB_ROUND_STOCHASTIC ? c->d_tbase : nullptr;
-      const bool pairs = pairs_on(c);
+      const bool tiles = tiles_on(c), pairs = !tiles && pairs_on(c);
+      const int shape = tile_shape(c);
+      int launches = 0;  // of one replay (the buffers swap once per launch)
+      if (tiles)
+        for (int64_t k = 0; k < c->graph.steps; k += tile_steps(c, shape, c->graph.steps - k)) ++launches;
       hipError_t e = c->graph.get(
           from,
           [&](int k, hipStream_t st) {
+            if (tiles) {  // every launch with the first step
+              hipError_t er = hipSuccess;
+              int b = from;
+              for (int64_t j = 0; k == 0 && j < c->graph.steps && er == hipSuccess; b ^= 1) {
+                const int m = tile_steps(c, shape, c->graph.steps - j);
+                er = launch_tile_steps(c, shape, m, b, WHAT_STEP, 0, st, (uint32_t)j, tb);
+                j += m;
+              }
+              return er;
+            }
             if (!pairs) return launch_plain_step(c, from ^ (k & 1), st, (uint32_t)k, tb);
             // two steps per launch: one launch for each even k, the buffers swap once per launch
             return (k & 1) ? hipSuccess : launch_two_steps(c, from ^ ((k >> 1) & 1), st, (uint32_t)k, tb);
@@ -450,8 +521,30 @@ int lb_step(lb_ctx *c, int64_t n) {
       if (e == hipSuccess) e = hipGraphLaunch(g, c->stream);
       if (e != hipSuccess) return hip_fail(c, e, "step graph");
       c->t += c->graph.steps;
+      if (tiles) c->cur ^= launches & 1;
       if (pairs) c->cur ^= (c->graph.steps >> 1) & 1;
       n -= c->graph.steps;
+    }
+  }
+  if (tiles_on(c)) {
+    const int shape = tile_shape(c);
+    while (n > 0) {
+      const int m = tile_steps(c, shape, n);
+      uint32_t mask = 0;
+      for (int k = 0; k < m && c->reduce_every > 0; ++k)
+        if ((c->t + k) % c->reduce_every == 0) mask |= 1u << k;
+      if (mask && (rc = ensure_accrows(c, tile_blocks(c, shape)))) return rc;
+      hipError_t e = launch_tile_steps(c, shape, m, c->cur, mask ? WHAT_STEP_ACCUM : WHAT_STEP, mask, c->stream,
+                                       (uint32_t)c->t, nullptr);
+      if (e != hipSuccess) return hip_fail(c, e, "tile step launch");
+      if (mask) {
+        c->acc_nb = tile_blocks(c, shape);
+        c->acc_pending += __builtin_popcount(mask);
+        reduced = true;
+      }
+      c->cur ^= 1;
+      c->t += m;
+      n -= m;
     }
   }
   if (pairs_on(c) && c->reduce_every == 0) {
@@ -633,6 +726,7 @@ int lb_set_tile(lb_ctx *c, int32_t tx, int32_t sy) {
   if (grid_blocks(c, tx, sy, nullptr) > kMaxBlocks) return fail(c, LB_EINVAL, "too many workgroups");
   c->tx = tx;
   c->sy = std::min<int32_t>(sy, c->lat.ly);
+  c->shape_set = true;
   c->graph.clear();  // captured launches carry the old shape
   return LB_OK;
 }
@@ -788,6 +882,21 @@ int lb_autotune(lb_ctx *c, int32_t trial_steps, int32_t *tx_out, int32_t *sy_out
   }
   c->tx = rc ? tx0 : best_tx;
   c->sy = rc ? sy0 : best_sy;
+  // the tile step competes too; where it wins, the shape found serves the passes that march
+  const bool set0 = c->shape_set;
+  c->shape_set = false;
+  if (!rc && tiles_on(c)) {
+    const int shape = tile_shape(c), n = tile_steps(c, shape, 1 << 20);
+    const double ms = time_launches(c->stream, 2, trial_steps, [&]() {
+      return launch_tile_steps(c, shape, n, c->cur, WHAT_STEP, 0, c->stream, (uint32_t)c->t, nullptr);
+    }) / n;
+    if (ms < 0.0) rc = hip_fail(c, hipGetLastError(), "autotune trial");
+    else if (ms < best) best = ms;
+    else c->shape_set = true;
+  } else if (!rc) {
+    c->shape_set = true;
+  }
+  if (rc) c->shape_set = set0;
   c->graph.clear();
   if (rc) return rc;
   if (tx_out) *tx_out = c->tx;

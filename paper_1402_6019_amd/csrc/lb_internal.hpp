@@ -74,6 +74,47 @@ struct StepArgs {
   double *accrows;            // WHAT_STEP_ACCUM: [gridDim.x][ACC_N] running sums
 };
 
+// Parameters of a lattice as the per-site arithmetic uses them, in the arithmetic type.
+template <typename R>
+struct SiteConsts {
+  R K1[2], K2[2], K4[2], K5[2], K8[2];  // shell couplings K(q); K4 and K8 twice it (|c| = 2 along an axis)
+  R tau[2], om[2], rref[2], psiw[2], rhow[2];
+  R T1, T2, gx, gy, psi0, nirho0;
+};
+
+// Kernel arguments of the tile step (lb_tile.hpp), passed by value.  The parameters come in the
+// arithmetic type: converting them per wave cost as much as a third of a site's update.
+template <typename R>
+struct TileArgs {
+  const void *src;     // post-collision populations of the previous step (pull source)
+  void *dst;           // post-collision populations of the launch's last step
+  double *accrows;     // reducing launches: [gridDim.x][ACC_N] running sums
+  void *fields;        // WHAT_STEP_FIELDS*: fields of the states stepped from and the populations
+  void *xw;            // of their rows next to the walls (StepArgs::out_rho, out_u), the bytes from
+  size_t fields_stride, xw_stride;  // one state to the next
+  uint32_t pitch_b, buf_b;          // bytes of a plane row and of the buffer
+  int lx, ly;
+  uint32_t ntx, ntx_mul;            // tiles per row; b / ntx = mulhi(b, ntx_mul) for every workgroup b
+  int cross_psi, moving;
+  uint32_t red_mask;                // which steps of the launch reduce (bit k: step k)
+  uint32_t t_step;                  // MODE_BF16SR: as StepArgs
+  const double *t_base;
+  double wall_mom[2][2];
+  double rho_ref[2], psi0, irho0;   // the fields' own (FP64) parameters
+  SiteConsts<R> c;
+};
+
+// What a tile launch does beside stepping.
+struct TileOpts {
+  uint32_t red_mask = 0;                     // WHAT_STEP_ACCUM: which steps of the launch reduce
+  size_t fields_stride = 0, xw_stride = 0;   // WHAT_STEP_FIELDS*: bytes from one state's outputs to the next's
+};
+
+// Tile shapes of the tile step: sites per tile, and the most steps of one launch.
+constexpr int kTileShapes = 4;
+constexpr int kTileX[kTileShapes] = {8, 16, 16, 32}, kTileY[kTileShapes] = {8, 8, 16, 16};
+constexpr int kTileSteps[kTileShapes] = {3, 3, 3, 2};
+
 // Batched launches: one tile of one instance.
 struct TileDesc {
   int inst;   // instance index (into BatchArgs::inst)
@@ -208,6 +249,16 @@ constexpr size_t kStaticScratchDoubles = (size_t)1 << 19;
 hipError_t static_scratch_setup(int device);
 // That address (nullptr before static_scratch_setup succeeded on the device).
 double *static_scratch(int device);
+
+// n steps (1 .. kTileSteps[shape]) of the tile step; what: WHAT_STEP or WHAT_STEP_ACCUM.
+hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
+                       hipStream_t st);
+hipError_t launch_tile_f64(int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
+                           hipStream_t st);
+hipError_t launch_tile_f32(int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
+                           hipStream_t st);
+hipError_t launch_tile_bf16(bool stochastic, int ns, int walls, int what, int shape, int n, const StepArgs &a,
+                            const TileOpts &o, hipStream_t st);
 
 // Per storage mode (lb_step_f64.hip, lb_step_f32.hip, lb_step_bf16.hip): the launchers that
 // launch_step / launch_batch_step / step_blocks_per_cu dispatch to.

@@ -299,6 +299,17 @@ hipError_t launch_step2(int mode, int ns, int walls, int nb, const StepArgs &a, 
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
+                       hipStream_t st) {
+  switch (mode) {
+    case MODE_F64: return launch_tile_f64(ns, walls, what, shape, n, a, o, st);
+    case MODE_F32: return launch_tile_f32(ns, walls, what, shape, n, a, o, st);
+    case MODE_BF16: return launch_tile_bf16(false, ns, walls, what, shape, n, a, o, st);
+    case MODE_BF16SR: return launch_tile_bf16(true, ns, walls, what, shape, n, a, o, st);
+  }
+  return hipErrorInvalidValue;
+}
+
 int step_blocks_per_cu(int mode, int ns, int walls, int tx) {
   switch (mode) {
     case MODE_F64: return blocks_per_cu_f64(ns, walls, tx);
