@@ -7,7 +7,8 @@ stresses are FP64 sums in another order (relative 1e-12 of sums of at most 1e5 t
 import numpy as np
 import pytest
 
-from cases import emulsion_case, film_case, make_sim
+import lbgen
+from cases import film_case, make_sim
 
 pytestmark = pytest.mark.gpu
 
@@ -18,7 +19,11 @@ SIZES = [(5, 5), (9, 41), (160, 5), (64, 64), (61, 37), (131, 130), (301, 147), 
 def case(lx, ly, storage, ns, walls):
     if ns == 1:
         return film_case(lx, ly, seed=lx, storage=storage, tau=0.9)
-    c = emulsion_case(lx, ly, walls=walls, fraction=0.6, seed=lx + ly, storage=storage, g=1e-5, rmin=2.0, rmax=4.0, tau=1.1)
+    # the emulsion couplings on random densities between the two phases (any lattice size)
+    a = np.random.default_rng(lx + ly).uniform(0.3, 1.1, (ly, lx))
+    c = dict(film_case(lx, ly, storage=storage, tau=1.1), ns=2, walls=int(walls), g1=lbgen.EMULSION_G1, g2=lbgen.EMULSION_G2,
+             gab=lbgen.EMULSION_GAB, body=(1e-5, 0.0), rho_wall=lbgen.EMULSION_POOR if walls else (0.0, 0.0),
+             rho0=lbgen.EMULSION_RHO0, rho=np.stack([a, 1.4 - a]), rho_ref=(0.7, 0.7))
     if walls:
         c["u_wall"] = (-0.01, 0.02)
     return c
