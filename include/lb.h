@@ -424,8 +424,8 @@ int lb_batch_init(lb_batch **out, int32_t n, const lb_lattice *lats, const lb_co
                   const lb_psi_params *psis, const double *const *rho_init, void *pop_a, void *pop_b,
                   size_t pop_bytes, void *hip_stream);
 
-/* Advance every instance by n >= 0 steps: one launch per step over the tiles of all
-   instances (plus one reduction launch on reduced steps).  Asynchronous. */
+/* Advance every instance by n >= 0 steps: one launch over the tiles of all instances per two or
+   three steps (as lb_step), or per step (lb_batch_set_tile).  Asynchronous. */
 int lb_batch_step(lb_batch *b, int64_t n);
 
 /* As lb_set_reduce_every, for every instance. */
@@ -439,14 +439,15 @@ int lb_batch_set_rounding(lb_batch *b, int32_t mode);
 /* As lb_set_graph: graphs of `steps` batch launches. */
 int lb_batch_set_graph(lb_batch *b, int32_t steps);
 
-/* Tile shape of all instances (tx in {64, 128, 256}, sy >= 1) and the persistent grid:
-   grid workgroups take the tiles in rounds (grid = 0: one workgroup per tile).  Rebuilds the
-   tile table.  Synchronises. */
+/* Tile shape of the row-marching kernels for all instances (tx in {64, 128, 256}, sy >= 1) and
+   the persistent grid: grid workgroups take the tiles in rounds (grid = 0: one workgroup per
+   tile).  As lb_set_tile, a shape set here has lb_batch_step march rows in it, one step per
+   launch, instead of stepping in rectangular tiles.  Rebuilds the tile table.  Synchronises. */
 int lb_batch_set_tile(lb_batch *b, int32_t tx, int32_t sy, int32_t grid);
 int lb_batch_get_tile(const lb_batch *b, int32_t *tx, int32_t *sy, int32_t *grid);
 
-/* Autotuner over tx, sy in {2, ..., 32} and grid in {resident workgroups, one per tile}, as
-   lb_autotune; out[3] = (tx, sy, grid) and *ms (either may be NULL).  Synchronises. */
+/* Autotuner over tx, sy in {2, ..., 32} and grid in {resident workgroups, one per tile}, and the
+   tile step, as lb_autotune; out[3] = (tx, sy, grid) and *ms (either may be NULL).  Synchronises. */
 int lb_batch_autotune(lb_batch *b, int32_t trial_steps, int32_t out[3], double *ms);
 
 /* Moments of instance i, as lb_moments (device outputs [n_species][ly_i][lx_i] and

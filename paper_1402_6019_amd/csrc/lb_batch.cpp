@@ -57,6 +57,13 @@ struct lb_batch {
   double *d_acc = nullptr;       // [n][4]: wall stress sums (bot, top), count, bad
   double *h_acc = nullptr;       // pinned copy of d_acc
   size_t tile_cap = 0;
+  // tile step (lb_tile.hpp): its shape, per-instance arguments, tiles, reduction rows and jobs
+  bool shape_set = false;  // lb_batch_set_tile, or an autotuner that found the tile step slower: marched rows
+  int shape = 0, nst = 0;
+  void *d_targs = nullptr;
+  TileDesc *d_ttiles = nullptr;
+  double *d_taccrows = nullptr;
+  ReduceJob *d_tjobs = nullptr;
   hipEvent_t ev = nullptr;
   bool check_pending = false;
   bool unstable = false;
@@ -156,9 +163,88 @@ int build_tiles(lb_batch *b, int tx, int sy) {
   return LB_OK;
 }
 
+// Whether steps run in tiles (see lb_batch_set_tile); none fit if there are too many to list.
+bool tiles_on(const lb_batch *b) { return !b->shape_set && b->nst > 0; }
+
+// Tables of the tile step: the smallest shape whose tiles fit the compute units one each, as for
+// one lattice, tiles row by row within each instance.  Built once; synchronises the stream.
+template <typename R>
+int build_step_tiles_t(lb_batch *b) {
+  auto tiles_of = [&](int i, int k) {
+    return (long long)((b->lat[i].lx + kTileX[k] - 1) / kTileX[k]) * ((b->lat[i].ly + kTileY[k] - 1) / kTileY[k]);
+  };
+  long long total = 0;
+  for (b->shape = 0; b->shape < kTileShapes; ++b->shape) {
+    total = 0;
+    for (int i = 0; i < b->n; ++i) total += tiles_of(i, b->shape);
+    if (total <= b->n_cu || b->shape == kTileShapes - 1) break;
+  }
+  if (total > kMaxBlocks) return LB_OK;
+  const int bx = kTileX[b->shape], by = kTileY[b->shape];
+  std::vector<TileArgs<R>> args(b->n);
+  std::vector<TileDesc> tiles;
+  std::vector<ReduceJob> jobs(b->n);
+  tiles.reserve((size_t)total);
+  for (int i = 0; i < b->n; ++i) {
+    args[i] = make_tile_args<R>(b->args[i], (uint32_t)(b->ns * elem_size(b->storage)), bx);
+    jobs[i] = ReduceJob{(int)tiles.size(), (int)tiles_of(i, b->shape), 1.0 / b->lat[i].lx};
+    for (int ty = 0; ty * by < b->lat[i].ly; ++ty)
+      for (int tx = 0; tx * bx < b->lat[i].lx; ++tx) tiles.push_back(TileDesc{i, tx, ty, (int)tiles.size()});
+  }
+  hipError_t e;
+  if ((e = hipMalloc(&b->d_targs, args.size() * sizeof(args[0]))) != hipSuccess ||
+      (e = hipMalloc(&b->d_ttiles, tiles.size() * sizeof(TileDesc))) != hipSuccess ||
+      (e = hipMalloc(&b->d_tjobs, jobs.size() * sizeof(ReduceJob))) != hipSuccess ||
+      (e = hipMalloc(&b->d_taccrows, tiles.size() * ACC_N * sizeof(double))) != hipSuccess)
+    return bfail(b, LB_ENOMEM, std::string("step tiles: ") + hipGetErrorString(e));
+  if ((e = launch_fill(b->d_taccrows, 0.0, (int)tiles.size() * ACC_N, b->stream)) != hipSuccess ||
+      (e = hipMemcpyAsync(b->d_targs, args.data(), args.size() * sizeof(args[0]), hipMemcpyHostToDevice, b->stream)) !=
+          hipSuccess ||
+      (e = hipMemcpyAsync(b->d_ttiles, tiles.data(), tiles.size() * sizeof(TileDesc), hipMemcpyHostToDevice,
+                          b->stream)) != hipSuccess ||
+      (e = hipMemcpyAsync(b->d_tjobs, jobs.data(), jobs.size() * sizeof(ReduceJob), hipMemcpyHostToDevice,
+                          b->stream)) != hipSuccess ||
+      (e = hipStreamSynchronize(b->stream)) != hipSuccess)
+    return bhip(b, e, "step tiles");
+  b->nst = (int)tiles.size();
+  return LB_OK;
+}
+
+int build_step_tiles(lb_batch *b) {
+  return b->storage == LB_F64 ? build_step_tiles_t<double>(b) : build_step_tiles_t<float>(b);
+}
+
+// Steps of the next tile launch with n left (see lb_api.cpp).
+int tile_steps(const lb_batch *b, int64_t n) {
+  const int most = kTileSteps[b->shape];
+  if (most == 3 && n == 4) return 2;
+  return (int)std::min<int64_t>(most, n);
+}
+
+// n steps of every instance in one launch of the tile step from buffer `from` to the other one;
+// stores as for one lattice of the batch's footprint.
+hipError_t launch_tile_steps(const lb_batch *b, int n, int from, int what, uint32_t red_mask, hipStream_t st,
+                             uint32_t t_step, const double *t_base) {
+  BatchTiles a{};
+  a.inst = b->d_targs;
+  a.tiles = b->d_ttiles;
+  a.ntiles = b->nst;
+  a.stream_stores = streaming_stores(b->footprint) && (n == 1 || b->storage == LB_F64);
+  a.src = static_cast<const char *>(b->pop[from]);
+  a.dst = static_cast<char *>(b->pop[from ^ 1]);
+  a.accrows = b->d_taccrows;
+  a.t_step = t_step;
+  a.t_base = t_base;
+  TileOpts o;
+  o.red_mask = red_mask;
+  const int mode = b->storage == LB_BF16DEV && b->rounding == LB_ROUND_STOCHASTIC ? MODE_BF16SR : b->storage;
+  return launch_tile(mode, b->ns, b->walls, what, b->shape, n, a, o, st);
+}
+
 int flush_acc(lb_batch *b) {
   if (b->acc_pending == 0) return LB_OK;
-  hipError_t e = launch_batch_flush(b->d_accrows, b->d_jobs, b->n, b->d_acc, (double)b->acc_pending, b->stream);
+  const bool tiles = tiles_on(b);
+  hipError_t e = launch_batch_flush(tiles ? b->d_taccrows : b->d_accrows, tiles ? b->d_tjobs : b->d_jobs, b->n, b->d_acc, (double)b->acc_pending, b->stream);
   if (e != hipSuccess) return bhip(b, e, "reduction flush");
   b->acc_pending = 0;
   return LB_OK;
@@ -309,6 +395,7 @@ int lb_batch_init(lb_batch **out, int32_t n, const lb_lattice *lats, const lb_co
   const int tx = maxlx >= 256 ? 256 : (maxlx >= 128 ? 128 : 64);
   b->grid = resident(b, tx);
   int rc = build_tiles(b, tx, 8);
+  if (!rc) rc = build_step_tiles(b);
   if (rc) {
     g_batch_init_error = b->err;
     lb_batch_destroy(b);
@@ -355,9 +442,23 @@ int lb_batch_step(lb_batch *b, int64_t n) {
       hipGraphExec_t g = nullptr;
       const int from = b->cur;
       const double *tb = b->rounding == LB_ROUND_STOCHASTIC ? b->d_tbase : nullptr;
+      const bool tiles = tiles_on(b);
+      int launches = 0;  // of one replay (the buffers swap once per launch)
+      if (tiles)
+        for (int64_t k = 0; k < b->graph.steps; k += tile_steps(b, b->graph.steps - k)) ++launches;
       hipError_t e = b->graph.get(
           from,
           [&](int k, hipStream_t st) {
+            if (tiles) {  // every launch with the first step
+              hipError_t er = hipSuccess;
+              int buf = from;
+              for (int64_t j = 0; k == 0 && j < b->graph.steps && er == hipSuccess; buf ^= 1) {
+                const int m = tile_steps(b, b->graph.steps - j);
+                er = launch_tile_steps(b, m, buf, WHAT_STEP, 0, st, (uint32_t)j, tb);
+                j += m;
+              }
+              return er;
+            }
             return launch_tiles(b, WHAT_STEP, from ^ (k & 1), 0, nt, st, nullptr, nullptr, 0, (uint32_t)k, tb);
           },
           &g);
@@ -366,10 +467,25 @@ int lb_batch_step(lb_batch *b, int64_t n) {
       if (e == hipSuccess) e = hipGraphLaunch(g, b->stream);
       if (e != hipSuccess) return bhip(b, e, "step graph");
       b->t += b->graph.steps;
+      if (tiles) b->cur ^= launches & 1;
       n -= b->graph.steps;
     }
   }
   bool reduced = false;
+  while (tiles_on(b) && n > 0) {
+    const int m = tile_steps(b, n);
+    uint32_t mask = 0;
+    for (int k = 0; k < m && b->reduce_every > 0; ++k)
+      if ((b->t + k) % b->reduce_every == 0) mask |= 1u << k;
+    hipError_t e = launch_tile_steps(b, m, b->cur, mask ? WHAT_STEP_ACCUM : WHAT_STEP, mask, b->stream, (uint32_t)b->t,
+                                     nullptr);
+    if (e != hipSuccess) return bhip(b, e, "batch step launch");
+    reduced |= mask != 0;
+    b->acc_pending += __builtin_popcount(mask);
+    b->cur ^= 1;
+    b->t += m;
+    n -= m;
+  }
   for (int64_t k = 0; k < n; ++k) {
     const bool red = b->reduce_every > 0 && (b->t % b->reduce_every) == 0;
     hipError_t e = launch_tiles(b, red ? WHAT_STEP_ACCUM : WHAT_STEP, b->cur, 0, nt, b->stream, nullptr, nullptr, 0,
@@ -428,6 +544,7 @@ int lb_batch_set_tile(lb_batch *b, int32_t tx, int32_t sy, int32_t grid) {
   if (sy < 1) return bfail(b, LB_EINVAL, "sy must be >= 1");
   if (grid < 0 || grid > kMaxBlocks) return bfail(b, LB_EINVAL, "grid must be in [0, 2^20]");
   b->grid = grid;
+  b->shape_set = true;
   return build_tiles(b, tx, sy);
 }
 
@@ -484,6 +601,16 @@ int lb_batch_autotune(lb_batch *b, int32_t trial_steps, int32_t out[3], double *
   const int rc2 = build_tiles(b, rc ? tx0 : btx, rc ? sy0 : bsy);
   if (rc) return rc;
   if (rc2) return rc2;
+  // the tile step competes too; where it wins, the shape found serves the passes that march
+  if (b->nst > 0) {
+    const int m = kTileSteps[b->shape];
+    const double ms = time_launches(b->stream, 2, trial_steps, [&]() {
+      return launch_tile_steps(b, m, b->cur, WHAT_STEP, 0, b->stream, (uint32_t)b->t, nullptr);
+    }) / m;
+    if (ms < 0.0) return bhip(b, hipGetLastError(), "autotune trial");
+    b->shape_set = ms >= best;
+    best = std::min(best, ms);
+  }
   if (out) {
     out[0] = b->tx;
     out[1] = b->sy;
@@ -658,7 +785,7 @@ void lb_batch_destroy(lb_batch *b) {
   if (b->check_pending && b->ev) (void)hipEventSynchronize(b->ev);
   (void)hipStreamSynchronize(b->stream);
   for (void *p : {(void *)b->d_args, (void *)b->d_tiles, (void *)b->d_jobs, (void *)b->d_partials, (void *)b->d_accrows,
-                  (void *)b->d_prof,
+                  (void *)b->d_prof, (void *)b->d_targs, (void *)b->d_ttiles, (void *)b->d_taccrows, (void *)b->d_tjobs,
                   (void *)b->d_totals, (void *)b->d_acc})
     if (p) (void)hipFree(p);
   if (b->h_acc) (void)hipHostFree(b->h_acc);

@@ -101,8 +101,54 @@ struct TileArgs {
   const double *t_base;
   double wall_mom[2][2];
   double rho_ref[2], psi0, irho0;   // the fields' own (FP64) parameters
+  long long offset;                 // batch: byte offset of this instance in each population buffer
   SiteConsts<R> c;
 };
+
+// The arguments of a tile launch from those of the row-marching step.
+template <typename R>
+inline TileArgs<R> make_tile_args(const StepArgs &a, uint32_t site_b, int bx) {
+  TileArgs<R> t{};
+  t.offset = a.offset;
+  t.src = a.src;
+  t.dst = a.dst;
+  t.accrows = a.accrows;
+  t.fields = a.out_rho;
+  t.xw = a.out_u;
+  t.pitch_b = (uint32_t)a.pitch * site_b;
+  t.buf_b = 9u * (uint32_t)a.plane * site_b;
+  t.lx = a.lx;
+  t.ly = a.ly;
+  t.ntx = (uint32_t)((a.lx + bx - 1) / bx);
+  t.ntx_mul = (uint32_t)(((1ull << 32) + t.ntx - 1) / t.ntx);  // unused for one tile per row
+  t.cross_psi = a.cross_psi;
+  t.moving = a.moving;
+  t.t_step = a.t_step;
+  t.t_base = a.t_base;
+  t.psi0 = a.psi0;
+  t.irho0 = a.irho0;
+  for (int s = 0; s < 2; ++s) {
+    t.rho_ref[s] = a.rho_ref[s];
+    for (int w = 0; w < 2; ++w) t.wall_mom[w][s] = a.wall_mom[w][s];
+    t.c.K1[s] = R(a.K[s][0]);
+    t.c.K2[s] = R(a.K[s][1]);
+    t.c.K4[s] = R(2.0 * a.K[s][2]);
+    t.c.K5[s] = R(a.K[s][3]);
+    t.c.K8[s] = R(2.0 * a.K[s][4]);
+    t.c.tau[s] = R(a.tau[s]);
+    t.c.om[s] = R(a.omega[s]);
+    t.c.rref[s] = R(a.rho_ref[s]);
+    t.c.psiw[s] = R(a.psi_w[s]);
+    t.c.rhow[s] = R(a.rho_w[s]);
+  }
+  t.c.T1 = R(a.T[0]);
+  t.c.T2 = R(a.T[1]);
+  t.c.gx = R(a.body[0]);
+  t.c.gy = R(a.body[1]);
+  t.c.psi0 = R(a.psi0);
+  t.c.nirho0 = R(-a.irho0);
+  return t;
+}
 
 // What a tile launch does beside stepping.
 struct TileOpts {
@@ -137,6 +183,29 @@ struct BatchArgs {
   int stream_stores;     // non-temporal population stores (see StepArgs)
   double *accrows;       // WHAT_STEP_ACCUM: [tiles][ACC_N] running sums, row TileDesc::part
   uint32_t t_step;       // MODE_BF16SR: time step of the launch (see StepArgs)
+  const double *t_base;
+};
+
+// Kernel arguments of the batched tile step, and the same as the host passes them to the launcher
+// (inst: device array of TileArgs in the batch's arithmetic type).
+template <typename R>
+struct BatchTileArgs {
+  const TileArgs<R> *inst;
+  const TileDesc *tiles;
+  const char *src;
+  char *dst;
+  double *accrows;  // reducing launches: [tiles][ACC_N], row TileDesc::part
+  uint32_t red_mask, t_step;
+  const double *t_base;
+};
+struct BatchTiles {
+  const void *inst;
+  const TileDesc *tiles;
+  int ntiles, stream_stores;
+  const char *src;
+  char *dst;
+  double *accrows;
+  uint32_t t_step;
   const double *t_base;
 };
 
@@ -250,15 +319,22 @@ hipError_t static_scratch_setup(int device);
 // That address (nullptr before static_scratch_setup succeeded on the device).
 double *static_scratch(int device);
 
-// n steps (1 .. kTileSteps[shape]) of the tile step; what: WHAT_STEP or WHAT_STEP_ACCUM.
-hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
-                       hipStream_t st);
-hipError_t launch_tile_f64(int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
-                           hipStream_t st);
-hipError_t launch_tile_f32(int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
-                           hipStream_t st);
-hipError_t launch_tile_bf16(bool stochastic, int ns, int walls, int what, int shape, int n, const StepArgs &a,
-                            const TileOpts &o, hipStream_t st);
+// n steps (1 .. kTileSteps[shape]) of the tile step of one lattice, or of a batch; what: WHAT_STEP
+// or WHAT_STEP_ACCUM.  Per storage mode in lb_tile_f64.hip, lb_tile_f32.hip, lb_tile_bf16.hip.
+#define LB_TILE_LAUNCHERS(A)                                                                                       \
+  hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,  \
+                         hipStream_t st);                                                                          \
+  hipError_t launch_tile_f64(int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,        \
+                             hipStream_t st);                                                                      \
+  hipError_t launch_tile_f32(int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,        \
+                             hipStream_t st);                                                                      \
+  hipError_t launch_tile_bf16(int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,       \
+                              hipStream_t st);                                                                     \
+  hipError_t launch_tile_bf16sr(int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,     \
+                                hipStream_t st);
+LB_TILE_LAUNCHERS(StepArgs)
+LB_TILE_LAUNCHERS(BatchTiles)
+#undef LB_TILE_LAUNCHERS
 
 // Per storage mode (lb_step_f64.hip, lb_step_f32.hip, lb_step_bf16.hip): the launchers that
 // launch_step / launch_batch_step / step_blocks_per_cu dispatch to.

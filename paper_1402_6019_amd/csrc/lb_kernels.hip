@@ -299,15 +299,26 @@ hipError_t launch_step2(int mode, int ns, int walls, int nb, const StepArgs &a, 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
-                       hipStream_t st) {
+template <typename A>
+static hipError_t launch_tile_any(int mode, int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,
+                                  hipStream_t st) {
   switch (mode) {
     case MODE_F64: return launch_tile_f64(ns, walls, what, shape, n, a, o, st);
     case MODE_F32: return launch_tile_f32(ns, walls, what, shape, n, a, o, st);
-    case MODE_BF16: return launch_tile_bf16(false, ns, walls, what, shape, n, a, o, st);
-    case MODE_BF16SR: return launch_tile_bf16(true, ns, walls, what, shape, n, a, o, st);
+    case MODE_BF16: return launch_tile_bf16(ns, walls, what, shape, n, a, o, st);
+    case MODE_BF16SR: return launch_tile_bf16sr(ns, walls, what, shape, n, a, o, st);
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
+                       hipStream_t st) {
+  return launch_tile_any(mode, ns, walls, what, shape, n, a, o, st);
+}
+
+hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const BatchTiles &b, const TileOpts &o,
+                       hipStream_t st) {
+  return launch_tile_any(mode, ns, walls, what, shape, n, b, o, st);
 }
 
 int step_blocks_per_cu(int mode, int ns, int walls, int tx) {

@@ -44,8 +44,13 @@ constexpr size_t tile_lds_bytes() {
 // A coordinate wrapped onto [0, n); lattices narrower than a region may wrap more than once.
 __device__ __forceinline__ int wrap_any(int v, int n, bool narrow) { return narrow ? ((v % n) + n) % n : wrapi(v, n); }
 
+// N steps of the tile whose first site is (x0, y0), of the lattice described by a, from src to dst.
+// t0: time step of the first (stochastic rounding); red_mask: which steps reduce, into the
+// running sums accrow.
 template <int MODE, int NS, bool WALLS, int WHAT, int BX, int BY, int N, int NT, int STP>
-__global__ __launch_bounds__(NT) void tile_kernel(TileArgs<typename Codec<MODE>::R> a) {
+__device__ __forceinline__ void tile_steps(const TileArgs<typename Codec<MODE>::R> &a, const void *const src,
+                                           void *const dst, const int x0, const int y0, const uint32_t t0,
+                                           const uint32_t red_mask, double *const accrow) {
   using C = Codec<MODE>;
   using R = typename C::R;
   using S = typename C::S;
@@ -62,15 +67,10 @@ __global__ __launch_bounds__(NT) void tile_kernel(TileArgs<typename Codec<MODE>:
   const int lx = a.lx, ly = a.ly;
   constexpr uint32_t site_b = (uint32_t)(NS * sizeof(S));
   const uint32_t plane_b = a.pitch_b, row_b = 9u * a.pitch_b, buf_b = a.buf_b;
-  const uint32_t logical = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
-  const uint32_t by = a.ntx == 1 ? logical : __umulhi(logical, a.ntx_mul);
-  const int x0 = (int)(logical - by * a.ntx) * BX, y0 = (int)by * BY;
   const int tid = threadIdx.x;
   const bool narrow_x = lx < D::ex(1) + BX, narrow_y = ly < D::ex(1) - BX + 2 * BY;
   const SiteConsts<R> &p = a.c;
 
-  uint32_t t0 = 0;
-  if constexpr (MODE == MODE_BF16SR) t0 = launch_step_index<MODE>(a.t_step, a.t_base);
   double wb = 0.0, wt = 0.0, nbad = 0.0;
 
   auto stage = [&](auto kc) {
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(NT) void tile_kernel(TileArgs<typename Codec<MODE>:
     int pe[M], yg[M];  // the corner (-2, -2) of the site's neighbourhood in psi, and its row
     R f[M][NS][9];
     if constexpr (k == 1) {
-      const Rsrc rs = make_rsrc(a.src, buf_b);
+      const Rsrc rs = make_rsrc(src, buf_b);
       L fl[M][NS][9];
 #pragma unroll
       for (int m = 0; m < M; ++m) {
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(NT) void tile_kernel(TileArgs<typename Codec<MODE>:
       site_update<C, NS>(p, f[m], [&](int dx, int dy) { return pp[(dy + 2) * EX + dx + 2]; },
                          [&](int dx, int dy) { return xp[(dy + 2) * EX + dx + 2]; }, rho, fsa);
       if constexpr (ACCUM) {
-        if (in && ((a.red_mask >> (k - 1)) & 1u)) {
+        if (in && ((red_mask >> (k - 1)) & 1u)) {
           bool bad = false;
 #pragma unroll
           for (int s = 0; s < NS; ++s) {
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(NT) void tile_kernel(TileArgs<typename Codec<MODE>:
         hs = mix32((uint32_t)(y * lx + x) ^ tseed);
       }
       if constexpr (k == N) {
-        const Rsrc rd = make_rsrc(a.dst, buf_b);
+        const Rsrc rd = make_rsrc(dst, buf_b);
         const uint32_t o = (uint32_t)(y0 + sy) * row_b + (uint32_t)(x0 + sx) * site_b;
 #pragma unroll
         for (int l = 0; l < 9; ++l) {
@@ -286,58 +286,35 @@ __global__ __launch_bounds__(NT) void tile_kernel(TileArgs<typename Codec<MODE>:
     if (tid < ACC_N) {
       double t = 0.0;
       for (int w = 0; w < NW; ++w) t += red[w][tid];
-      a.accrows[(size_t)blockIdx.x * ACC_N + tid] += t;
+      accrow[tid] += t;
     }
   }
+}
+
+// One lattice: one workgroup per tile, tiles row by row, in contiguous ranges over the XCDs.
+template <int MODE, int NS, bool WALLS, int WHAT, int BX, int BY, int N, int NT, int STP>
+__global__ __launch_bounds__(NT) void tile_kernel(TileArgs<typename Codec<MODE>::R> a) {
+  const uint32_t logical = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t by = a.ntx == 1 ? logical : __umulhi(logical, a.ntx_mul);
+  tile_steps<MODE, NS, WALLS, WHAT, BX, BY, N, NT, STP>(
+      a, a.src, a.dst, (int)(logical - by * a.ntx) * BX, (int)by * BY, launch_step_index<MODE>(a.t_step, a.t_base),
+      a.red_mask, WHAT == WHAT_STEP_ACCUM ? a.accrows + (size_t)blockIdx.x * ACC_N : nullptr);
+}
+
+// Many lattices: one workgroup per entry of the host's list of every instance's tiles.
+template <int MODE, int NS, bool WALLS, int WHAT, int BX, int BY, int N, int NT, int STP>
+__global__ __launch_bounds__(NT) void batch_tile_kernel(BatchTileArgs<typename Codec<MODE>::R> b) {
+  const TileDesc td = b.tiles[xcd_remap(blockIdx.x, gridDim.x)];
+  const auto &a = b.inst[uni((uint32_t)td.inst)];
+  tile_steps<MODE, NS, WALLS, WHAT, BX, BY, N, NT, STP>(
+      a, b.src + a.offset, b.dst + a.offset, (int)uni((uint32_t)td.strip) * BX, (int)uni((uint32_t)td.seg) * BY,
+      launch_step_index<MODE>(b.t_step, b.t_base), b.red_mask,
+      WHAT == WHAT_STEP_ACCUM ? b.accrows + (size_t)td.part * ACC_N : nullptr);
 }
 
 // ---------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------
-
-// The arguments of a tile launch from those of the row-marching step.
-template <typename R>
-static TileArgs<R> make_tile_args(const StepArgs &a, uint32_t site_b, int bx) {
-  TileArgs<R> t{};
-  t.src = a.src;
-  t.dst = a.dst;
-  t.accrows = a.accrows;
-  t.fields = a.out_rho;
-  t.xw = a.out_u;
-  t.pitch_b = (uint32_t)a.pitch * site_b;
-  t.buf_b = 9u * (uint32_t)a.plane * site_b;
-  t.lx = a.lx;
-  t.ly = a.ly;
-  t.ntx = (uint32_t)((a.lx + bx - 1) / bx);
-  t.ntx_mul = (uint32_t)(((1ull << 32) + t.ntx - 1) / t.ntx);  // unused for one tile per row
-  t.cross_psi = a.cross_psi;
-  t.moving = a.moving;
-  t.t_step = a.t_step;
-  t.t_base = a.t_base;
-  t.psi0 = a.psi0;
-  t.irho0 = a.irho0;
-  for (int s = 0; s < 2; ++s) {
-    t.rho_ref[s] = a.rho_ref[s];
-    for (int w = 0; w < 2; ++w) t.wall_mom[w][s] = a.wall_mom[w][s];
-    t.c.K1[s] = R(a.K[s][0]);
-    t.c.K2[s] = R(a.K[s][1]);
-    t.c.K4[s] = R(2.0 * a.K[s][2]);
-    t.c.K5[s] = R(a.K[s][3]);
-    t.c.K8[s] = R(2.0 * a.K[s][4]);
-    t.c.tau[s] = R(a.tau[s]);
-    t.c.om[s] = R(a.omega[s]);
-    t.c.rref[s] = R(a.rho_ref[s]);
-    t.c.psiw[s] = R(a.psi_w[s]);
-    t.c.rhow[s] = R(a.rho_w[s]);
-  }
-  t.c.T1 = R(a.T[0]);
-  t.c.T2 = R(a.T[1]);
-  t.c.gx = R(a.body[0]);
-  t.c.gy = R(a.body[1]);
-  t.c.psi0 = R(a.psi0);
-  t.c.nirho0 = R(-a.irho0);
-  return t;
-}
 
 template <int MODE, int NS, bool WALLS, int WHAT, int BX, int BY, int N, int NT, int STP>
 static hipError_t launch_tile_k(const StepArgs &a, const TileOpts &o, hipStream_t st) {
@@ -352,9 +329,19 @@ static hipError_t launch_tile_k(const StepArgs &a, const TileOpts &o, hipStream_
   return hipGetLastError();
 }
 
-// n = 1 .. tile_max_steps(shape) steps in tiles of the shape; store policy by a.stream_stores.
-template <int MODE, int NS, bool WALLS, int WHAT>
-static hipError_t launch_tile_w(int shape, int n, const StepArgs &a, const TileOpts &o, hipStream_t st) {
+template <int MODE, int NS, bool WALLS, int WHAT, int BX, int BY, int N, int NT, int STP>
+static hipError_t launch_tile_k(const BatchTiles &b, const TileOpts &o, hipStream_t st) {
+  using R = typename Codec<MODE>::R;
+  BatchTileArgs<R> t{static_cast<const TileArgs<R> *>(b.inst), b.tiles, b.src, b.dst, b.accrows, o.red_mask, b.t_step, b.t_base};
+  hipLaunchKernelGGL((batch_tile_kernel<MODE, NS, WALLS, WHAT, BX, BY, N, NT, STP>), dim3(b.ntiles), dim3(NT),
+                     (tile_lds_bytes<MODE, NS, BX, BY, N>()), st, t);
+  return hipGetLastError();
+}
+
+// n = 1 .. kTileSteps[shape] steps of a lattice (A: StepArgs) or a batch (BatchTiles) in tiles of the
+// shape; store policy by a.stream_stores.
+template <int MODE, int NS, bool WALLS, int WHAT, typename A>
+static hipError_t launch_tile_w(int shape, int n, const A &a, const TileOpts &o, hipStream_t st) {
   constexpr int WT = kStoreWriteThrough, NTS = kStoreStreaming;
   switch (shape * 4 + n) {
     case 0 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 1, 256, WT>(a, o, st);
@@ -376,11 +363,20 @@ static hipError_t launch_tile_w(int shape, int n, const StepArgs &a, const TileO
   return hipErrorInvalidValue;
 }
 
-template <int MODE, int WHAT>
-static hipError_t launch_tile_m(int ns, int walls, int shape, int n, const StepArgs &a, const TileOpts &o,
-                                hipStream_t st) {
+template <int MODE, int WHAT, typename A>
+static hipError_t launch_tile_m(int ns, int walls, int shape, int n, const A &a, const TileOpts &o, hipStream_t st) {
   if (ns == 1) return walls ? launch_tile_w<MODE, 1, true, WHAT>(shape, n, a, o, st) : launch_tile_w<MODE, 1, false, WHAT>(shape, n, a, o, st);
   return walls ? launch_tile_w<MODE, 2, true, WHAT>(shape, n, a, o, st) : launch_tile_w<MODE, 2, false, WHAT>(shape, n, a, o, st);
+}
+
+template <int MODE, typename A>
+static hipError_t launch_tile_what(int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,
+                                   hipStream_t st) {
+  switch (what) {
+    case WHAT_STEP: return launch_tile_m<MODE, WHAT_STEP>(ns, walls, shape, n, a, o, st);
+    case WHAT_STEP_ACCUM: return launch_tile_m<MODE, WHAT_STEP_ACCUM>(ns, walls, shape, n, a, o, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace lb355

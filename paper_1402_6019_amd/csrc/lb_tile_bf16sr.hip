@@ -1,0 +1,18 @@
+// Tile step of the BF16-deviation storage mode, rounding stochastically: the instantiations of the tile
+// kernels for this mode.
+
+#include "lb_tile.hpp"
+
+namespace lb355 {
+
+hipError_t launch_tile_bf16sr(int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
+                           hipStream_t st) {
+  return launch_tile_what<MODE_BF16SR>(ns, walls, what, shape, n, a, o, st);
+}
+
+hipError_t launch_tile_bf16sr(int ns, int walls, int what, int shape, int n, const BatchTiles &b, const TileOpts &o,
+                           hipStream_t st) {
+  return launch_tile_what<MODE_BF16SR>(ns, walls, what, shape, n, b, o, st);
+}
+
+}  // namespace lb355

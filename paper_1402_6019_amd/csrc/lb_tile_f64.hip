@@ -1,4 +1,4 @@
-// Tile step of the F64 storage mode: the instantiations of the tile kernel for this mode.
+// Tile step of the FP64 storage mode: the instantiations of the tile kernels for this mode.
 
 #include "lb_tile.hpp"
 
@@ -6,11 +6,12 @@ namespace lb355 {
 
 hipError_t launch_tile_f64(int ns, int walls, int what, int shape, int n, const StepArgs &a, const TileOpts &o,
                            hipStream_t st) {
-  switch (what) {
-    case WHAT_STEP: return launch_tile_m<MODE_F64, WHAT_STEP>(ns, walls, shape, n, a, o, st);
-    case WHAT_STEP_ACCUM: return launch_tile_m<MODE_F64, WHAT_STEP_ACCUM>(ns, walls, shape, n, a, o, st);
-  }
-  return hipErrorInvalidValue;
+  return launch_tile_what<MODE_F64>(ns, walls, what, shape, n, a, o, st);
+}
+
+hipError_t launch_tile_f64(int ns, int walls, int what, int shape, int n, const BatchTiles &b, const TileOpts &o,
+                           hipStream_t st) {
+  return launch_tile_what<MODE_F64>(ns, walls, what, shape, n, b, o, st);
 }
 
 }  // namespace lb355

@@ -92,3 +92,29 @@ def test_autotune_takes_the_faster_of_tile_and_march():
     f = sim.checkpoint().cpu().numpy()
     sim.close()
     assert np.array_equal(f, populations(c, (5,), tile=(64, 7))[0])
+
+
+@pytest.mark.parametrize("storage,rounding", [("f64", None), ("f32", None), ("bf16dev", "stochastic")])
+@pytest.mark.parametrize("sizes", [[(61, 37), (20, 9), (40, 33)], [(300, 147), (517, 60), (33, 200), (5, 7)]])
+def test_batch_tile_steps_are_bitwise_the_marched_steps(storage, rounding, sizes):
+    """Instances of uneven sizes, few enough for one tile per compute unit and more; reductions and
+    graph replay too."""
+    from paper_1402_6019_amd import Batch
+    cases = [case(lx, ly, storage, 2, True) for lx, ly in sizes]
+    keys = ("g1", "g2", "gab", "body", "rho_wall", "tau", "psi0", "rho0", "rho_ref", "u_wall")
+    out = []
+    for march in (False, True):
+        b = Batch([dict({k: c[k] for k in keys}, lx=c["lx"], ly=c["ly"], rho_init=c["rho"]) for c in cases], n_species=2,
+                  walls=True, storage=storage)
+        if rounding:
+            b.set_rounding(rounding)
+        if march:
+            b.set_tile(64, 7)
+        b.set_graph(10)
+        b.step(24)
+        b.set_reduce_every(2)
+        b.step(5)
+        out.append(([b.checkpoint(i).cpu().numpy() for i in range(b.n)], b.wall_stress()))
+        b.close()
+    assert all(np.array_equal(x, y) for x, y in zip(out[0][0], out[1][0]))
+    assert np.abs(out[0][1] - out[1][1]).max() <= 1e-12 * np.abs(out[1][1]).max()
