@@ -68,7 +68,8 @@ int lb3_init(lb3_ctx **out, const lb3_lattice *lat, const lb3_couplings *cpl, co
              const lb_psi_params *psi, const double *rho_init, void *pop_a, void *pop_b, size_t pop_bytes,
              void *hip_stream);
 
-/* Advance n >= 0 steps of eq. (LB) in 3-D: one fused launch per step (pull streaming with
+/* Advance n >= 0 steps of eq. (LB) in 3-D: one fused launch per step, or two on small lattices,
+   whose context then holds a field of psi and rho (pull streaming with
    bounce-back, moments, psi, the two-belt force of eq. (FORCE) over the cube, the A-B
    repulsion and the body force, the velocity shift, BGK collision with the rest-population
    closure, store).  Asynchronous. */
@@ -93,8 +94,9 @@ int lb3_checkpoint(lb3_ctx *ctx, void *dst_f64);
 int lb3_restore(lb3_ctx *ctx, const void *src_f64);
 
 /* Launch shape: ty in {1, 2, 4} rows of 64 columns per workgroup (ty waves), or 8 with FP32
-   storage, and sz >= 1 z-planes per workgroup; any shape gives bitwise identical results.
-   LB_EINVAL otherwise.  Host call. */
+   storage, and sz >= 1 z-planes per workgroup, for a kernel that takes any of them; without a
+   call the library launches fixed tiles, faster, chosen by the lattice.  Any shape gives bitwise
+   identical results.  LB_EINVAL otherwise.  Host call. */
 int lb3_set_tile(lb3_ctx *ctx, int32_t ty, int32_t sz);
 int lb3_get_tile(const lb3_ctx *ctx, int32_t *ty, int32_t *sz);
 

@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblb355.so")
 SOURCES = ["lb_step_bf16.hip", "lb_step_f64.hip", "lb_step_f32.hip", "lb_tile_f64.hip", "lb_tile_f32.hip", "lb_tile_bf16.hip", "lb_tile_bf16sr.hip",
-           "lb_kernels.hip", "lb_adjoint.hip", "lb_static.hip", "lb3_kernels.hip", "lb_api.cpp", "lb_batch.cpp", "lb_rheology.cpp", "lb3_api.cpp"]
+           "lb_kernels.hip", "lb_adjoint.hip", "lb_static.hip", "lb3_kernels.hip", "lb3_march.hip", "lb3_split.hip", "lb_api.cpp", "lb_batch.cpp", "lb_rheology.cpp", "lb3_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -11,6 +11,7 @@
 
 #include "../../include/lb3.h"
 #include "lb3_internal.hpp"
+#include "lb_host.hpp"
 
 using namespace lb355;
 
@@ -73,6 +74,8 @@ struct lb3_ctx {
   hipStream_t stream = nullptr;
   int pitch = 0;
   int ty = 4, sz = 16;
+  bool shape_set = false;  // lb3_set_tile: the kernel that takes any launch shape
+  void *d_psi = nullptr;   // field of the split step, where that is taken
   int n_cu = 256;
   int64_t t = 0;
   double *d_partials = nullptr;
@@ -99,7 +102,8 @@ void grid3(const lb3_ctx *c, int ty, int sz, int *nstrip, int *nband, int *nseg)
   *nseg = (c->lat.lz + sz - 1) / sz;
 }
 
-// Default shape: eight rows per workgroup in FP32 (the halo is pulled in one round, together
+// Shape of step3_kernel reported until lb3_set_tile sets one: eight rows per workgroup in FP32 (the
+// halo is pulled in one round, together
 // with the workgroup's own sites: measured 6% faster than four rows at 256^3) and four in FP64
 // (its registers allow no more), fewer when the lattice is narrower, and z-segments long enough
 // that the whole grid is resident at once (one pass over the lattice; a second partial round
@@ -141,11 +145,36 @@ Lb3Args args3(const lb3_ctx *c) {
   return a;
 }
 
+// Launch of march3_kernel: segments long enough that every compute unit marches one.
+void march_grid3(const lb3_ctx *c, Lb3Args &a) {
+  const int ty = march3_rows(c->lat.storage == LB_F64 ? MODE_F64 : MODE_F32);
+  a.nstrip = (c->lat.lx + 31) / 32;
+  a.nband = (c->lat.ly + ty - 1) / ty;
+  const int segs = std::max(1, c->n_cu / (a.nstrip * a.nband));
+  a.sz = std::max(1, (c->lat.lz + segs - 1) / segs);
+  a.nseg = (c->lat.lz + a.sz - 1) / a.sz;
+  a.stream_stores = host::streaming_stores(lb3_pop_bytes(&c->lat));
+}
+
+// Whether the step goes in two passes (lb3_split.hip) instead of the march: where the march's
+// segments have at most eight planes, of which it pulls four more than it updates.  us per step,
+// split and march: FP32 64 x 48 x 40 19 and 26, 100 x 70 x 60 (segments of five) 54 and 61,
+// 128 x 128 x 64 (eight) 103 and 113, 128^3 (sixteen) 235 and 190; FP64 64 x 48 x 40 27 and 31,
+// 100 x 70 x 60 (nine) 110 and 98.
+bool split_rule(const lb3_ctx *c) {
+  Lb3Args a{};
+  march_grid3(c, a);
+  return a.sz <= 8;
+}
+
 int mode3(const lb3_ctx *c) { return c->lat.storage == LB_F64 ? MODE_F64 : MODE_F32; }
 
 int launch_what(lb3_ctx *c, int what, void *rho, void *u, int out_f32) {
   Lb3Args a = args3(c);
-  const int nb = a.nstrip * a.nband * a.nseg;
+  const bool split = !c->shape_set && c->d_psi;
+  if (!c->shape_set && !split) march_grid3(c, a);
+  a.psi = c->d_psi;
+  const int nb = split ? split3_tiles(c->lat.lx, c->lat.ly, c->lat.lz, &a.nstrip, &a.nband) : a.nstrip * a.nband * a.nseg;
   a.src = c->pop[c->cur];
   a.dst = c->pop[c->cur ^ 1];
   a.out_rho = rho;
@@ -162,7 +191,9 @@ int launch_what(lb3_ctx *c, int what, void *rho, void *u, int out_f32) {
     }
     a.partials = c->d_partials;
   }
-  hipError_t e = launch_step3(mode3(c), c->lat.n_species, c->lat.walls, what, c->ty, nb, a, c->stream);
+  hipError_t e = c->shape_set ? launch_step3(mode3(c), c->lat.n_species, c->lat.walls, what, c->ty, nb, a, c->stream)
+                 : split      ? launch_split3(mode3(c), c->lat.n_species, c->lat.walls, what, nb, a, c->stream)
+                              : launch_march3(mode3(c), c->lat.n_species, c->lat.walls, what, nb, a, c->stream);
   if (e != hipSuccess) return hip_fail3(c, e, "3-D step launch");
   if (what == WHAT_OBSERVE) {
     e = launch_reduce3(c->d_partials, nb, c->d_totals, c->stream);
@@ -239,6 +270,7 @@ int lb3_init(lb3_ctx **out, const lb3_lattice *lat, const lb3_couplings *cpl, co
   void *d_rho = nullptr;
   const size_t rho_bytes = (size_t)lat->n_species * nsite * sizeof(double);
   if ((e = hipMalloc(&c->d_totals, RED3_N * sizeof(double))) != hipSuccess ||
+      (split_rule(c) && (e = hipMalloc(&c->d_psi, nsite * lat->n_species * lat->n_species * elem3(lat->storage))) != hipSuccess) ||
       (e = hipMalloc(&d_rho, rho_bytes)) != hipSuccess ||
       (e = hipMemcpyAsync(d_rho, rho_init, rho_bytes, hipMemcpyHostToDevice, c->stream)) != hipSuccess) {
     g_init_error3 = std::string("allocation / copy: ") + hipGetErrorString(e);
@@ -330,6 +362,7 @@ int lb3_set_tile(lb3_ctx *c, int32_t ty, int32_t sz) {
   if (!ty_ok || sz < 1) return fail3(c, LB_EINVAL, "ty must be 1, 2, 4 (or 8 with FP32 storage) and sz >= 1");
   c->ty = ty;
   c->sz = std::min(sz, c->lat.lz);
+  c->shape_set = true;
   return LB_OK;
 }
 
@@ -349,6 +382,7 @@ void lb3_destroy(lb3_ctx *c) {
   (void)hipStreamSynchronize(c->stream);
   if (c->d_partials) (void)hipFree(c->d_partials);
   if (c->d_totals) (void)hipFree(c->d_totals);
+  if (c->d_psi) (void)hipFree(c->d_psi);
   delete c;
 }
 

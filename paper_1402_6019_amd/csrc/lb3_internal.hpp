@@ -28,6 +28,8 @@ struct Lb3Args {
   double psi0, irho0;
   double rho_w[2], psi_w[2];
   double rho_ref[2];
+  int stream_stores;  // both population buffers exceed the Infinity Cache (march3_kernel)
+  void *psi;          // split step: [ns == 2 ? 2 : 1][lz][ly][lx] psi, then rho, of both species
 };
 
 // Arguments of the 3-D layout kernels.
@@ -40,6 +42,12 @@ struct Lb3Layout {
 
 hipError_t launch_step3(int mode, int ns, int walls, int what, int ty, int nblocks, const Lb3Args &a,
                         hipStream_t st);
+// The same passes by lb3_march.hip: tiles of 32 columns by march3_rows(mode) rows.
+hipError_t launch_march3(int mode, int ns, int walls, int what, int nblocks, const Lb3Args &a, hipStream_t st);
+int march3_rows(int mode);
+// The same passes by lb3_split.hip (field a.psi); split3_tiles: its tiles, and those per row and plane.
+hipError_t launch_split3(int mode, int ns, int walls, int what, int nblocks, const Lb3Args &a, hipStream_t st);
+int split3_tiles(int lx, int ly, int lz, int *nstrip, int *nband);
 hipError_t launch_reduce3(const double *partials, int nblocks, double *totals, hipStream_t st);
 // kind: 0 init (in: rho [ns][lz][ly][lx]), 1 restore (in: canonical f), 2 checkpoint (out: canonical f)
 hipError_t launch_layout3(int kind, int mode, int walls, const Lb3Layout &a, hipStream_t st);
