@@ -24,7 +24,12 @@
 //     psibar_s(y) += sum_h K_s(q) c . (A_s(y+c) - A_s(y-c)),   A_s = psi_s Fbar_s
 //     rbar_sbar(y) += G_AB sum_{h in belt 1} t(q) c . (B_s(y+c) - B_s(y-c)),  B_s = r_s Fbar_s
 //   and rhobar = psi'(rho) psibar enters every lambda_l(t).
-// All three kernels work on canonical-layout arrays [..][y][x], one thread per site.
+// One kernel does both parts of a reverse step on canonical-layout arrays [..][y][x]: a workgroup
+// takes the local part for its tile plus a frame of two sites, keeps A and B of those in LDS and
+// gathers for its tile.  As two kernels (the local part of every site to memory, then the gather)
+// a step of a 512 x 256 channel in FP64 took 19.5 + 7.3 us, most of it the latency of one wave per
+// tile row with nothing to overlap it, and wrote and read A and B (128 bytes per site) between
+// them; the local part of the frame, computed by two tiles, costs less.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -34,6 +39,7 @@
 #include <utility>
 
 #include "lb_internal.hpp"
+#include "lb_step.hpp"
 #include "lb_tables.hpp"
 
 namespace lb355 {
@@ -41,18 +47,6 @@ namespace lb355 {
 namespace {
 
 __device__ inline int wrapx(int a, int n) { return a < 0 ? a + n : (a >= n ? a - n : a); }
-
-template <typename R>
-struct AdjView {
-  const AdjArgs &a;
-  int lx, ly;
-  size_t n;  // sites
-  __device__ AdjView(const AdjArgs &aa) : a(aa), lx(aa.lx), ly(aa.ly), n((size_t)aa.lx * aa.ly) {}
-  __device__ R *fields() const { return static_cast<R *>(a.fields); }
-  // field k (0 rho, 1 psi, 2 jx, 3 jy) of species s at site i
-  __device__ R fld(int k, int s, size_t i) const { return fields()[((size_t)k * 2 + s) * n + i]; }
-  __device__ R &fldw(int k, int s, size_t i) const { return fields()[((size_t)k * 2 + s) * n + i]; }
-};
 
 // Calls f(std::integral_constant<int, i>{}) for i = 0, 1, ..., N - 1 in order, so that the stencil
 // constants indexed by i are compile-time values inside f.
@@ -75,6 +69,11 @@ __device__ inline R cmul(R v) {
   else if constexpr (C == -1) return -v;
   else return R(C) * v;
 }
+
+// a b + c: fused in FP64, where it only drops a rounding; two operations in FP32, whose sensitivities
+// (sums that nearly cancel) would move with any change of their roundings.
+__device__ inline double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline float mad(float a, float b, float c) { return a * b + c; }
 
 // The equilibrium polynomial's derivative along one axis, 3 c + 9 (c_l . u) c - 3 u_a for
 // c = c_l,a, grouped as ((3 c) + (9 (c_l . u)) c) - 3 u_a.
@@ -108,42 +107,6 @@ __device__ inline T block_sum(T v, T *sm) {
 
 }  // namespace
 
-// The two reverse kernels work on 64 x 4 tiles of sites (one wave per tile row, 256 threads).
-// Everything a site reads from its two-belt neighbourhood (psi and rho of the forward state
-// for the force, psi_s Fbar_s and r_s Fbar_s for the gather) is first staged for the tile plus
-// a halo of two sites into LDS, so each neighbour value is fetched from memory once per tile
-// instead of once per reader.
-constexpr int ATX = 64, ATY = 4, AHX = ATX + 4, AHY = ATY + 4;
-
-// Site index of lattice point (x, y) for staging, any distance outside the lattice (x always
-// periodic; y periodic unless walls, where rows outside are not sites).
-template <bool WALLS>
-__device__ inline bool stage_site(int x, int y, int lx, int ly, size_t &i) {
-  if (WALLS && (y < 0 || y >= ly)) return false;
-  const int xi = ((x % lx) + lx) % lx;
-  const int yi = WALLS ? y : ((y % ly) + ly) % ly;
-  i = (size_t)yi * lx + xi;
-  return true;
-}
-
-// Per-tile sums of the nine sensitivities and loss terms: a wave reduction each, then the
-// four waves in order (one barrier), added to this tile's own row of running sums.
-__device__ inline void tile_accumulate(const double (&vals)[ADJ_N], double (*sm)[ADJ_N], double *row) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < ADJ_N; ++k) {
-    double v = vals[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (lane == 0) sm[wv][k] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x < ADJ_N) {
-    const int k = threadIdx.x;
-    row[k] += ((sm[0][k] + sm[1][k]) + sm[2][k]) + sm[3][k];
-  }
-}
-
 // The term of lambda common to every l at one site: the force's dependence on the
 // neighbours' psi (and rho), gathered with the forward stencil from A_s = psi_s Fbar_s and
 // B_s = r_s Fbar_s.  ab(which, s, dx, dy, bx, by) gives A_s (which = 0) or B_s (which = 1) at
@@ -161,7 +124,7 @@ __device__ inline void gather_corr(const AdjArgs &a, const AB &ab, const R (&rho
       R px, py, mx, my;
       ab(0, s, hx, hy, px, py);
       ab(0, s, -hx, -hy, mx, my);
-      acc += Kq[HQ[h]] * pair_dot<hx, hy>(px - mx, py - my);
+      acc = mad(Kq[HQ[h]], pair_dot<hx, hy>(px - mx, py - my), acc);
     });
     psib[s] += acc;
   }
@@ -174,7 +137,7 @@ __device__ inline void gather_corr(const AdjArgs &a, const AB &ab, const R (&rho
         R px, py, mx, my;
         ab(1, s, hx, hy, px, py);
         ab(1, s, -hx, -hy, mx, my);
-        acc += R(a.t[HQ[h]]) * pair_dot<hx, hy>(px - mx, py - my);
+        acc = mad(R(a.t[HQ[h]]), pair_dot<hx, hy>(px - mx, py - my), acc);
       });
       // B_s uses species s's own r (r_s Fbar_s); it lands on the other species' field
       if (a.cross_psi) psib[o] += R(a.gab) * acc;
@@ -184,391 +147,380 @@ __device__ inline void gather_corr(const AdjArgs &a, const AB &ab, const R (&rho
   for (int s = 0; s < NS; ++s) corr[s] = rbar[s] + psib[s] * R(a.psi0) * R(a.irho0) * exp(-rho[s] * R(a.irho0));
 }
 
-// Local part of the reverse step: force recompute, transposed streaming, the collision's
-// and velocity shift's adjoints; writes lam (the local part of lambda(t)), Fbar and per-tile
-// partial sums.
-//
-// GIN: the common term of lambda(t+1) is not read from memory but gathered here, for the tile
-// plus a halo of one, from A_s and B_s of step t + 1 (tile plus a halo of three) and the
-// densities of state t + 1: the separate gather of step t + 1 is not needed.
-template <typename R, int NS, bool WALLS, bool GIN>
-__global__ __launch_bounds__(256) void adj_local_kernel(AdjArgs a) {
-  AdjView<R> v(a);
-  constexpr int GX = ATX + 6, GY = ATY + 6;  // A_s, B_s of step t + 1 staged with a halo of three
-  __shared__ R sps[2][AHY][AHX];  // psi of the forward state, tile + halo
-  __shared__ R srh[2][AHY][AHX];  // rho
-  __shared__ R scn[2][ATY + 2][ATX + 2];  // corr of lambda(t+1), tile + halo of one
-  __shared__ R sab[GIN ? 2 : 1][GIN ? 4 : 1][GIN ? GY : 1][GIN ? GX : 1];
-  __shared__ double sm[4][ADJ_N];
-  const R *corr_next = static_cast<const R *>(a.corr_next);
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int x0 = blockIdx.x * ATX, y0 = blockIdx.y * ATY;
-  const bool live = x0 + tx < v.lx && y0 + ty < v.ly;
-  // memory accesses of lanes past the lattice's end use its last site (results discarded)
-  const int xs = min(x0 + tx, v.lx - 1), y = min(y0 + ty, v.ly - 1);
-  const size_t i = (size_t)y * v.lx + xs;
-  const R *lam_next = static_cast<const R *>(a.lam_next);
-  R *lamout = static_cast<R *>(a.lam);
-  R *fbar = static_cast<R *>(a.fbar);
+// An array of planes of n sites as one buffer range, planes in the uniform offset; WIDE (an array past
+// 4 GiB) takes a range per plane instead, spanning up to three (a reflected link reads the plane two
+// above or below its own).
+template <typename R, bool WIDE>
+struct Planes {
+  Rsrc all;
+  const void *base;
+  size_t n;
+  __device__ Planes(const void *p, int planes, size_t nn)
+      : all(make_rsrc(p, WIDE ? 0u : (uint32_t)planes * (uint32_t)(nn * sizeof(R)))), base(p), n(nn) {}
+  __device__ __forceinline__ Rsrc range(int pl) const {
+    return WIDE ? make_rsrc(static_cast<const R *>(base) + (size_t)pl * n, 3u * (uint32_t)(n * sizeof(R))) : all;
+  }
+  __device__ __forceinline__ uint32_t plane(int pl) const { return WIDE ? 0u : uni((uint32_t)pl * (uint32_t)(n * sizeof(R))); }
+  __device__ __forceinline__ R load(int pl, uint32_t off) const {
+    if constexpr (sizeof(R) == 8) return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(range(pl), off, plane(pl), 0));
+    else return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(range(pl), off, plane(pl), 0));
+  }
+  __device__ __forceinline__ void store(int pl, uint32_t off, R v) const {
+    if constexpr (sizeof(R) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), range(pl), off, plane(pl), 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), range(pl), off, plane(pl), 0);
+  }
+};
 
-  // Every load of the pass is issued before its first use, with no branch between the
-  // requests, so that they are in flight together (a wave holds one tile row and has nothing
-  // else to overlap them with).  First what the site reads outside the staged neighbourhood:
-  // j_s, and lambda(t+1) at the transposed-streaming sources.  The population leaving x along
-  // c_l arrives at x + c_l, or bounces back into opp(l) at x when x + c_l is a wall row; the
-  // bounce is folded into the address (y is the same across a wave, so is the bounce).
-  R rho[2], jx[2], jy[2], psi[2], Fx[2], Fy[2];
-  R lsrc[2][Q];
-  for (int s = 0; s < NS; ++s) {
-    jx[s] = v.fld(2, s, i);
-    jy[s] = v.fld(3, s, i);
-  }
-  each_index<Q>([&](auto L) {
-    constexpr int l = decltype(L)::value, cx = CXS[l], cy = CYS[l];
-    const int yn = y + cy;
-    const bool bounce = WALLS && cy != 0 && (yn < 0 || yn >= v.ly);
-    const size_t j = bounce ? i : (size_t)(WALLS ? yn : wrapx(yn, v.ly)) * v.lx + wrapx(xs + cx, v.lx);
-    const int pl = bounce ? OPPS[l] : l;
-    for (int s = 0; s < NS; ++s) lsrc[s][l] = lam_next[((size_t)s * Q + pl) * v.n + j];
-  });
-  // and, on the two wall rows, their pre-collision populations (the wall stress's source)
-  R xwr[2][Q];
-  if constexpr (WALLS) {
-    if (y == 0 || y == v.ly - 1) {
-      each_index<Q>([&](auto L) {
-        constexpr int l = decltype(L)::value, cy = CYS[l];
-        if constexpr (cy != 0)
-          for (int s = 0; s < NS; ++s) xwr[s][l] = R(a.x[((size_t)(s * Q + l) * 2 + (cy < 0 ? 0 : 1)) * v.lx + xs]);
-      });
+// Sites of a tile's local region (frame of two) and of the staged psi and rho (frame of four).
+template <int BX, int BY>
+struct AdjDims {
+  static constexpr int LX = BX + 4, LY = BY + 4, SX = BX + 8, SY = BY + 8, NL = LX * LY, NSTG = SX * SY;
+};
+template <typename R, int NS, int BX, int BY, int NT>
+constexpr size_t adj_lds_bytes() {
+  using D = AdjDims<BX, BY>;
+  constexpr size_t sites = (size_t)NS * (2 * D::NSTG + 4 * D::NL) * sizeof(R), sums = (size_t)ADJ_N * NT * sizeof(double);
+  return sites > sums ? sites : sums;
+}
+
+// One reverse step: lambda(t) from lambda(t+1) (a.lam_next) and the state of step t (a.fields, a.x), and
+// this step's sensitivities and loss terms, added to the tile's row of running sums.
+// The gather over A and B reads two sites past the tile, so the local part runs on the tile and a frame
+// of two and A and B never leave LDS: FP64 with two species moves 352 B per site (8 planes of fields, 18
+// of lambda each way) where a local and a gather pass moved 640.  Bound by FP64 and address
+// instructions at two waves per SIMD (236 registers), not by memory: 512 x 256 walled, FP64, two
+// species, beside the recompute stream: 23.0 us (4 TB/s) against 19.5 + 7.3 us for the two passes.  One
+// buffer range per array, planes in the uniform offset: a range per plane spilled scalar registers (728
+// of 2800 vector instructions only moved them; 25.9 us).
+template <typename R, int NS, bool WALLS, bool WIDE, int BX, int BY, int NT>
+__global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
+  using D = AdjDims<BX, BY>;
+  constexpr int M = (D::NL + NT - 1) / NT, MT = (BX * BY + NT - 1) / NT;  // rounds of the region and of the tile
+  R *const sps = reinterpret_cast<R *>(lb_smem);  // psi of the state [NS][SY][SX]
+  R *const srh = sps + NS * D::NSTG;              // rho
+  R *const sab = srh + NS * D::NSTG;              // A_s, B_s (x, y each) [NS][4][LY][LX]
+  const int tid = threadIdx.x, lx = a.lx, ly = a.ly;
+  const size_t n = (size_t)lx * ly;
+  const Planes<R, WIDE> fields(a.fields, 8, n), lnext(a.lam_next, NS == 2 ? 18 : 9, n), lout(a.lam, NS == 2 ? 18 : 9, n);
+  const int ntx = (lx + BX - 1) / BX;
+  const int by = (int)blockIdx.x / ntx, bx = (int)blockIdx.x - by * ntx;
+  const int x0 = bx * BX, y0 = by * BY;
+  const bool narrow = lx < 2 * D::SX || ly < 2 * D::SY;
+  auto wrap = [&](int v, int m) { return narrow ? ((v % m) + m) % m : wrapx(v, m); };
+  // Site i of the local region: the tile's sites first, then its frame (two rows below and above, two
+  // columns on either side), relative to the tile's first site.
+  auto site = [&](int i, int &sx, int &sy) {
+    sy = i / BX;
+    sx = i - sy * BX;
+    if (i >= BX * BY) {
+      const int q = i - BX * BY, t = q - 4 * D::LX, r = q / D::LX, c = t & 3;
+      sx = t < 0 ? q - r * D::LX - 2 : (c < 2 ? c - 2 : c + BX - 2);
+      sy = t < 0 ? (r < 2 ? r - 2 : r + BY - 2) : t >> 2;
     }
-  }
-  // Then the staging: psi and rho of the tile plus a halo of two, the common term of
-  // lambda(t+1) plus a halo of one.  Points that are not sites (past a wall, or past the end of
-  // the staging range) load site 0 and store the wall value or zero instead.
-  constexpr int NPS = (AHX * AHY + 255) / 256, NCN = ((ATX + 2) * (ATY + 2) + 255) / 256;
-  R vps[NPS][2], vrh[NPS][2], vcn[NCN][2];
-  bool inps[NPS], incn[NCN];
+  };
+
+  // psi and rho of the tile and a frame of four; past a wall the ghost values
+  constexpr int NST = (D::NSTG + NT - 1) / NT;
+  R vps[NST][NS], vrh[NST][NS];
+  bool solid[NST];
 #pragma unroll
-  for (int it = 0; it < NPS; ++it) {
-    const int k = threadIdx.x + it * 256, hx = k % AHX, hy = k / AHX;
-    size_t j = 0;
-    inps[it] = k < AHX * AHY && stage_site<WALLS>(x0 - 2 + hx, y0 - 2 + hy, v.lx, v.ly, j);
-    if (!inps[it]) j = 0;
+  for (int it = 0; it < NST; ++it) {
+    const int k = min(tid + it * NT, D::NSTG - 1), hy = k / D::SX, hx = k - hy * D::SX;
+    const int y = y0 + hy - 4;
+    solid[it] = WALLS && (y < 0 || y >= ly);
+    const int yc = WALLS ? min(max(y, 0), ly - 1) : wrap(y, ly);
+    const uint32_t off = (uint32_t)(((size_t)yc * lx + wrap(x0 + hx - 4, lx)) * sizeof(R));
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      vps[it][s] = v.fld(1, s, j);
-      vrh[it][s] = v.fld(0, s, j);
-    }
-  }
-  // with GIN: A_s, B_s of step t + 1 (tile + halo of three), and in vcn the densities of state
-  // t + 1 at the points where the common term is gathered; else the common term itself
-  constexpr int NAB = GIN ? (GX * GY + 255) / 256 : 1;
-  R vab[NAB][2][4];
-  bool inab[NAB];
-  const R *fbar_next = static_cast<const R *>(a.fbar_next);
-  const R *rho_next = static_cast<const R *>(a.fields_next);  // field 0 (rho) of state t + 1
-  if constexpr (GIN) {
-#pragma unroll
-    for (int it = 0; it < NAB; ++it) {
-      const int k = threadIdx.x + it * 256, hx = k % GX, hy = k / GX;
-      size_t j = 0;
-      inab[it] = k < GX * GY && stage_site<WALLS>(x0 - 3 + hx, y0 - 3 + hy, v.lx, v.ly, j);
-      if (!inab[it]) j = 0;
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) vab[it][s][c] = fbar_next[((size_t)s * 4 + c) * v.n + j];
+      vps[it][s] = fields.load(2 + s, off);
+      vrh[it][s] = fields.load(s, off);
     }
   }
 #pragma unroll
-  for (int it = 0; it < NCN; ++it) {
-    const int k = threadIdx.x + it * 256, hx = k % (ATX + 2), hy = k / (ATX + 2);
-    size_t j = 0;
-    incn[it] = k < (ATX + 2) * (ATY + 2) && stage_site<WALLS>(x0 - 1 + hx, y0 - 1 + hy, v.lx, v.ly, j);
-    if (!incn[it]) j = 0;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) vcn[it][s] = GIN ? rho_next[(size_t)s * v.n + j] : corr_next[(size_t)s * v.n + j];
-  }
-#pragma unroll
-  for (int it = 0; it < NPS; ++it) {
-    const int k = threadIdx.x + it * 256, hx = k % AHX, hy = k / AHX;
-    if (k < AHX * AHY) {
+  for (int it = 0; it < NST; ++it) {
+    const int k = tid + it * NT;
+    if (k < D::NSTG) {
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        sps[s][hy][hx] = inps[it] ? vps[it][s] : R(a.psi_w[s]);
-        srh[s][hy][hx] = inps[it] ? vrh[it][s] : R(a.rho_w[s]);
-      }
-    }
-  }
-  if constexpr (GIN) {
-#pragma unroll
-    for (int it = 0; it < NAB; ++it) {
-      const int k = threadIdx.x + it * 256, hx = k % GX, hy = k / GX;
-      if (k < GX * GY) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) sab[s][c][hy][hx] = inab[it] ? vab[it][s][c] : R(0);
-      }
-    }
-    __syncthreads();
-    // the common term of lambda(t+1) at the tile + halo of one, exactly as the gather pass
-    // computes it at those sites (zero at points that are not sites)
-#pragma unroll
-    for (int it = 0; it < NCN; ++it) {
-      const int k = threadIdx.x + it * 256, hx = k % (ATX + 2), hy = k / (ATX + 2);
-      if (k < (ATX + 2) * (ATY + 2)) {
-        auto ab = [&](int which, int s, int dx, int dy, R &bx, R &by) {
-          bx = sab[s][2 * which + 0][hy + 2 + dy][hx + 2 + dx];
-          by = sab[s][2 * which + 1][hy + 2 + dy][hx + 2 + dx];
-        };
-        R rn[2] = {vcn[it][0], NS == 2 ? vcn[it][NS - 1] : R(0)}, cn[2];
-        gather_corr<R, NS>(a, ab, rn, cn);
-#pragma unroll
-        for (int s = 0; s < NS; ++s) scn[s][hy][hx] = incn[it] ? cn[s] : R(0);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int it = 0; it < NCN; ++it) {
-      const int k = threadIdx.x + it * 256, hx = k % (ATX + 2), hy = k / (ATX + 2);
-      if (k < (ATX + 2) * (ATY + 2)) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) scn[s][hy][hx] = incn[it] ? vcn[it][s] : R(0);
+        sps[s * D::NSTG + k] = solid[it] ? R(a.psi_w[s]) : vps[it][s];
+        srh[s * D::NSTG + k] = solid[it] ? R(a.rho_w[s]) : vrh[it][s];
       }
     }
   }
   __syncthreads();
 
-  auto psi_at = [&](int s, int dx, int dy) -> R { return sps[s][ty + 2 + dy][tx + 2 + dx]; };
-  auto rho_at = [&](int s, int dx, int dy) -> R { return srh[s][ty + 2 + dy][tx + 2 + dx]; };
-
-  R s1x[2], s1y[2], s2x[2], s2y[2], xx[2], xy[2], self[2];
-  for (int s = 0; s < NS; ++s) {
-    rho[s] = rho_at(s, 0, 0);
-    psi[s] = psi_at(s, 0, 0);
-    // two-belt sums with the attractive (w) and repulsive (p) shell weights
-    R ax = 0, ay = 0, bx = 0, by = 0;
-    each_index<NHALF>([&](auto H) {
-      constexpr int h = decltype(H)::value, hx = HX[h], hy = HY[h];
-      const R d = psi_at(s, hx, hy) - psi_at(s, -hx, -hy);
-      const R wq = R(a.w[HQ[h]]), pq = R(a.p[HQ[h]]);
-      if constexpr (hx != 0) {
-        ax += cmul<hx>(wq) * d;
-        bx += cmul<hx>(pq) * d;
-      }
-      if constexpr (hy != 0) {
-        ay += cmul<hy>(wq) * d;
-        by += cmul<hy>(pq) * d;
-      }
-    });
-    s1x[s] = ax; s1y[s] = ay; s2x[s] = bx; s2y[s] = by;
-    Fx[s] = -psi[s] * (R(a.g1[s]) * ax + R(a.g2[s]) * bx);
-    Fy[s] = -psi[s] * (R(a.g1[s]) * ay + R(a.g2[s]) * by);
-    xx[s] = 0; xy[s] = 0; self[s] = 0;
-  }
-  if (NS == 2) {
-    for (int s = 0; s < 2; ++s) {
-      const int o = 1 - s;
-      R cx = 0, cy = 0;
-      each_index<4>([&](auto H) {
-        constexpr int h = decltype(H)::value, hx = HX[h], hy = HY[h];
-        const R d = a.cross_psi ? psi_at(o, hx, hy) - psi_at(o, -hx, -hy) : rho_at(o, hx, hy) - rho_at(o, -hx, -hy);
-        const R tq = R(a.t[HQ[h]]);
-        if constexpr (hx != 0) cx += cmul<hx>(tq) * d;
-        if constexpr (hy != 0) cy += cmul<hy>(tq) * d;
-      });
-      xx[s] = cx;
-      xy[s] = cy;
-      self[s] = a.cross_psi ? psi[s] : rho[s];
-      Fx[s] -= R(a.gab) * self[s] * cx;
-      Fy[s] -= R(a.gab) * self[s] * cy;
+  double vals[ADJ_N];
+#pragma unroll
+  for (int k = 0; k < ADJ_N; ++k) vals[k] = 0.0;
+  R lam[MT][NS][Q];  // the local part of lambda(t) at the tile's sites
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int i0 = tid + m * NT;
+    if ((m + 1) * NT > D::NL && i0 >= D::NL) continue;
+    int sx, sy;
+    site(i0, sx, sy);
+    const bool own = m < MT && i0 < BX * BY;
+    const int e = (sy + 2) * D::LX + sx + 2;
+    const int yr = y0 + sy;
+    if (WALLS && (yr < 0 || yr >= ly)) {  // not a site: nothing of it enters a gather
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sab[(s * 4 + c) * D::NL + e] = R(0);
+      continue;
     }
-  }
-  for (int s = 0; s < NS; ++s) {
-    Fx[s] += rho[s] * R(a.body[0]);
-    Fy[s] += rho[s] * R(a.body[1]);
-  }
+    const int x = wrap(x0 + sx, lx), y = WALLS ? yr : wrap(yr, ly);
+    const bool live = own && x0 + sx < lx && yr < ly;
+    const uint32_t pb = (uint32_t)(n * sizeof(R));
+    const uint32_t off = (uint32_t)(((size_t)y * lx + x) * sizeof(R));
 
-  // common velocity and the shifted equilibrium velocities
-  R nx = 0, ny = 0, den = 0, rtot = 0, mx = 0, my = 0;
-  for (int s = 0; s < NS; ++s) {
-    const R om = R(a.omega[s]);
-    nx += om * jx[s];
-    ny += om * jy[s];
-    den += om * rho[s];
-    rtot += rho[s];
-    mx += jx[s] + R(0.5) * Fx[s];
-    my += jy[s] + R(0.5) * Fy[s];
-  }
-  // reciprocals taken once per site: the rest of the pass multiplies
-  // 1 / lx comes from the host, rounded in R as a division here would round it
-  const R iden = R(1) / den, irt = R(1) / rtot, ilx = sizeof(R) == 8 ? R(a.ilx) : R(a.ilxf);
-  const R upx = nx * iden, upy = ny * iden;
-  const R urx = mx * irt;  // reported (half-force) velocity, x component
-  const R ilr = ilx * irt;  // 1 / (lx rho_tot)
-
-  // adjoint sources of this step's loss
-  const R cW = R(a.cW), cQ = R(a.cQ);
-  double loss_w = 0.0;  // summed over the wall row's links, divided by lx once
-  const double loss_q = live ? double(cQ * urx) / v.lx : 0.0;
-
-  R ubx = 0, uby = 0;  // adjoint of u'
-  R rbar[2], jbx[2], jby[2], fbx[2], fby[2];
-  R lp[2][Q];
-  for (int s = 0; s < NS; ++s) {
-    const R om = R(a.omega[s]), tau = R(a.tau[s]);
-    const R ir = R(1) / rho[s];
-    const R ux = upx + tau * Fx[s] * ir, uy = upy + tau * Fy[s] * ir;
-    const R uu = ux * ux + uy * uy;
-    R rb = 0, bx = 0, by = 0;
+    // lambda(t+1) where the populations leaving the site arrive: along c_l, or bounced back into
+    // opp(l) at the site where x + c_l lies past a wall (the range of each pair of links spans both)
+    R lsrc[NS][Q], jx[NS], jy[NS];
     each_index<Q>([&](auto L) {
-      constexpr int l = decltype(L)::value, cx = CXS[l], cy = CYS[l];
-      // lambda(t+1) at the transposed-streaming source (loaded above) and its common term
-      const bool bounce = WALLS && cy != 0 && (y + cy < 0 || y + cy >= v.ly);
-      R al = lsrc[s][l] + (bounce ? scn[s][ty + 1][tx + 1] : scn[s][ty + 1 + cy][tx + 1 + cx]);
-      R cu = R(0);  // c_l . u
-      if constexpr (cx != 0 && cy != 0) cu = cmul<cx>(ux) + cmul<cy>(uy);
-      else if constexpr (cx != 0) cu = cmul<cx>(ux);
-      else if constexpr (cy != 0) cu = cmul<cy>(uy);
-      const R wl = R(WD2Q9[l]);
-      const R poly = R(1) + R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu;  // f^eq_l / (W_l rho_s)
-      const R feq = wl * rho[s] * poly;
-      if constexpr (WALLS && cy != 0) {
-        if (y == (cy < 0 ? 0 : v.ly - 1)) {
-          // wall stress: d/dy_l of cW (1/2)(1/lx) (2 c_lx y_l - 6 W_l rho_w c_lx^2 U); the
-          // moving wall's share is constant
-          if constexpr (cx != 0) al += cmul<cx>(cW) * ilx;
-          // post-collision population leaving the wall row
-          const R yl = (R(1) - om) * xwr[s][l] + om * feq;
-          const R mw = R(3) * wl * R(a.rho_w[s]) * R(cx * cx) * R(cy < 0 ? a.u_wall[0] : a.u_wall[1]);
-          if (live) loss_w += double(cW * (R(cx) * yl - mw));
-        }
-      }
-      lp[s][l] = (R(1) - om) * al;
-      rb += om * al * wl * poly;  // omega al f^eq / rho
-      const R k = om * al * wl * rho[s];
-      bx += k * eq_grad<cx>(cu, ux);
-      by += k * eq_grad<cy>(cu, uy);
+      constexpr int l = decltype(L)::value, cx = CXS[l], cy = CYS[l], lo = l < OPPS[l] ? l : OPPS[l];
+      const int yn = y + cy;
+      const bool bounce = WALLS && cy != 0 && (yn < 0 || yn >= ly);
+      const uint32_t up = bounce ? (uint32_t)(OPPS[l] - lo) * pb : (uint32_t)(l - lo) * pb;  // walls: planes above lo
+      const uint32_t j = bounce ? off : (uint32_t)(((size_t)(WALLS ? yn : wrapx(yn, ly)) * lx + wrapx(x + cx, lx)) * sizeof(R));
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        lsrc[s][l] = WALLS && cy != 0 ? lnext.load(s * Q + lo, up + j) : lnext.load(s * Q + l, j);
     });
-    // u_s = u' + tau F_s / rho_s
-    ubx += bx;
-    uby += by;
-    fbx[s] = tau * bx * ir;
-    fby[s] = tau * by * ir;
-    rb -= tau * (Fx[s] * bx + Fy[s] * by) * (ir * ir);
-    rbar[s] = rb;
-  }
-  for (int s = 0; s < NS; ++s) {
-    const R om = R(a.omega[s]);
-    // u' = sum omega j / sum omega rho
-    jbx[s] = om * ubx * iden;
-    jby[s] = om * uby * iden;
-    rbar[s] -= om * (upx * ubx + upy * uby) * iden;
-    // flow rate: Q = (1/lx) sum (sum_s j_s + F_s / 2)_x / sum_s rho_s
-    jbx[s] += cQ * ilr;
-    fbx[s] += R(0.5) * cQ * ilr;
-    rbar[s] -= cQ * urx * ilr;
-  }
-  // force: F_s = -psi_s S_s - G_AB self_s X_s + rho_s g
-  double dg1[2] = {0, 0}, dg2[2] = {0, 0}, dgab = 0, dgx = 0, dgy = 0;
-  R psib[2] = {0, 0};
-  for (int s = 0; s < NS; ++s) {
-    const R Sx = R(a.g1[s]) * s1x[s] + R(a.g2[s]) * s2x[s], Sy = R(a.g1[s]) * s1y[s] + R(a.g2[s]) * s2y[s];
-    psib[s] -= fbx[s] * Sx + fby[s] * Sy;
-    rbar[s] += fbx[s] * R(a.body[0]) + fby[s] * R(a.body[1]);
-    if (NS == 2) {
-      const R cb = -R(a.gab) * (fbx[s] * xx[s] + fby[s] * xy[s]);
-      if (a.cross_psi) psib[s] += cb;
-      else rbar[s] += cb;
-    }
-    if (live) {
-      dg1[s] = double(-psi[s] * (fbx[s] * s1x[s] + fby[s] * s1y[s]));
-      dg2[s] = double(-psi[s] * (fbx[s] * s2x[s] + fby[s] * s2y[s]));
-      dgab += double(-self[s] * (fbx[s] * xx[s] + fby[s] * xy[s]));
-      dgx += double(fbx[s] * rho[s]);
-      dgy += double(fby[s] * rho[s]);
-    }
-    // psi'(rho) = (psi0 / rho0) exp(-rho / rho0)
-    rbar[s] += psib[s] * R(a.psi0) * R(a.irho0) * exp(-rho[s] * R(a.irho0));
-  }
-  if (live) {
+#pragma unroll
     for (int s = 0; s < NS; ++s) {
+      jx[s] = fields.load(4 + s, off);
+      jy[s] = fields.load(6 + s, off);
+    }
+    // and, on the two wall rows, their pre-collision populations (the wall stress's source)
+    R xwr[NS][Q];
+    if constexpr (WALLS) {
+      if (y == 0 || y == ly - 1) {
+        each_index<Q>([&](auto L) {
+          constexpr int l = decltype(L)::value, cy = CYS[l];
+          if constexpr (cy != 0)
+            for (int s = 0; s < NS; ++s) xwr[s][l] = R(a.x[((size_t)(s * Q + l) * 2 + (cy < 0 ? 0 : 1)) * lx + x]);
+        });
+      }
+    }
+
+    const R *const pp = sps + (sy + 4) * D::SX + sx + 4, *const rr = srh + (sy + 4) * D::SX + sx + 4;
+    auto psi_at = [&](int s, int dx, int dy) -> R { return pp[s * D::NSTG + dy * D::SX + dx]; };
+    auto rho_at = [&](int s, int dx, int dy) -> R { return rr[s * D::NSTG + dy * D::SX + dx]; };
+
+    R rho[2], psi[2], Fx[2], Fy[2];
+    R s1x[2], s1y[2], s2x[2], s2y[2], xx[2], xy[2], self[2];
+    for (int s = 0; s < NS; ++s) {
+      rho[s] = rho_at(s, 0, 0);
+      psi[s] = psi_at(s, 0, 0);
+      // two-belt sums with the attractive (w) and repulsive (p) shell weights
+      R ax = 0, ay = 0, bx = 0, by = 0;
+      each_index<NHALF>([&](auto H) {
+        constexpr int h = decltype(H)::value, hx = HX[h], hy = HY[h];
+        const R d = psi_at(s, hx, hy) - psi_at(s, -hx, -hy);
+        const R wq = R(a.w[HQ[h]]), pq = R(a.p[HQ[h]]);
+        if constexpr (hx != 0) {
+          ax = mad(cmul<hx>(wq), d, ax);
+          bx = mad(cmul<hx>(pq), d, bx);
+        }
+        if constexpr (hy != 0) {
+          ay = mad(cmul<hy>(wq), d, ay);
+          by = mad(cmul<hy>(pq), d, by);
+        }
+      });
+      s1x[s] = ax; s1y[s] = ay; s2x[s] = bx; s2y[s] = by;
+      Fx[s] = -psi[s] * (R(a.g1[s]) * ax + R(a.g2[s]) * bx);
+      Fy[s] = -psi[s] * (R(a.g1[s]) * ay + R(a.g2[s]) * by);
+      xx[s] = 0; xy[s] = 0; self[s] = 0;
+    }
+    if (NS == 2) {
+      for (int s = 0; s < 2; ++s) {
+        const int o = 1 - s;
+        R cx = 0, cy = 0;
+        each_index<4>([&](auto H) {
+          constexpr int h = decltype(H)::value, hx = HX[h], hy = HY[h];
+          const R d = a.cross_psi ? psi_at(o, hx, hy) - psi_at(o, -hx, -hy) : rho_at(o, hx, hy) - rho_at(o, -hx, -hy);
+          const R tq = R(a.t[HQ[h]]);
+          if constexpr (hx != 0) cx = mad(cmul<hx>(tq), d, cx);
+          if constexpr (hy != 0) cy = mad(cmul<hy>(tq), d, cy);
+        });
+        xx[s] = cx;
+        xy[s] = cy;
+        self[s] = a.cross_psi ? psi[s] : rho[s];
+        Fx[s] -= R(a.gab) * self[s] * cx;
+        Fy[s] -= R(a.gab) * self[s] * cy;
+      }
+    }
+    for (int s = 0; s < NS; ++s) {
+      Fx[s] = mad(rho[s], R(a.body[0]), Fx[s]);
+      Fy[s] = mad(rho[s], R(a.body[1]), Fy[s]);
+    }
+
+    // common velocity and the shifted equilibrium velocities
+    R nx = 0, ny = 0, den = 0, rtot = 0, mx = 0, my = 0;
+    for (int s = 0; s < NS; ++s) {
+      const R om = R(a.omega[s]);
+      nx = mad(om, jx[s], nx);
+      ny = mad(om, jy[s], ny);
+      den = mad(om, rho[s], den);
+      rtot += rho[s];
+      mx += mad(R(0.5), Fx[s], jx[s]);
+      my += mad(R(0.5), Fy[s], jy[s]);
+    }
+    // reciprocals taken once per site: the rest of the pass multiplies
+    // 1 / lx comes from the host, rounded in R as a division here would round it
+    const R iden = R(1) / den, irt = R(1) / rtot, ilx = sizeof(R) == 8 ? R(a.ilx) : R(a.ilxf);
+    const R upx = nx * iden, upy = ny * iden;
+    const R urx = mx * irt;  // reported (half-force) velocity, x component
+    const R ilr = ilx * irt;  // 1 / (lx rho_tot)
+
+    // adjoint sources of this step's loss
+    const R cW = R(a.cW), cQ = R(a.cQ);
+    double loss_w = 0.0;
+    const double loss_q = live ? double(cQ * urx) : 0.0;  // divided by lx with the tile's sum
+
+    R ubx = 0, uby = 0;  // adjoint of u'
+    R rbar[2], jbx[2], jby[2], fbx[2], fby[2];
+    R lp[2][Q];
+    for (int s = 0; s < NS; ++s) {
+      const R om = R(a.omega[s]), tau = R(a.tau[s]);
+      const R ir = R(1) / rho[s];
+      const R ux = upx + tau * Fx[s] * ir, uy = upy + tau * Fy[s] * ir;
+      const R uu = ux * ux + uy * uy;
+      R rb = 0, bx = 0, by = 0;
       each_index<Q>([&](auto L) {
         constexpr int l = decltype(L)::value, cx = CXS[l], cy = CYS[l];
-        R lam_l = lp[s][l] + rbar[s];
-        if constexpr (cx != 0) lam_l += cmul<cx>(jbx[s]);
-        if constexpr (cy != 0) lam_l += cmul<cy>(jby[s]);
-        lamout[((size_t)s * Q + l) * v.n + i] = lam_l;
+        R al = lsrc[s][l];
+        R cu = R(0);  // c_l . u
+        if constexpr (cx != 0 && cy != 0) cu = cmul<cx>(ux) + cmul<cy>(uy);
+        else if constexpr (cx != 0) cu = cmul<cx>(ux);
+        else if constexpr (cy != 0) cu = cmul<cy>(uy);
+        const R wl = R(WD2Q9[l]);
+        const R poly = R(1) + R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu;  // f^eq_l / (W_l rho_s)
+        const R feq = wl * rho[s] * poly;
+        if constexpr (WALLS && cy != 0) {
+          if (y == (cy < 0 ? 0 : ly - 1)) {
+            // wall stress: d/dy_l of cW (1/2)(1/lx) (2 c_lx y_l - 6 W_l rho_w c_lx^2 U); the
+            // moving wall's share is constant
+            if constexpr (cx != 0) al += cmul<cx>(cW) * ilx;
+            // post-collision population leaving the wall row
+            const R yl = (R(1) - om) * xwr[s][l] + om * feq;
+            const R mw = R(3) * wl * R(a.rho_w[s]) * R(cx * cx) * R(cy < 0 ? a.u_wall[0] : a.u_wall[1]);
+            if (live) loss_w += double(cW * (R(cx) * yl - mw));
+          }
+        }
+        lp[s][l] = (R(1) - om) * al;
+        rb = mad(om * al * wl, poly, rb);  // omega al f^eq / rho
+        const R k = om * al * wl * rho[s];
+        bx = mad(k, eq_grad<cx>(cu, ux), bx);
+        by = mad(k, eq_grad<cy>(cu, uy), by);
       });
-      // what the gather needs of this site: A_s = psi_s Fbar_s, B_s = r_s Fbar_s
-      fbar[((size_t)s * 4 + 0) * v.n + i] = psi[s] * fbx[s];
-      fbar[((size_t)s * 4 + 1) * v.n + i] = psi[s] * fby[s];
-      fbar[((size_t)s * 4 + 2) * v.n + i] = self[s] * fbx[s];
-      fbar[((size_t)s * 4 + 3) * v.n + i] = self[s] * fby[s];
+      // u_s = u' + tau F_s / rho_s
+      ubx += bx;
+      uby += by;
+      fbx[s] = tau * bx * ir;
+      fby[s] = tau * by * ir;
+      rb -= tau * (Fx[s] * bx + Fy[s] * by) * (ir * ir);
+      rbar[s] = rb;
+    }
+    for (int s = 0; s < NS; ++s) {
+      const R om = R(a.omega[s]);
+      // u' = sum omega j / sum omega rho
+      jbx[s] = om * ubx * iden;
+      jby[s] = om * uby * iden;
+      rbar[s] -= om * (upx * ubx + upy * uby) * iden;
+      // flow rate: Q = (1/lx) sum (sum_s j_s + F_s / 2)_x / sum_s rho_s
+      jbx[s] += cQ * ilr;
+      fbx[s] += R(0.5) * cQ * ilr;
+      rbar[s] -= cQ * urx * ilr;
+    }
+    // force: F_s = -psi_s S_s - G_AB self_s X_s + rho_s g
+    double dg1[2] = {0, 0}, dg2[2] = {0, 0}, dgab = 0, dgx = 0, dgy = 0;
+    R psib[2] = {0, 0};
+    for (int s = 0; s < NS; ++s) {
+      const R Sx = R(a.g1[s]) * s1x[s] + R(a.g2[s]) * s2x[s], Sy = R(a.g1[s]) * s1y[s] + R(a.g2[s]) * s2y[s];
+      psib[s] -= fbx[s] * Sx + fby[s] * Sy;
+      rbar[s] += fbx[s] * R(a.body[0]) + fby[s] * R(a.body[1]);
+      if (NS == 2) {
+        const R cb = -R(a.gab) * (fbx[s] * xx[s] + fby[s] * xy[s]);
+        if (a.cross_psi) psib[s] += cb;
+        else rbar[s] += cb;
+      }
+      if (live) {
+        dg1[s] = double(-psi[s] * (fbx[s] * s1x[s] + fby[s] * s1y[s]));
+        dg2[s] = double(-psi[s] * (fbx[s] * s2x[s] + fby[s] * s2y[s]));
+        dgab += double(-self[s] * (fbx[s] * xx[s] + fby[s] * xy[s]));
+        dgx += double(fbx[s] * rho[s]);
+        dgy += double(fby[s] * rho[s]);
+      }
+      // psi'(rho) = (psi0 / rho0) exp(-rho / rho0)
+      rbar[s] += psib[s] * R(a.psi0) * R(a.irho0) * exp(-rho[s] * R(a.irho0));
+    }
+    if (own) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        each_index<Q>([&](auto L) {
+          constexpr int l = decltype(L)::value, cx = CXS[l], cy = CYS[l];
+          R lam_l = lp[s][l] + rbar[s];
+          if constexpr (cx != 0) lam_l += cmul<cx>(jbx[s]);
+          if constexpr (cy != 0) lam_l += cmul<cy>(jby[s]);
+          lam[m < MT ? m : 0][s][l] = lam_l;
+        });
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      sab[(s * 4 + 0) * D::NL + e] = psi[s] * fbx[s];
+      sab[(s * 4 + 1) * D::NL + e] = psi[s] * fby[s];
+      sab[(s * 4 + 2) * D::NL + e] = self[s] * fbx[s];
+      sab[(s * 4 + 3) * D::NL + e] = self[s] * fby[s];
+    }
+    if (live) {
+      const double v[ADJ_N] = {dg1[0], dg1[1], dg2[0], dg2[1], dgab, dgx, dgy, loss_w, loss_q};
+#pragma unroll
+      for (int k = 0; k < ADJ_N; ++k) vals[k] += v[k];
     }
   }
-  // per-tile partial sums, accumulated over the reverse steps in each tile's own row
-  // (fixed order: waves, then steps, then tiles in the final pass)
-  if (WALLS) loss_w /= v.lx;
-  double vals[ADJ_N] = {dg1[0], dg1[1], dg2[0], dg2[1], dgab, dgx, dgy, loss_w, loss_q};
-  const size_t blk = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-  tile_accumulate(vals, sm, a.partials + blk * ADJ_N);
-}
+  __syncthreads();
 
-// Nonlocal part: the force's dependence on the neighbours' psi (and rho), gathered with the
-// forward stencil; writes corr, the term of lambda(t) common to every l (the next reverse step
-// adds it to lam as it reads lambda).
-template <typename R, int NS, bool WALLS>
-__global__ __launch_bounds__(256) void adj_gather_kernel(AdjArgs a) {
-  AdjView<R> v(a);
-  // per species: psi_s Fbar_s (x, y) and r_s Fbar_s (x, y) of tile + halo, zero off the lattice
-  __shared__ R sab[2][4][AHY][AHX];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int x0 = blockIdx.x * ATX, y0 = blockIdx.y * ATY;
-  const R *fbar = static_cast<const R *>(a.fbar);
-  const int x = x0 + tx, y = y0 + ty;
-  const bool live = x < v.lx && y < v.ly;
-  const size_t i = live ? (size_t)y * v.lx + x : 0;
-  // every load is issued before the barrier, together: rho_s of this site, then the staged
-  // values (points that are not sites load site 0 and store zero)
-  R rho[2];
-  for (int s = 0; s < NS; ++s) rho[s] = v.fld(0, s, i);
-  constexpr int NST = (AHX * AHY + 255) / 256;
-  R vab[NST][2][4];
-  bool in[NST];
+  // the term of lambda(t) common to every l, gathered from the tile and its frame
 #pragma unroll
-  for (int it = 0; it < NST; ++it) {
-    const int k = threadIdx.x + it * 256, hx = k % AHX, hy = k / AHX;
-    size_t j = 0;
-    in[it] = k < AHX * AHY && stage_site<WALLS>(x0 - 2 + hx, y0 - 2 + hy, v.lx, v.ly, j);
-    if (!in[it]) j = 0;
+  for (int m = 0; m < MT; ++m) {
+    const int i0 = tid + m * NT, sy = i0 / BX, sx = i0 - sy * BX;
+    if (i0 >= BX * BY || x0 + sx >= lx || y0 + sy >= ly) continue;
+    const R *const q = sab + (sy + 2) * D::LX + sx + 2;
+    auto ab = [&](int which, int s, int dx, int dy, R &vx, R &vy) {
+      vx = q[(s * 4 + 2 * which + 0) * D::NL + dy * D::LX + dx];
+      vy = q[(s * 4 + 2 * which + 1) * D::NL + dy * D::LX + dx];
+    };
+    R rho[2] = {0, 0}, corr[2];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) rho[s] = srh[s * D::NSTG + (sy + 4) * D::SX + sx + 4];
+    gather_corr<R, NS>(a, ab, rho, corr);
+    const uint32_t off = (uint32_t)(((size_t)(y0 + sy) * lx + x0 + sx) * sizeof(R));
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) vab[it][s][c] = fbar[((size_t)s * 4 + c) * v.n + j];
+      for (int l = 0; l < Q; ++l)
+        lout.store(s * Q + l, off, lam[m][s][l] + corr[s]);
   }
-#pragma unroll
-  for (int it = 0; it < NST; ++it) {
-    const int k = threadIdx.x + it * 256, hx = k % AHX, hy = k / AHX;
-    if (k < AHX * AHY) {
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sab[s][c][hy][hx] = in[it] ? vab[it][s][c] : R(0);
-    }
-  }
+
+  // the tile's sums, through LDS: wave w sums the terms w, w + waves, ... over the threads, in a fixed
+  // order, and adds them to the tile's row (a shuffle tree of every term in every wave took as
+  // many LDS operations as the update)
   __syncthreads();
-  if (!live) return;  // after the kernel's only barrier
-  R *corr = static_cast<R *>(a.corr);
-  // A_s = psi_s Fbar_s (which = 0) or B_s = r_s Fbar_s (which = 1) at a neighbour
-  auto ab = [&](int which, int s, int dx, int dy, R &bx, R &by) {
-    bx = sab[s][2 * which + 0][ty + 2 + dy][tx + 2 + dx];
-    by = sab[s][2 * which + 1][ty + 2 + dy][tx + 2 + dx];
-  };
-  R cn[2];
-  gather_corr<R, NS>(a, ab, rho, cn);
-  for (int s = 0; s < NS; ++s) corr[(size_t)s * v.n + i] = cn[s];
+  double *const sm = reinterpret_cast<double *>(lb_smem);  // [ADJ_N][NT]
+#pragma unroll
+  for (int k = 0; k < ADJ_N; ++k) sm[k * NT + tid] = vals[k];
+  __syncthreads();
+  const int lane = tid & 63;
+  for (int k = tid >> 6; k < ADJ_N; k += NT / 64) {
+    double v = sm[k * NT + lane];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) v += sm[k * NT + w * 64 + lane];
+    v = wave_sum(v);
+    if (k == ADJ_LW || k == ADJ_LQ) v /= lx;
+    if (lane == 0) a.partials[(size_t)blockIdx.x * ADJ_N + k] += v;
+  }
 }
 
 // acc[k] += sum over blocks of partials[block][k], in block order (deterministic).
@@ -587,27 +539,44 @@ __global__ void zero_kernel(uint32_t *p, size_t n) {
   if (i < n) p[i] = 0u;
 }
 
-int adj_blocks(int lx, int ly) { return ((lx + ATX - 1) / ATX) * ((ly + ATY - 1) / ATY); }
+// Tile of the reverse step: the largest that gives every compute unit one, as the frame it adds to
+// the local part shrinks with its size.
+static int adj_shape(int lx, int ly) {
+  auto tiles = [&](int bx, int by) { return (long long)((lx + bx - 1) / bx) * ((ly + by - 1) / by); };
+  return tiles(32, 16) >= 256 ? 2 : (tiles(16, 16) >= 256 ? 1 : 0);
+}
 
-template <typename R, int NS, bool WALLS>
-static hipError_t adj_step_t(const AdjArgs &a, int gin, int gout, hipStream_t st) {
-  const dim3 tiles((a.lx + ATX - 1) / ATX, (a.ly + ATY - 1) / ATY), block(ATX * ATY);
-  if (gin) hipLaunchKernelGGL((adj_local_kernel<R, NS, WALLS, true>), tiles, block, 0, st, a);
-  else hipLaunchKernelGGL((adj_local_kernel<R, NS, WALLS, false>), tiles, block, 0, st, a);
-  if (gout) hipLaunchKernelGGL((adj_gather_kernel<R, NS, WALLS>), tiles, block, 0, st, a);
+int adj_blocks(int lx, int ly) {
+  const int k = adj_shape(lx, ly), bx = k == 2 ? 32 : 16, by = k == 0 ? 8 : 16;
+  return ((lx + bx - 1) / bx) * ((ly + by - 1) / by);
+}
+
+template <typename R, int NS, bool WALLS, bool WIDE, int BX, int BY, int NT>
+static hipError_t adj_step_k(const AdjArgs &a, hipStream_t st) {
+  hipLaunchKernelGGL((adj_step_kernel<R, NS, WALLS, WIDE, BX, BY, NT>), dim3((unsigned)adj_blocks(a.lx, a.ly)), dim3(NT),
+                     (adj_lds_bytes<R, NS, BX, BY, NT>()), st, a);
   return hipGetLastError();
 }
 
-template <typename R>
-static hipError_t adj_step_r(int ns, int walls, const AdjArgs &a, int gin, int gout, hipStream_t st) {
-  if (ns == 1) return walls ? adj_step_t<R, 1, true>(a, gin, gout, st) : adj_step_t<R, 1, false>(a, gin, gout, st);
-  return walls ? adj_step_t<R, 2, true>(a, gin, gout, st) : adj_step_t<R, 2, false>(a, gin, gout, st);
+template <typename R, int NS, bool WALLS>
+static hipError_t adj_step_t(const AdjArgs &a, hipStream_t st) {
+  if ((size_t)a.lx * a.ly * 9 * NS * sizeof(R) >= ((size_t)1 << 32))  // always the widest tile
+    return adj_step_k<R, NS, WALLS, true, 32, 16, 512>(a, st);
+  switch (adj_shape(a.lx, a.ly)) {
+    case 0: return adj_step_k<R, NS, WALLS, false, 16, 8, 256>(a, st);
+    case 1: return adj_step_k<R, NS, WALLS, false, 16, 16, 448>(a, st);
+  }
+  return adj_step_k<R, NS, WALLS, false, 32, 16, 512>(a, st);
 }
 
-hipError_t launch_adjoint_step(int fp64, int ns, int walls, const AdjArgs &a, int gather_in, int gather_out,
-                               hipStream_t st) {
-  return fp64 ? adj_step_r<double>(ns, walls, a, gather_in, gather_out, st)
-              : adj_step_r<float>(ns, walls, a, gather_in, gather_out, st);
+template <typename R>
+static hipError_t adj_step_r(int ns, int walls, const AdjArgs &a, hipStream_t st) {
+  if (ns == 1) return walls ? adj_step_t<R, 1, true>(a, st) : adj_step_t<R, 1, false>(a, st);
+  return walls ? adj_step_t<R, 2, true>(a, st) : adj_step_t<R, 2, false>(a, st);
+}
+
+hipError_t launch_adjoint_step(int fp64, int ns, int walls, const AdjArgs &a, hipStream_t st) {
+  return fp64 ? adj_step_r<double>(ns, walls, a, st) : adj_step_r<float>(ns, walls, a, st);
 }
 
 hipError_t launch_adjoint_reduce(const double *partials, int lx, int ly, double *acc, hipStream_t st) {

@@ -122,28 +122,6 @@ hipError_t launch_plain_step(const lb_ctx *c, int from, hipStream_t st, uint32_t
   return launch_step(step_mode(c), c->lat.n_species, c->lat.walls, WHAT_STEP, c->tx, nb, a, st);
 }
 
-// One plain step from buffer `from` that also writes what the adjoint's reverse step reads of
-// that state (as launch_checkpoint_fields_from does): fields (FP64 if fp64) and the FP64
-// populations of the rows next to the walls into dst.  Bitwise the same step and the same
-// fields as the two separate launches, with one pass over the state.  sy > 0 overrides the
-// context's segment height (any height gives bitwise the same step).
-hipError_t launch_plain_step_fields(const lb_ctx *c, int from, void *dst, void *fields, int fp64, hipStream_t st,
-                                    int sy = 0) {
-  if (sy <= 0) sy = c->sy;
-  int nseg = 0;
-  const int nb = grid_blocks(c, c->tx, sy, &nseg);
-  StepArgs a;
-  fill_step_args(c, a);
-  a.sy = sy;
-  a.nseg = nseg;
-  a.src = c->pop[from];
-  a.dst = c->pop[from ^ 1];
-  a.out_rho = fields;
-  a.out_u = dst;
-  return launch_step(step_mode(c), c->lat.n_species, c->lat.walls, fp64 ? WHAT_STEP_FIELDS : WHAT_STEP_FIELDS32, c->tx,
-                     nb, a, st);
-}
-
 // Segments of the two-step kernel: rows per segment (the context's choice, or the default that
 // makes the whole grid resident at once) and the grid size.
 int grid2(const lb_ctx *c, int *sy_out, int *nseg_out) {
@@ -179,9 +157,8 @@ bool pairs_on(const lb_ctx *c) {
 
 // Whether plain and reducing steps run in tiles (lb_tile.hpp), several per launch; else in marched
 // rows of the launch shape that lb_set_tile or the autotuner set, or in the pairs that
-// lb_set_two_step forces.  The tile launch finds a workgroup's tile by a multiplication that is
-// exact while tiles per row times tiles stay below 2^32 (any lattice of fewer than 30 M columns).
-bool tiles_on(const lb_ctx *c);
+// lb_set_two_step forces.
+bool tiles_on(const lb_ctx *c) { return !c->shape_set && c->two_step != LB_TWO_STEP_ON; }
 
 // Tile shape: the smallest whose tiles fit the compute units one each.  A launch lasts as long as
 // its busiest compute unit, so up to that point a larger tile only adds work, and beyond it a
@@ -197,13 +174,6 @@ int tile_shape(const lb_ctx *c) {
 
 int tile_blocks(const lb_ctx *c, int shape) {
   return ((c->lat.lx + kTileX[shape] - 1) / kTileX[shape]) * ((c->lat.ly + kTileY[shape] - 1) / kTileY[shape]);
-}
-
-bool tiles_on(const lb_ctx *c) {
-  if (c->shape_set || c->two_step == LB_TWO_STEP_ON) return false;
-  const int s = kTileShapes - 1;
-  const uint64_t ntx = (uint64_t)((c->lat.lx + kTileX[s] - 1) / kTileX[s]);
-  return ntx * ntx * (uint64_t)((c->lat.ly + kTileY[s] - 1) / kTileY[s]) < (1ull << 32);
 }
 
 // Steps of the next tile launch with n left: as many as the shape takes, but no single step at
@@ -231,6 +201,25 @@ hipError_t launch_tile_steps(const lb_ctx *c, int shape, int n, int from, int wh
   TileOpts o;
   o.red_mask = red_mask;
   return launch_tile(step_mode(c), c->lat.n_species, c->lat.walls, what, shape, n, a, o, st);
+}
+
+// n = 1 or 2 plain steps from buffer `from` that also write what the adjoint's reverse step reads of
+// the states stepped from (as launch_checkpoint_fields_from does): fields (FP64 if fp64) and the
+// FP64 populations of the rows next to the walls into xw, the second state's fb and xb bytes
+// further on.  Bitwise the same steps and the same fields as the separate passes.
+hipError_t launch_fields_steps(const lb_ctx *c, int n, int from, void *xw, size_t xb, void *fields, size_t fb, int fp64,
+                               hipStream_t st) {
+  StepArgs a;
+  fill_step_args(c, a);
+  a.src = c->pop[from];
+  a.dst = c->pop[from ^ 1];
+  a.out_rho = fields;
+  a.out_u = xw;
+  TileOpts o;
+  o.fields_stride = fb;
+  o.xw_stride = xb;
+  return launch_tile(c->lat.storage, c->lat.n_species, c->lat.walls, fp64 ? WHAT_STEP_FIELDS : WHAT_STEP_FIELDS32,
+                     tile_shape(c), n, a, o, st);
 }
 
 // Two plain steps in one launch (time steps t_step and t_step + 1) from buffer `from` to the
@@ -926,8 +915,7 @@ struct AdjLayout {
   int64_t per = 1;   // states per segment buffer
   int nbuf = 1;      // segment buffers
   size_t s64 = 0, lamb = 0, nsite = 0, fb = 0, xw = 0;
-  size_t corrb = 0, fbb = 0;
-  size_t ckpt = 0, seg = 0, fin = 0, lam0 = 0, lam1 = 0, corr0 = 0, corr1 = 0, fields = 0, fbar = 0, partials = 0, acc = 0;
+  size_t ckpt = 0, seg = 0, fin = 0, lam0 = 0, lam1 = 0, fields = 0, partials = 0, acc = 0;
   size_t total = 0;
 };
 
@@ -962,12 +950,7 @@ AdjLayout adjoint_layout(const lb_ctx *c, int64_t T, int32_t every, int32_t flag
   L.fin = o; o += L.all ? 0 : align256(lb_pop_bytes(&c->lat));
   L.lam0 = o; o += L.lamb;
   L.lam1 = o; o += L.lamb;
-  L.corrb = align256((size_t)ns * L.nsite * rs);
-  L.corr0 = o; o += L.corrb;
-  L.corr1 = o; o += L.corrb;
   L.fields = o; o += (size_t)nstate * L.fb;  // one set per state of a segment (of the run when all)
-  L.fbb = align256(8 * L.nsite * rs);
-  L.fbar = o; o += 2 * L.fbb;  // ping-pong: a reverse step reads the next step's and writes its own
   L.partials = o; o += align256((size_t)adj_blocks(c->lat.lx, c->lat.ly) * ADJ_N * 8);
   L.acc = o; o += align256(ADJ_N * 8);
   L.total = o;
@@ -1042,11 +1025,12 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   hipError_t e = hipSuccess;
   if (L.all) {
     // forward pass keeping what the reverse step reads of every state: no recompute later
-    for (int64_t t = 0; t < T && e == hipSuccess; ++t) {
-      e = launch_plain_step_fields(c, c->cur, ws + L.seg + (size_t)t * L.xw, ws + L.fields + (size_t)t * L.fb, fp64,
-                                   c->stream);
+    for (int64_t t = 0; t < T && e == hipSuccess; t += 2) {
+      const int n = (int)std::min<int64_t>(2, T - t);
+      e = launch_fields_steps(c, n, c->cur, ws + L.seg + (size_t)t * L.xw, L.xw, ws + L.fields + (size_t)t * L.fb, L.fb,
+                              fp64, c->stream);
       c->cur ^= 1;
-      ++c->t;
+      c->t += n;
     }
     if (e != hipSuccess) return done(hip_fail(c, e, "adjoint forward pass"));
   } else {
@@ -1062,7 +1046,6 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   const size_t popb = lb_pop_bytes(&c->lat);
   if (!L.all) e = hipMemcpyAsync(ws + L.fin, c->pop[cur_final], popb, hipMemcpyDeviceToDevice, c->stream);
   if (e == hipSuccess) e = launch_zero(ws + L.lam1, L.lamb, c->stream);
-  if (e == hipSuccess) e = launch_zero(ws + L.corr1, L.corrb, c->stream);
   if (e == hipSuccess) e = launch_zero(ws + L.acc, ADJ_N * 8, c->stream);
   if (e == hipSuccess)
     e = launch_zero(ws + L.partials, (size_t)adj_blocks(c->lat.lx, c->lat.ly) * ADJ_N * 8, c->stream);
@@ -1072,57 +1055,31 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   AdjArgs a = adjoint_args(c, loss_weights[0], loss_weights[1], T);
   a.partials = reinterpret_cast<double *>(ws + L.partials);
   double *acc = reinterpret_cast<double *>(ws + L.acc);
-  // lambda(t+1) is lam_buf[q] + corr_buf[q], lambda(t) lam_buf[q ^ 1] + corr_buf[q ^ 1]
+  // lambda(t+1) is lam_buf[q], lambda(t) lam_buf[q ^ 1]
   char *lam_buf[2] = {ws + L.lam1, ws + L.lam0};
-  char *corr_buf[2] = {ws + L.corr1, ws + L.corr0};
-  // psi_s Fbar_s and r_s Fbar_s of step t + 1 in fbar_buf[q], of step t in fbar_buf[q ^ 1]
-  char *fbar_buf[2] = {ws + L.fbar, ws + L.fbar + L.fbb};
   int q = 0;
   // what the reverse step reads of state jj of segment buffer b
   auto seg_x = [&](int b, int jj) { return ws + L.seg + ((size_t)b * L.per + jj) * L.xw; };
   auto seg_f = [&](int b, int jj) { return ws + L.fields + ((size_t)b * L.per + jj) * L.fb; };
-  // A recompute that runs beside the reverse sweep takes at most one workgroup per CU (taller
-  // segments), leaving the rest of the chip to the reverse kernels; measured 5% faster on the
-  // 512 x 256 channel than the resident grid of the context's launch shape.
-  int rsy = c->sy;
-  if (L.nbuf == 2) {
-    const int nstrip = (c->lat.lx + c->tx - 1) / c->tx;
-    const int nseg = std::max(1, c->n_cu / nstrip);
-    rsy = std::min(c->lat.ly, std::max(c->sy, (c->lat.ly + nseg - 1) / nseg));
-  }
+  // Every state of a segment but the last is stepped from, two per launch, which writes its fields
+  // on the way; the last one's fields come from a pass of their own.
   auto recompute = [&](int from, int len, int b, hipStream_t st) -> hipError_t {
     hipError_t er = hipSuccess;
-    // every state but the last is stepped from, which writes its fields on the way; the last
-    // one's fields come from a pass of their own
-    for (int jj = 0; jj < len && er == hipSuccess; ++jj) {
-      if (jj + 1 < len) er = launch_plain_step_fields(c, from ^ (jj & 1), seg_x(b, jj), seg_f(b, jj), fp64, st, rsy);
-      else er = launch_checkpoint_fields_from(c, from ^ (jj & 1), seg_x(b, jj), seg_f(b, jj), fp64, st);
-    }
+    int buf = from;
+    for (int jj = 0; jj + 1 < len && er == hipSuccess; jj += 2, buf ^= 1)
+      er = launch_fields_steps(c, std::min(2, len - 1 - jj), buf, seg_x(b, jj), L.xw, seg_f(b, jj), L.fb, fp64, st);
+    if (er == hipSuccess) er = launch_checkpoint_fields_from(c, buf, seg_x(b, len - 1), seg_f(b, len - 1), fp64, st);
     return er;
   };
-  // FP32 sweeps: inside a segment the local pass gathers the common term of lambda(t+1)
-  // itself, from the next step's fbar and the next state's fields in the same segment buffer;
-  // the first reverse step of a segment reads it from memory, written by the gather pass that
-  // follows the last reverse step of the segment after it (zero for lambda(T)).  FP64 sweeps
-  // keep the separate gather pass after every local pass: their gather inside the local pass
-  // (LDS traffic of the halo) measured no faster, and its LDS footprint left less room for the
-  // recompute running beside it.
-  const bool fuse_gather = !fp64;
   auto reverse = [&](int q0, int len, int b, hipStream_t st) -> hipError_t {
     hipError_t er = hipSuccess;
     int qq = q0;
     for (int jj = len - 1; jj >= 0 && er == hipSuccess; --jj) {
-      const int gin = fuse_gather && jj + 1 < len ? 1 : 0, gout = !fuse_gather || jj == 0 ? 1 : 0;
       a.x = reinterpret_cast<const double *>(seg_x(b, jj));
       a.fields = seg_f(b, jj);
-      a.fields_next = gin ? seg_f(b, jj + 1) : nullptr;
       a.lam_next = lam_buf[qq];
-      a.corr_next = corr_buf[qq];
       a.lam = lam_buf[qq ^ 1];
-      a.corr = corr_buf[qq ^ 1];
-      a.fbar_next = fbar_buf[qq];
-      a.fbar = fbar_buf[qq ^ 1];
-      er = launch_adjoint_step(fp64, c->lat.n_species, c->lat.walls, a, gin, gout, st);
+      er = launch_adjoint_step(fp64, c->lat.n_species, c->lat.walls, a, st);
       qq ^= 1;
     }
     return er;
@@ -1192,7 +1149,7 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
     }
     if (er == hipSuccess && two) er = hipEventRecord(ev_rec[b], c->stream);
     if (er != hipSuccess) return hip_fail(c, er, "adjoint recompute");
-    c->cur = from ^ ((len - 1) & 1);
+    c->cur = from ^ ((len / 2) & 1);  // len - 1 steps, two per launch
     return LB_OK;
   };
   // the reverse steps of segment k (second stream, after its recompute)

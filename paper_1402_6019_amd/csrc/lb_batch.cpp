@@ -186,7 +186,7 @@ int build_step_tiles_t(lb_batch *b) {
   std::vector<ReduceJob> jobs(b->n);
   tiles.reserve((size_t)total);
   for (int i = 0; i < b->n; ++i) {
-    args[i] = make_tile_args<R>(b->args[i], (uint32_t)(b->ns * elem_size(b->storage)), bx);
+    args[i] = make_tile_args<R>(b->args[i], (uint32_t)(b->ns * elem_size(b->storage)), bx, by);
     jobs[i] = ReduceJob{(int)tiles.size(), (int)tiles_of(i, b->shape), 1.0 / b->lat[i].lx};
     for (int ty = 0; ty * by < b->lat[i].ly; ++ty)
       for (int tx = 0; tx * bx < b->lat[i].lx; ++tx) tiles.push_back(TileDesc{i, tx, ty, (int)tiles.size()});

@@ -19,7 +19,7 @@ enum StepWhat {
   WHAT_PROFILE = 4,      // per-row sums of the current state (velocity, stress parts), store nothing
   WHAT_STRESS = 5,       // write the site pressure tensor of the current state, store nothing
   WHAT_STEP_ACCUM = 6,   // step, adding wall stress and health counts to per-workgroup FP64 running sums
-  // step, also writing what the adjoint's reverse step reads of the state it steps from: rho,
+  // tile step, also writing what the adjoint's reverse step reads of the states it steps from: rho,
   // psi, j of every site (out_rho, [4][2][ly][lx], FP64 / FP32) and the canonical FP64
   // populations of the rows next to the walls (out_u, [s][l][2][lx])
   WHAT_STEP_FIELDS = 7,
@@ -94,7 +94,7 @@ struct TileArgs {
   size_t fields_stride, xw_stride;  // one state to the next
   uint32_t pitch_b, buf_b;          // bytes of a plane row and of the buffer
   int lx, ly;
-  uint32_t ntx, ntx_mul;            // tiles per row; b / ntx = mulhi(b, ntx_mul) for every workgroup b
+  uint32_t ntx, ntx_mul;            // tiles per row; b / ntx = mulhi(b, ntx_mul) for every workgroup b (0: divide)
   int cross_psi, moving;
   uint32_t red_mask;                // which steps of the launch reduce (bit k: step k)
   uint32_t t_step;                  // MODE_BF16SR: as StepArgs
@@ -107,7 +107,7 @@ struct TileArgs {
 
 // The arguments of a tile launch from those of the row-marching step.
 template <typename R>
-inline TileArgs<R> make_tile_args(const StepArgs &a, uint32_t site_b, int bx) {
+inline TileArgs<R> make_tile_args(const StepArgs &a, uint32_t site_b, int bx, int by) {
   TileArgs<R> t{};
   t.offset = a.offset;
   t.src = a.src;
@@ -120,7 +120,9 @@ inline TileArgs<R> make_tile_args(const StepArgs &a, uint32_t site_b, int bx) {
   t.lx = a.lx;
   t.ly = a.ly;
   t.ntx = (uint32_t)((a.lx + bx - 1) / bx);
-  t.ntx_mul = (uint32_t)(((1ull << 32) + t.ntx - 1) / t.ntx);  // unused for one tile per row
+  // exact while tiles per row times tiles stay below 2^32
+  const uint64_t tiles = (uint64_t)t.ntx * (uint32_t)((a.ly + by - 1) / by);
+  t.ntx_mul = t.ntx > 1 && tiles * t.ntx < (1ull << 32) ? (uint32_t)(((1ull << 32) + t.ntx - 1) / t.ntx) : 0u;
   t.cross_psi = a.cross_psi;
   t.moving = a.moving;
   t.t_step = a.t_step;
@@ -234,18 +236,9 @@ struct LayoutArgs {
 struct AdjArgs {
   const double *x;       // pre-collision populations f(t) of the rows next to the walls, [s][l][2][x]
                          // (bottom row, then top row), FP64; read with walls only
-  // lambda(t) is kept in two parts: lam [s][l][y][x], written by the local pass, and corr
-  // [s][y][x], the term common to every l that the gather adds; lambda_l = lam_l + corr.
-  const void *lam_next;   // lam of lambda(t+1) (R)
-  const void *corr_next;  // corr of lambda(t+1) (R)
-  void *lam;              // lam of lambda(t) (R, written)
-  void *corr;             // corr of lambda(t) (R, written)
-  void *fields;          // [4][2][y][x] (R): rho, psi, jx, jy of f(t)
-  void *fbar;            // [2][4][y][x] (R): psi_s Fbar_s and r_s Fbar_s (x, y components), written
-  // With the common term of lambda(t+1) gathered in the local pass instead of read from
-  // corr_next: fbar of step t + 1 and the fields of f(t + 1).
-  const void *fbar_next;
-  const void *fields_next;
+  const void *lam_next;  // lambda(t+1) [s][l][y][x] (R)
+  void *lam;             // lambda(t) (R, written)
+  const void *fields;    // [4][2][y][x] (R): rho, psi, jx, jy of f(t)
   double *partials;      // [blocks][ADJ_N]
   int lx, ly;
   int cross_psi, pad_;
@@ -265,12 +258,8 @@ struct AdjArgs {
 enum AdjSlot { ADJ_G1A = 0, ADJ_G1B, ADJ_G2A, ADJ_G2B, ADJ_GAB, ADJ_GX, ADJ_GY, ADJ_LW, ADJ_LQ, ADJ_N };
 
 int adj_blocks(int lx, int ly);
-// One reverse step; adds this step's per-block sensitivities to a.partials.  gather_in: the
-// local pass gathers the common term of lambda(t+1) from a.fbar_next and a.fields_next
-// instead of reading a.corr_next; gather_out: a gather pass writes a.corr for lambda(t) (the
-// next reverse step reads it from memory).
-hipError_t launch_adjoint_step(int fp64, int ns, int walls, const AdjArgs &a, int gather_in, int gather_out,
-                               hipStream_t st);
+// One reverse step; adds this step's per-block sensitivities to a.partials.
+hipError_t launch_adjoint_step(int fp64, int ns, int walls, const AdjArgs &a, hipStream_t st);
 // acc[k] += sum over blocks of partials[block][k] (fixed order).
 hipError_t launch_adjoint_reduce(const double *partials, int lx, int ly, double *acc, hipStream_t st);
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
@@ -319,8 +308,8 @@ hipError_t static_scratch_setup(int device);
 // That address (nullptr before static_scratch_setup succeeded on the device).
 double *static_scratch(int device);
 
-// n steps (1 .. kTileSteps[shape]) of the tile step of one lattice, or of a batch; what: WHAT_STEP
-// or WHAT_STEP_ACCUM.  Per storage mode in lb_tile_f64.hip, lb_tile_f32.hip, lb_tile_bf16.hip.
+// n steps (1 .. kTileSteps[shape]) of the tile step of one lattice, or of a batch; what: WHAT_STEP,
+// WHAT_STEP_ACCUM or, one lattice and at most two steps, WHAT_STEP_FIELDS*.  Per storage mode in lb_tile_f64.hip, lb_tile_f32.hip, lb_tile_bf16.hip.
 #define LB_TILE_LAUNCHERS(A)                                                                                       \
   hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,  \
                          hipStream_t st);                                                                          \

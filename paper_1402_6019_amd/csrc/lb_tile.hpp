@@ -295,7 +295,7 @@ __device__ __forceinline__ void tile_steps(const TileArgs<typename Codec<MODE>::
 template <int MODE, int NS, bool WALLS, int WHAT, int BX, int BY, int N, int NT, int STP>
 __global__ __launch_bounds__(NT) void tile_kernel(TileArgs<typename Codec<MODE>::R> a) {
   const uint32_t logical = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
-  const uint32_t by = a.ntx == 1 ? logical : __umulhi(logical, a.ntx_mul);
+  const uint32_t by = a.ntx_mul ? __umulhi(logical, a.ntx_mul) : logical / a.ntx;
   tile_steps<MODE, NS, WALLS, WHAT, BX, BY, N, NT, STP>(
       a, a.src, a.dst, (int)(logical - by * a.ntx) * BX, (int)by * BY, launch_step_index<MODE>(a.t_step, a.t_base),
       a.red_mask, WHAT == WHAT_STEP_ACCUM ? a.accrows + (size_t)blockIdx.x * ACC_N : nullptr);
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(NT) void batch_tile_kernel(BatchTileArgs<typename C
 template <int MODE, int NS, bool WALLS, int WHAT, int BX, int BY, int N, int NT, int STP>
 static hipError_t launch_tile_k(const StepArgs &a, const TileOpts &o, hipStream_t st) {
   using C = Codec<MODE>;
-  TileArgs<typename C::R> t = make_tile_args<typename C::R>(a, (uint32_t)(NS * sizeof(typename C::S)), BX);
+  TileArgs<typename C::R> t = make_tile_args<typename C::R>(a, (uint32_t)(NS * sizeof(typename C::S)), BX, BY);
   t.red_mask = o.red_mask;
   t.fields_stride = o.fields_stride;
   t.xw_stride = o.xw_stride;
@@ -369,12 +369,43 @@ static hipError_t launch_tile_m(int ns, int walls, int shape, int n, const A &a,
   return walls ? launch_tile_w<MODE, 2, true, WHAT>(shape, n, a, o, st) : launch_tile_w<MODE, 2, false, WHAT>(shape, n, a, o, st);
 }
 
+// The passes that also write the adjoint's fields: one or two steps, stores written through (the
+// recomputed states' buffers are read again at once).
+template <int MODE, int NS, bool WALLS, int WHAT>
+static hipError_t launch_tile_fields(int shape, int n, const StepArgs &a, const TileOpts &o, hipStream_t st) {
+  constexpr int WT = kStoreWriteThrough;
+  switch (shape * 4 + n) {
+    case 0 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 1, 256, WT>(a, o, st);
+    case 0 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 2, 384, WT>(a, o, st);
+    case 1 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 1, 256, WT>(a, o, st);
+    case 1 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 2, 512, WT>(a, o, st);
+    case 2 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 1, 448, WT>(a, o, st);
+    case 2 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 2, 512, WT>(a, o, st);
+    case 3 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 1, 512, WT>(a, o, st);
+    case 3 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 512, WT>(a, o, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int MODE, int WHAT>
+static hipError_t launch_tile_fields_m(int ns, int walls, int shape, int n, const StepArgs &a, const TileOpts &o,
+                                       hipStream_t st) {
+  if (ns == 1) return walls ? launch_tile_fields<MODE, 1, true, WHAT>(shape, n, a, o, st) : launch_tile_fields<MODE, 1, false, WHAT>(shape, n, a, o, st);
+  return walls ? launch_tile_fields<MODE, 2, true, WHAT>(shape, n, a, o, st) : launch_tile_fields<MODE, 2, false, WHAT>(shape, n, a, o, st);
+}
+
 template <int MODE, typename A>
 static hipError_t launch_tile_what(int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,
                                    hipStream_t st) {
   switch (what) {
     case WHAT_STEP: return launch_tile_m<MODE, WHAT_STEP>(ns, walls, shape, n, a, o, st);
     case WHAT_STEP_ACCUM: return launch_tile_m<MODE, WHAT_STEP_ACCUM>(ns, walls, shape, n, a, o, st);
+  }
+  if constexpr (std::is_same<A, StepArgs>::value && MODE != MODE_BF16SR) {  // the adjoint: one lattice, no random rounding
+    switch (what) {
+      case WHAT_STEP_FIELDS: return launch_tile_fields_m<MODE, WHAT_STEP_FIELDS>(ns, walls, shape, n, a, o, st);
+      case WHAT_STEP_FIELDS32: return launch_tile_fields_m<MODE, WHAT_STEP_FIELDS32>(ns, walls, shape, n, a, o, st);
+    }
   }
   return hipErrorInvalidValue;
 }
