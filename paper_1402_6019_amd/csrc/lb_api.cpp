@@ -163,7 +163,7 @@ bool tiles_on(const lb_ctx *c) { return !c->shape_set && c->two_step != LB_TWO_S
 // Tile shape: the smallest whose tiles fit the compute units one each.  A launch lasts as long as
 // its busiest compute unit, so up to that point a larger tile only adds work, and beyond it a
 // smaller one only adds overlap: per step of 188 x 168 FP64 sites (one species) 16 x 8 tiles
-// took 2.7 us, 8 x 8 3.5 and 16 x 16 3.4; of a 512 x 512 FP32 channel 32 x 16 tiles 7.4 us,
+// took 2.6 us, 8 x 8 3.0 and 16 x 16 3.0; of a 512 x 512 FP32 channel 32 x 16 tiles 7.4 us,
 // 16 x 16 8.1.
 int tile_shape(const lb_ctx *c) {
   for (int k = 0; k < kTileShapes - 1; ++k)
@@ -179,7 +179,7 @@ int tile_blocks(const lb_ctx *c, int shape) {
 // Steps of the next tile launch with n left: as many as the shape takes, but no single step at
 // the end where two launches of two do (3 + 1 = 2 + 2); one with two steps per launch turned off.
 int tile_steps(const lb_ctx *c, int shape, int64_t n) {
-  const int most = c->two_step == LB_TWO_STEP_OFF ? 1 : kTileSteps[shape];
+  const int most = c->two_step == LB_TWO_STEP_OFF ? 1 : tile_most_steps(shape, c->lat.storage == LB_F64, c->lat.n_species);
   if (most == 3 && n == 4) return 2;
   return (int)std::min<int64_t>(most, n);
 }

@@ -216,7 +216,7 @@ int build_step_tiles(lb_batch *b) {
 
 // Steps of the next tile launch with n left (see lb_api.cpp).
 int tile_steps(const lb_batch *b, int64_t n) {
-  const int most = kTileSteps[b->shape];
+  const int most = tile_most_steps(b->shape, b->storage == LB_F64, b->ns);
   if (most == 3 && n == 4) return 2;
   return (int)std::min<int64_t>(most, n);
 }
@@ -603,7 +603,7 @@ int lb_batch_autotune(lb_batch *b, int32_t trial_steps, int32_t out[3], double *
   if (rc2) return rc2;
   // the tile step competes too; where it wins, the shape found serves the passes that march
   if (b->nst > 0) {
-    const int m = kTileSteps[b->shape];
+    const int m = tile_most_steps(b->shape, b->storage == LB_F64, b->ns);
     const double ms = time_launches(b->stream, 2, trial_steps, [&]() {
       return launch_tile_steps(b, m, b->cur, WHAT_STEP, 0, b->stream, (uint32_t)b->t, nullptr);
     }) / m;

@@ -158,10 +158,15 @@ struct TileOpts {
   size_t fields_stride = 0, xw_stride = 0;   // WHAT_STEP_FIELDS*: bytes from one state's outputs to the next's
 };
 
-// Tile shapes of the tile step: sites per tile, and the most steps of one launch.
-constexpr int kTileShapes = 4;
-constexpr int kTileX[kTileShapes] = {8, 16, 16, 32}, kTileY[kTileShapes] = {8, 8, 16, 16};
-constexpr int kTileSteps[kTileShapes] = {3, 3, 3, 2};
+// Tile shapes of the tile step: sites per tile, and the most steps of one launch.  The last two are the
+// same tile, of one workgroup per compute unit (more threads, three steps) and of two.
+constexpr int kTileShapes = 5;
+constexpr int kTileX[kTileShapes] = {8, 16, 16, 32, 32}, kTileY[kTileShapes] = {8, 8, 16, 16, 16};
+
+// Steps of one launch at most: three, in 32 x 16 tiles with one per compute unit (512 x 256, FP32,
+// walled: 4.40 us per step against 4.64 for two; beyond that the overlaps cost more than the launches:
+// 4096 x 512 62 and 44) unless the copy of f* outgrows LDS (two species in FP64).
+inline int tile_most_steps(int shape, bool fp64, int ns) { return shape == 4 || (shape == 3 && fp64 && ns == 2) ? 2 : 3; }
 
 // Batched launches: one tile of one instance.
 struct TileDesc {
@@ -308,7 +313,7 @@ hipError_t static_scratch_setup(int device);
 // That address (nullptr before static_scratch_setup succeeded on the device).
 double *static_scratch(int device);
 
-// n steps (1 .. kTileSteps[shape]) of the tile step of one lattice, or of a batch; what: WHAT_STEP,
+// n steps (1 .. tile_most_steps) of the tile step of one lattice, or of a batch; what: WHAT_STEP,
 // WHAT_STEP_ACCUM or, one lattice and at most two steps, WHAT_STEP_FIELDS*.  Per storage mode in lb_tile_f64.hip, lb_tile_f32.hip, lb_tile_bf16.hip.
 #define LB_TILE_LAUNCHERS(A)                                                                                       \
   hipError_t launch_tile(int mode, int ns, int walls, int what, int shape, int n, const A &a, const TileOpts &o,  \

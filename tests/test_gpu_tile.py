@@ -54,6 +54,17 @@ def test_tile_steps_are_bitwise_the_marched_steps(lx, ly, storage, ns, walls):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("lx,ly", [(400, 300), (320, 200)])
+@pytest.mark.parametrize("storage,ns,walls", [("f64", 1, False), ("f64", 2, True), ("f32", 2, True), ("bf16dev", 2, False)])
+def test_wide_tiles_of_one_per_compute_unit(lx, ly, storage, ns, walls):
+    """32 x 16 tiles that fit the compute units one each: three steps per launch (FP64 with two
+    species: two), ragged on both sides and on one."""
+    c = case(lx, ly, storage, ns, walls)
+    print(lx, ly, storage, ns, walls, flush=True)
+    for a, b in zip(populations(c, (1, 2, 3, 4, 5)), populations(c, (1, 2, 3, 4, 5), tile=(64, 7))):
+        assert np.array_equal(a, b)
+
+
 def test_tile_steps_with_other_options():
     c = case(61, 37, "bf16dev", 2, True)
     a, b = (populations(c, (7,), tile=t, rounding="stochastic") for t in (None, (64, 7)))
