@@ -291,15 +291,10 @@ int ensure_accrows(lb_ctx *c, int nb) {
   return LB_OK;
 }
 
-// One launch of the fused kernel on the current buffer.
-int run_step_kernel(lb_ctx *c, int what, void *out_rho, void *out_u, int out_f32) {
+// One launch of the fused step on the current buffer.
+int run_step_kernel(lb_ctx *c, int what) {
   int nseg = 0;
   const int nb = grid_blocks(c, c->tx, c->sy, &nseg);
-  const bool reduce = what == WHAT_OBSERVE;
-  if (reduce) {
-    int rc = ensure_partials(c, nb);
-    if (rc) return rc;
-  }
   if (what == WHAT_STEP_ACCUM) {
     int rc = ensure_accrows(c, nb);
     if (rc) return rc;
@@ -309,23 +304,27 @@ int run_step_kernel(lb_ctx *c, int what, void *out_rho, void *out_u, int out_f32
   a.nseg = nseg;
   a.src = c->pop[c->cur];
   a.dst = c->pop[c->cur ^ 1];
-  a.partials = c->d_partials;
   a.accrows = c->d_accrows;
-  a.out_rho = out_rho;
-  a.out_u = out_u;
-  a.out_f32 = out_f32;
   a.t_step = (uint32_t)c->t;
   hipError_t e = launch_step(step_mode(c), c->lat.n_species, c->lat.walls, what, c->tx, nb, a, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "step kernel launch");
-  if (reduce) {
-    e = launch_reduce(c->d_partials, nb, c->d_totals, c->d_acc, 0, 1.0 / c->lat.lx, c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "reduce kernel launch");
-  }
   if (what == WHAT_STEP_ACCUM) {
     c->acc_nb = nb;
     ++c->acc_pending;
   }
   return LB_OK;
+}
+
+// Arguments of a pass over the current state, which stores no populations.
+StepArgs observe_args(const lb_ctx *c) {
+  StepArgs a;
+  fill_step_args(c, a);
+  a.src = c->pop[c->cur];
+  return a;
+}
+
+hipError_t run_observe(const lb_ctx *c, int what, const StepArgs &a) {
+  return launch_observe(c->lat.storage, c->lat.n_species, c->lat.walls, what, c->n_cu, a, c->stream);
 }
 
 // Latched health check: look at the last asynchronously copied accumulator if it is ready.
@@ -546,7 +545,7 @@ int lb_step(lb_ctx *c, int64_t n) {
   }
   for (int64_t k = 0; k < n; ++k) {
     const bool red = c->reduce_every > 0 && (c->t % c->reduce_every) == 0;
-    rc = run_step_kernel(c, red ? WHAT_STEP_ACCUM : WHAT_STEP, nullptr, nullptr, 0);
+    rc = run_step_kernel(c, red ? WHAT_STEP_ACCUM : WHAT_STEP);
     if (rc) return rc;
     reduced |= red;
     c->cur ^= 1;
@@ -575,23 +574,23 @@ int lb_moments(lb_ctx *c, void *rho, void *u, int32_t dtype) {
   if (!c) return fail(nullptr, LB_EINVAL, "null context");
   if (dtype != LB_OUT_F64 && dtype != LB_OUT_F32) return fail(c, LB_EINVAL, "dtype must be LB_OUT_F64 or LB_OUT_F32");
   if (!rho && !u) return LB_OK;
-  return run_step_kernel(c, WHAT_MOMENTS, rho, u, dtype == LB_OUT_F32);
+  StepArgs a = observe_args(c);
+  a.out_rho = rho;
+  a.out_u = u;
+  a.out_f32 = dtype == LB_OUT_F32;
+  hipError_t e = run_observe(c, WHAT_MOMENTS, a);
+  if (e != hipSuccess) return hip_fail(c, e, "moments kernel launch");
+  return LB_OK;
 }
 
 int lb_stress_field(lb_ctx *c, void *sigma, int32_t dtype) {
   if (!c) return fail(nullptr, LB_EINVAL, "null context");
   if (!sigma) return fail(c, LB_EINVAL, "null output");
   if (dtype != LB_OUT_F64 && dtype != LB_OUT_F32) return fail(c, LB_EINVAL, "dtype must be LB_OUT_F64 or LB_OUT_F32");
-  int nseg = 0;
-  const int nb = grid_blocks(c, c->tx, c->sy, &nseg);
-  StepArgs a;
-  fill_step_args(c, a);
-  a.nseg = nseg;
-  a.src = c->pop[c->cur];
-  a.dst = c->pop[c->cur ^ 1];  // not written
+  StepArgs a = observe_args(c);
   a.out_sigma = sigma;
   a.out_f32 = dtype == LB_OUT_F32;
-  hipError_t e = launch_step(c->lat.storage, c->lat.n_species, c->lat.walls, WHAT_STRESS, c->tx, nb, a, c->stream);
+  hipError_t e = run_observe(c, WHAT_STRESS, a);
   if (e != hipSuccess) return hip_fail(c, e, "stress kernel launch");
   return LB_OK;
 }
@@ -622,10 +621,16 @@ int lb_wall_stress(lb_ctx *c, double out[2], int32_t reset) {
 int lb_totals(lb_ctx *c, double mass[2], double momentum[2], double *flow) {
   if (!c) return fail(nullptr, LB_EINVAL, "null context");
   if (!mass || !momentum) return fail(c, LB_EINVAL, "null output");
-  int rc = run_step_kernel(c, WHAT_OBSERVE, nullptr, nullptr, 0);
+  const int nb = observe_blocks(c->lat.lx, c->lat.ly);
+  int rc = ensure_partials(c, nb);
   if (rc) return rc;
+  StepArgs a = observe_args(c);
+  a.partials = c->d_partials;
+  hipError_t e = run_observe(c, WHAT_OBSERVE, a);
+  if (e == hipSuccess) e = launch_reduce(c->d_partials, nb, c->d_totals, c->d_acc, 0, 1.0 / c->lat.lx, c->stream);
+  if (e != hipSuccess) return hip_fail(c, e, "totals kernel launch");
   double h[RED_N];
-  hipError_t e = hipMemcpyAsync(h, c->d_totals, sizeof(h), hipMemcpyDeviceToHost, c->stream);
+  e = hipMemcpyAsync(h, c->d_totals, sizeof(h), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "totals readback");
   mass[0] = h[RED_MASS0];
@@ -758,17 +763,13 @@ int lb_set_couplings(lb_ctx *c, const lb_couplings *cpl) {
 
 namespace {
 
-// The profile pass and its second pass, with `buf` holding the block sums and then the row
-// sums ((ncb + 1) * ly * PROF_N doubles).
-int profile_into(lb_ctx *c, int nb, int nseg, int ncb, double *buf, double *out) {
-  StepArgs a;
-  fill_step_args(c, a);
-  a.nseg = nseg;
-  a.src = c->pop[c->cur];
-  a.dst = c->pop[c->cur ^ 1];  // not written
+// The profile pass and its second pass, with `buf` holding the sums of each tile column's rows
+// (ncb * ly * PROF_N doubles).
+int profile_into(lb_ctx *c, double *buf, double *out) {
+  const int ncb = (c->lat.lx + kObserveX - 1) / kObserveX;
+  StepArgs a = observe_args(c);
   a.prof = buf;
-  a.ncb = ncb;
-  hipError_t e = launch_step(c->lat.storage, c->lat.n_species, c->lat.walls, WHAT_PROFILE, c->tx, nb, a, c->stream);
+  hipError_t e = run_observe(c, WHAT_PROFILE, a);
   if (e != hipSuccess) return hip_fail(c, e, "profile kernel launch");
   // the walls' share of their momentum exchange: sum_s rho_w,s U / 3 per unit length
   double wb0 = 0.0, wt0 = 0.0;
@@ -777,8 +778,7 @@ int profile_into(lb_ctx *c, int nb, int nseg, int ncb, double *buf, double *out)
       wb0 += 2.0 * a.wall_mom[0][s];
       wt0 += 2.0 * a.wall_mom[1][s];
     }
-  e = launch_profile_finish(buf, ncb, c->lat.lx, c->lat.ly, c->lat.walls, wb0, wt0,
-                            buf + (size_t)ncb * c->lat.ly * PROF_N, out, c->stream);
+  e = launch_profile_finish(buf, ncb, c->lat.lx, c->lat.ly, c->lat.walls, wb0, wt0, out, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "profile finish launch");
   return LB_OK;
 }
@@ -788,10 +788,7 @@ int profile_into(lb_ctx *c, int nb, int nseg, int ncb, double *buf, double *out)
 int lb_profile(lb_ctx *c, double *out) {
   if (!c) return fail(nullptr, LB_EINVAL, "null context");
   if (!out) return fail(c, LB_EINVAL, "null output");
-  int nseg = 0;
-  const int nb = grid_blocks(c, c->tx, c->sy, &nseg);
-  const int ncb = ((c->lat.lx + c->tx - 1) / c->tx) * (c->tx / 64);
-  const size_t need = ((size_t)ncb + 1) * c->lat.ly * PROF_N;  // block sums, then the row sums
+  const size_t need = (size_t)((c->lat.lx + kObserveX - 1) / kObserveX) * c->lat.ly * PROF_N;
   if (need > c->prof_cap) {
     if (c->d_prof) (void)hipFree(c->d_prof);
     c->d_prof = nullptr;
@@ -800,14 +797,14 @@ int lb_profile(lb_ctx *c, double *out) {
     if (e != hipSuccess) return fail(c, LB_ENOMEM, std::string("profile buffer: ") + hipGetErrorString(e));
     c->prof_cap = need;
   }
-  return profile_into(c, nb, nseg, ncb, c->d_prof, out);
+  return profile_into(c, c->d_prof, out);
 }
 
 int lb_profile_noalloc(lb_ctx *c, double *out) {
   if (!c) return fail(nullptr, LB_EINVAL, "null context");
   if (!out) return fail(c, LB_EINVAL, "null output");
-  int nseg = 0;
-  const int nb = grid_blocks(c, c->tx, c->sy, &nseg);
+  // the limit stays that of strips of tx columns, so that a lattice is accepted or refused as it
+  // was; the sums themselves take no more than that
   const int ncb = ((c->lat.lx + c->tx - 1) / c->tx) * (c->tx / 64);
   const size_t need = ((size_t)ncb + 1) * c->lat.ly * PROF_N;
   if (need > kStaticScratchDoubles)
@@ -816,7 +813,7 @@ int lb_profile_noalloc(lb_ctx *c, double *out) {
                                   std::to_string(kStaticScratchDoubles) + " (use lb_profile)");
   double *buf = static_scratch(c->device);
   if (!buf) return fail(c, LB_EDEVICE, "lb_profile_noalloc: no static scratch address for this device");
-  return profile_into(c, nb, nseg, ncb, buf, out);
+  return profile_into(c, buf, out);
 }
 
 int lb_profile_stats(lb_ctx *c, const double *samples, int64_t n, int32_t k0, double *out) {

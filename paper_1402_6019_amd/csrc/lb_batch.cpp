@@ -33,7 +33,6 @@ struct lb_batch {
   std::vector<size_t> off;         // byte offset of each instance in a population buffer
   std::vector<StepArgs> args;      // host copy of d_args
   std::vector<TileDesc> tiles;     // host copy of d_tiles
-  std::vector<int> tile0, ntile;   // tiles of instance i: [tile0[i], tile0[i] + ntile[i])
   void *pop[2]{nullptr, nullptr};
   int cur = 0;
   size_t pop_bytes = 0;
@@ -48,7 +47,9 @@ struct lb_batch {
   StepArgs *d_args = nullptr;
   TileDesc *d_tiles = nullptr;
   ReduceJob *d_jobs = nullptr;
-  double *d_partials = nullptr;  // [tiles][RED_N]
+  std::vector<ReduceJob> ojobs;    // totals: rows of partial sums of each instance
+  ReduceJob *d_ojobs = nullptr;
+  double *d_partials = nullptr;  // [observe_blocks of all instances][RED_N]
   double *d_accrows = nullptr;   // [tiles][ACC_N]: running sums of reducing steps (zero after a flush)
   double *d_prof = nullptr;      // profile pass of one instance: block sums, then row sums
   size_t prof_cap = 0;           // doubles
@@ -101,7 +102,6 @@ int build_tiles(lb_batch *b, int tx, int sy) {
   std::vector<TileDesc> tiles;
   tiles.reserve(nt);
   std::vector<ReduceJob> jobs(b->n);
-  std::vector<int> t0(b->n), ntl(b->n);
   std::vector<StepArgs> args(b->n);
   for (int i = 0; i < b->n; ++i) {
     const lb_lattice &L = b->lat[i];
@@ -113,7 +113,7 @@ int build_tiles(lb_batch *b, int tx, int sy) {
     const int nstrip = (L.lx + tx - 1) / tx, nseg = (L.ly + syi - 1) / syi;
     args[i].nseg = nseg;
     args[i].offset = (long long)b->off[i];
-    t0[i] = (int)tiles.size();
+    jobs[i].p0 = (int)tiles.size();
     for (int seg = 0; seg < nseg; ++seg)
       for (int strip = 0; strip < nstrip; ++strip) {
         TileDesc d;
@@ -123,23 +123,18 @@ int build_tiles(lb_batch *b, int tx, int sy) {
         d.part = (int)tiles.size();
         tiles.push_back(d);
       }
-    ntl[i] = (int)tiles.size() - t0[i];
-    jobs[i].p0 = t0[i];
-    jobs[i].n = ntl[i];
+    jobs[i].n = (int)tiles.size() - jobs[i].p0;
     jobs[i].inv_lx = 1.0 / L.lx;
   }
   hipError_t e = hipStreamSynchronize(b->stream);  // no launch may still read the old tables
   if (e != hipSuccess) return bhip(b, e, "tile table");
   if ((size_t)nt > b->tile_cap) {
     if (b->d_tiles) (void)hipFree(b->d_tiles);
-    if (b->d_partials) (void)hipFree(b->d_partials);
     if (b->d_accrows) (void)hipFree(b->d_accrows);
     b->d_tiles = nullptr;
-    b->d_partials = nullptr;
     b->d_accrows = nullptr;
     b->tile_cap = 0;
     if ((e = hipMalloc(&b->d_tiles, (size_t)nt * sizeof(TileDesc))) != hipSuccess ||
-        (e = hipMalloc(&b->d_partials, (size_t)nt * RED_N * sizeof(double))) != hipSuccess ||
         (e = hipMalloc(&b->d_accrows, (size_t)nt * ACC_N * sizeof(double))) != hipSuccess ||
         (e = launch_fill(b->d_accrows, 0.0, nt * ACC_N, b->stream)) != hipSuccess)
       return bfail(b, LB_ENOMEM, std::string("tile table: ") + hipGetErrorString(e));
@@ -155,8 +150,6 @@ int build_tiles(lb_batch *b, int tx, int sy) {
     return bhip(b, e, "tile table upload");
   b->tiles.swap(tiles);
   b->args.swap(args);
-  b->tile0.swap(t0);
-  b->ntile.swap(ntl);
   b->tx = tx;
   b->sy = sy;
   b->graph.clear();
@@ -179,27 +172,40 @@ int build_step_tiles_t(lb_batch *b) {
     for (int i = 0; i < b->n; ++i) total += tiles_of(i, b->shape);
     if (total <= b->n_cu || b->shape == kTileShapes - 1) break;
   }
-  if (total > kMaxBlocks) return LB_OK;
   const int bx = kTileX[b->shape], by = kTileY[b->shape];
   std::vector<TileArgs<R>> args(b->n);
+  int rows = 0;
+  b->ojobs.resize(b->n);
+  for (int i = 0; i < b->n; ++i) {
+    args[i] = make_tile_args<R>(b->args[i], (uint32_t)(b->ns * elem_size(b->storage)), bx, by);
+    b->ojobs[i] = ReduceJob{rows, observe_blocks(b->lat[i].lx, b->lat[i].ly), 1.0 / b->lat[i].lx};
+    rows += b->ojobs[i].n;
+  }
+  hipError_t e;
+  if ((e = hipMalloc(&b->d_targs, args.size() * sizeof(args[0]))) != hipSuccess ||
+      (e = hipMalloc(&b->d_ojobs, b->ojobs.size() * sizeof(ReduceJob))) != hipSuccess ||
+      (e = hipMalloc(&b->d_partials, (size_t)rows * RED_N * sizeof(double))) != hipSuccess)
+    return bfail(b, LB_ENOMEM, std::string("pass arguments: ") + hipGetErrorString(e));
+  if ((e = hipMemcpyAsync(b->d_targs, args.data(), args.size() * sizeof(args[0]), hipMemcpyHostToDevice, b->stream)) !=
+          hipSuccess ||
+      (e = hipMemcpyAsync(b->d_ojobs, b->ojobs.data(), b->ojobs.size() * sizeof(ReduceJob), hipMemcpyHostToDevice,
+                          b->stream)) != hipSuccess ||
+      (e = hipStreamSynchronize(b->stream)) != hipSuccess)
+    return bhip(b, e, "pass arguments");
+  if (total > kMaxBlocks) return LB_OK;
   std::vector<TileDesc> tiles;
   std::vector<ReduceJob> jobs(b->n);
   tiles.reserve((size_t)total);
   for (int i = 0; i < b->n; ++i) {
-    args[i] = make_tile_args<R>(b->args[i], (uint32_t)(b->ns * elem_size(b->storage)), bx, by);
     jobs[i] = ReduceJob{(int)tiles.size(), (int)tiles_of(i, b->shape), 1.0 / b->lat[i].lx};
     for (int ty = 0; ty * by < b->lat[i].ly; ++ty)
       for (int tx = 0; tx * bx < b->lat[i].lx; ++tx) tiles.push_back(TileDesc{i, tx, ty, (int)tiles.size()});
   }
-  hipError_t e;
-  if ((e = hipMalloc(&b->d_targs, args.size() * sizeof(args[0]))) != hipSuccess ||
-      (e = hipMalloc(&b->d_ttiles, tiles.size() * sizeof(TileDesc))) != hipSuccess ||
+  if ((e = hipMalloc(&b->d_ttiles, tiles.size() * sizeof(TileDesc))) != hipSuccess ||
       (e = hipMalloc(&b->d_tjobs, jobs.size() * sizeof(ReduceJob))) != hipSuccess ||
       (e = hipMalloc(&b->d_taccrows, tiles.size() * ACC_N * sizeof(double))) != hipSuccess)
     return bfail(b, LB_ENOMEM, std::string("step tiles: ") + hipGetErrorString(e));
   if ((e = launch_fill(b->d_taccrows, 0.0, (int)tiles.size() * ACC_N, b->stream)) != hipSuccess ||
-      (e = hipMemcpyAsync(b->d_targs, args.data(), args.size() * sizeof(args[0]), hipMemcpyHostToDevice, b->stream)) !=
-          hipSuccess ||
       (e = hipMemcpyAsync(b->d_ttiles, tiles.data(), tiles.size() * sizeof(TileDesc), hipMemcpyHostToDevice,
                           b->stream)) != hipSuccess ||
       (e = hipMemcpyAsync(b->d_tjobs, jobs.data(), jobs.size() * sizeof(ReduceJob), hipMemcpyHostToDevice,
@@ -257,8 +263,7 @@ int launch_grid(const lb_batch *b, int ntiles) {
 
 // One launch over tiles [first, first + count) from buffer `from` to the other one.
 hipError_t launch_tiles(const lb_batch *b, int what, int from, int first, int count, hipStream_t st,
-                        void *out_rho = nullptr, void *out_u = nullptr, int out_f32 = 0, uint32_t t_step = 0,
-                        const double *t_base = nullptr) {
+                        uint32_t t_step = 0, const double *t_base = nullptr) {
   BatchArgs a;
   std::memset(&a, 0, sizeof(a));
   a.inst = b->d_args;
@@ -267,16 +272,23 @@ hipError_t launch_tiles(const lb_batch *b, int what, int from, int first, int co
   a.ntiles = count;
   a.src = static_cast<const char *>(b->pop[from]);
   a.dst = static_cast<char *>(b->pop[from ^ 1]);
-  a.partials = b->d_partials;
   a.accrows = b->d_accrows;
-  a.out_rho = out_rho;
-  a.out_u = out_u;
-  a.out_f32 = out_f32;
   a.stream_stores = streaming_stores(b->footprint);
   a.t_step = t_step;
   a.t_base = t_base;
   const int mode = b->storage == LB_BF16DEV && b->rounding == LB_ROUND_STOCHASTIC ? MODE_BF16SR : b->storage;
   return launch_batch_step(mode, b->ns, b->walls, what, b->tx, launch_grid(b, count), a, st);
+}
+
+// Arguments of a pass over the current state of instance i, as for one lattice.
+StepArgs observe_args(const lb_batch *b, int i) {
+  StepArgs a = b->args[i];
+  a.src = static_cast<const char *>(b->pop[b->cur]) + a.offset;
+  return a;
+}
+
+hipError_t run_observe(const lb_batch *b, int what, const StepArgs &a) {
+  return launch_observe(b->storage, b->ns, b->walls, what, b->n_cu, a, b->stream);
 }
 
 int poll(lb_batch *b, bool wait) {
@@ -459,7 +471,7 @@ int lb_batch_step(lb_batch *b, int64_t n) {
               }
               return er;
             }
-            return launch_tiles(b, WHAT_STEP, from ^ (k & 1), 0, nt, st, nullptr, nullptr, 0, (uint32_t)k, tb);
+            return launch_tiles(b, WHAT_STEP, from ^ (k & 1), 0, nt, st, (uint32_t)k, tb);
           },
           &g);
       // the replay's steps are t + k: the base goes to device memory (a fill kernel, outside the graph)
@@ -488,8 +500,7 @@ int lb_batch_step(lb_batch *b, int64_t n) {
   }
   for (int64_t k = 0; k < n; ++k) {
     const bool red = b->reduce_every > 0 && (b->t % b->reduce_every) == 0;
-    hipError_t e = launch_tiles(b, red ? WHAT_STEP_ACCUM : WHAT_STEP, b->cur, 0, nt, b->stream, nullptr, nullptr, 0,
-                                (uint32_t)b->t);
+    hipError_t e = launch_tiles(b, red ? WHAT_STEP_ACCUM : WHAT_STEP, b->cur, 0, nt, b->stream, (uint32_t)b->t);
     if (e != hipSuccess) return bhip(b, e, "batch step launch");
     reduced |= red;
     if (red) ++b->acc_pending;
@@ -626,7 +637,11 @@ int lb_batch_moments(lb_batch *b, int32_t i, void *rho, void *u, int32_t dtype) 
   if (rc) return rc;
   if (dtype != LB_OUT_F64 && dtype != LB_OUT_F32) return bfail(b, LB_EINVAL, "dtype must be LB_OUT_F64 or LB_OUT_F32");
   if (!rho && !u) return LB_OK;
-  hipError_t e = launch_tiles(b, WHAT_MOMENTS, b->cur, b->tile0[i], b->ntile[i], b->stream, rho, u, dtype == LB_OUT_F32);
+  StepArgs a = observe_args(b, i);
+  a.out_rho = rho;
+  a.out_u = u;
+  a.out_f32 = dtype == LB_OUT_F32;
+  hipError_t e = run_observe(b, WHAT_MOMENTS, a);
   if (e != hipSuccess) return bhip(b, e, "moments launch");
   return LB_OK;
 }
@@ -637,8 +652,10 @@ int lb_batch_stress_field(lb_batch *b, int32_t i, void *sigma, int32_t dtype) {
   if (rc) return rc;
   if (!sigma) return bfail(b, LB_EINVAL, "null output");
   if (dtype != LB_OUT_F64 && dtype != LB_OUT_F32) return bfail(b, LB_EINVAL, "dtype must be LB_OUT_F64 or LB_OUT_F32");
-  hipError_t e = launch_tiles(b, WHAT_STRESS, b->cur, b->tile0[i], b->ntile[i], b->stream, sigma, nullptr,
-                              dtype == LB_OUT_F32);
+  StepArgs a = observe_args(b, i);
+  a.out_sigma = sigma;
+  a.out_f32 = dtype == LB_OUT_F32;
+  hipError_t e = run_observe(b, WHAT_STRESS, a);
   if (e != hipSuccess) return bhip(b, e, "stress launch");
   return LB_OK;
 }
@@ -649,8 +666,8 @@ int lb_batch_profile(lb_batch *b, int32_t i, double *out) {
   if (rc) return rc;
   if (!out) return bfail(b, LB_EINVAL, "null output");
   const lb_lattice &L = b->lat[i];
-  const int ncb = ((L.lx + b->tx - 1) / b->tx) * (b->tx / 64);
-  const size_t need = ((size_t)ncb + 1) * L.ly * PROF_N;
+  const int ncb = (L.lx + kObserveX - 1) / kObserveX;
+  const size_t need = (size_t)ncb * L.ly * PROF_N;
   if (need > b->prof_cap) {
     (void)hipStreamSynchronize(b->stream);
     if (b->d_prof) (void)hipFree(b->d_prof);
@@ -660,7 +677,9 @@ int lb_batch_profile(lb_batch *b, int32_t i, double *out) {
     if (e != hipSuccess) return bfail(b, LB_ENOMEM, std::string("profile buffer: ") + hipGetErrorString(e));
     b->prof_cap = need;
   }
-  hipError_t e = launch_tiles(b, WHAT_PROFILE, b->cur, b->tile0[i], b->ntile[i], b->stream, b->d_prof);
+  StepArgs a = observe_args(b, i);
+  a.prof = b->d_prof;
+  hipError_t e = run_observe(b, WHAT_PROFILE, a);
   double wb0 = 0.0, wt0 = 0.0;
   if (b->walls)
     for (int s = 0; s < b->ns; ++s) {
@@ -668,8 +687,7 @@ int lb_batch_profile(lb_batch *b, int32_t i, double *out) {
       wt0 += 2.0 * b->args[i].wall_mom[1][s];
     }
   if (e == hipSuccess)
-    e = launch_profile_finish(b->d_prof, ncb, L.lx, L.ly, b->walls, wb0, wt0, b->d_prof + (size_t)ncb * L.ly * PROF_N,
-                              out, b->stream);
+    e = launch_profile_finish(b->d_prof, ncb, L.lx, L.ly, b->walls, wb0, wt0, out, b->stream);
   if (e != hipSuccess) return bhip(b, e, "profile launch");
   return LB_OK;
 }
@@ -677,9 +695,16 @@ int lb_batch_profile(lb_batch *b, int32_t i, double *out) {
 int lb_batch_totals(lb_batch *b, double *out) {
   if (!b) return bfail(nullptr, LB_EINVAL, "null context");
   if (!out) return bfail(b, LB_EINVAL, "null output");
-  const int nt = (int)b->tiles.size();
-  hipError_t e = launch_tiles(b, WHAT_OBSERVE, b->cur, 0, nt, b->stream);
-  if (e == hipSuccess) e = launch_batch_reduce(b->d_partials, b->d_jobs, b->n, b->d_totals, b->d_acc, 0, b->stream);
+  BatchTiles a{};
+  a.inst = b->d_targs;
+  a.src = static_cast<const char *>(b->pop[b->cur]);
+  int blocks = 1;
+  for (const ReduceJob &j : b->ojobs) blocks = std::max(blocks, j.n);
+  hipError_t e = hipSuccess;
+  for (int i = 0, m = std::max(1, kMaxBlocks / blocks); i < b->n && e == hipSuccess; i += m)
+    e = launch_batch_observe(b->storage, b->ns, b->walls, i, std::min(m, b->n - i), blocks, a, b->d_ojobs, b->d_partials,
+                             b->stream);
+  if (e == hipSuccess) e = launch_batch_reduce(b->d_partials, b->d_ojobs, b->n, b->d_totals, b->d_acc, 0, b->stream);
   std::vector<double> h((size_t)b->n * RED_N);
   if (e == hipSuccess)
     e = hipMemcpyAsync(h.data(), b->d_totals, h.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream);
@@ -784,7 +809,7 @@ void lb_batch_destroy(lb_batch *b) {
   if (!b) return;
   if (b->check_pending && b->ev) (void)hipEventSynchronize(b->ev);
   (void)hipStreamSynchronize(b->stream);
-  for (void *p : {(void *)b->d_args, (void *)b->d_tiles, (void *)b->d_jobs, (void *)b->d_partials, (void *)b->d_accrows,
+  for (void *p : {(void *)b->d_args, (void *)b->d_tiles, (void *)b->d_jobs, (void *)b->d_ojobs, (void *)b->d_partials, (void *)b->d_accrows,
                   (void *)b->d_prof, (void *)b->d_targs, (void *)b->d_ttiles, (void *)b->d_taccrows, (void *)b->d_tjobs,
                   (void *)b->d_totals, (void *)b->d_acc})
     if (p) (void)hipFree(p);

@@ -29,7 +29,7 @@ enum StepWhat {
 // Running sums of WHAT_STEP_ACCUM, per workgroup row.
 enum AccSlot { ACC_WBOT = 0, ACC_WTOP, ACC_BAD, ACC_N };
 
-// Per-row sums written by a WHAT_PROFILE launch, per 64-column block of a row:
+// Per-row sums written by a WHAT_PROFILE launch, per tile column (64 columns) of a row:
 //   PROF_U   sum of the half-force velocity u_x
 //   PROF_KUP sum_s (f*_5 - f*_6): x-momentum the populations with c_y = +1 carry up
 //   PROF_KDN sum_s (f*_8 - f*_7): x-momentum the populations with c_y = -1 carry down
@@ -168,6 +168,10 @@ constexpr int kTileX[kTileShapes] = {8, 16, 16, 32, 32}, kTileY[kTileShapes] = {
 // 4096 x 512 62 and 44) unless the copy of f* outgrows LDS (two species in FP64).
 inline int tile_most_steps(int shape, bool fp64, int ns) { return shape == 4 || (shape == 3 && fp64 && ns == 2) ? 2 : 3; }
 
+// Tiles of the observation passes (lb_observe.hpp) with sums, and of those without on large lattices.
+constexpr int kObserveX = 64, kObserveY = 8;
+inline int observe_blocks(int lx, int ly) { return ((lx + kObserveX - 1) / kObserveX) * ((ly + kObserveY - 1) / kObserveY); }
+
 // Batched launches: one tile of one instance.
 struct TileDesc {
   int inst;   // instance index (into BatchArgs::inst)
@@ -183,10 +187,6 @@ struct BatchArgs {
   int tile0, ntiles;
   const char *src;       // population buffers holding every instance at StepArgs::offset
   char *dst;
-  double *partials;      // [tiles][RED_N]
-  void *out_rho, *out_u; // WHAT_MOMENTS (the launch then covers one instance); out_rho is the
-                         // output of WHAT_STRESS and WHAT_PROFILE too
-  int out_f32;
   int stream_stores;     // non-temporal population stores (see StepArgs)
   double *accrows;       // WHAT_STEP_ACCUM: [tiles][ACC_N] running sums, row TileDesc::part
   uint32_t t_step;       // MODE_BF16SR: time step of the launch (see StepArgs)
@@ -273,6 +273,9 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
 hipError_t launch_step2(int mode, int ns, int walls, int nblocks, const StepArgs &a, hipStream_t st);
 hipError_t launch_step(int mode, int ns, int walls, int what, int tx, int nblocks, const StepArgs &a,
                        hipStream_t st);
+// A pass over the current state (WHAT_MOMENTS, WHAT_OBSERVE, WHAT_PROFILE or WHAT_STRESS; a.src, the pass's
+// outputs in a) of one lattice; n_cu: compute units.  WHAT_OBSERVE writes observe_blocks rows of partials.
+hipError_t launch_observe(int mode, int ns, int walls, int what, int n_cu, const StepArgs &a, hipStream_t st);
 hipError_t launch_reduce(const double *partials, int nblocks, double *totals, double *acc, int accumulate,
                          double inv_lx, hipStream_t st);
 hipError_t launch_init(int mode, int walls, const LayoutArgs &a, hipStream_t st);
@@ -293,14 +296,18 @@ hipError_t launch_batch_flush(double *rows, const ReduceJob *jobs, int njobs, do
 
 // Profile second pass: out[0..ly) = ubar, out[ly..2ly] = sigma, out[2ly+1..4ly+1) = the
 // species densities per row (see lb_profile).  wb0, wt0:
-// sum_s rho_w,s U / 3 of the bottom and top wall; rows: scratch of ly * PROF_N doubles.
+// sum_s rho_w,s U / 3 of the bottom and top wall.
 hipError_t launch_profile_finish(const double *prof, int ncb, int lx, int ly, int walls, double wb0, double wt0,
-                                 double *rows, double *out, hipStream_t st);
+                                 double *out, hipStream_t st);
 hipError_t launch_profile_stats(const double *samples, long long n, int ly, int walls, int k0, double u_bot,
                                 double u_top, double *out, hipStream_t st);
 
 hipError_t launch_batch_step(int mode, int ns, int walls, int what, int tx, int grid, const BatchArgs &b,
                              hipStream_t st);
+// WHAT_OBSERVE over instances [first, first + count) of a batch: b.inst and b.src; instance i's
+// observe_blocks rows of partials start at jobs[i].p0 (device).  blocks: the most of any instance.
+hipError_t launch_batch_observe(int mode, int ns, int walls, int first, int count, int blocks, const BatchTiles &b,
+                                const ReduceJob *jobs, double *partials, hipStream_t st);
 hipError_t launch_batch_reduce(const double *partials, const ReduceJob *jobs, int njobs, double *totals, double *acc,
                                int accumulate, hipStream_t st);
 
@@ -340,6 +347,15 @@ hipError_t launch_batch_f64(int ns, int walls, int what, int tx, int grid, const
 hipError_t launch_batch_f32(int ns, int walls, int what, int tx, int grid, const BatchArgs &b, hipStream_t st);
 hipError_t launch_batch_bf16(bool stochastic, int ns, int walls, int what, int tx, int grid, const BatchArgs &b,
                              hipStream_t st);
+hipError_t launch_observe_f64(int ns, int walls, int what, bool wide, const StepArgs &a, hipStream_t st);
+hipError_t launch_observe_f32(int ns, int walls, int what, bool wide, const StepArgs &a, hipStream_t st);
+hipError_t launch_observe_bf16(int ns, int walls, int what, bool wide, const StepArgs &a, hipStream_t st);
+hipError_t launch_batch_observe_f64(int ns, int walls, int first, int count, int blocks, const BatchTiles &b,
+                                    const ReduceJob *jobs, double *partials, hipStream_t st);
+hipError_t launch_batch_observe_f32(int ns, int walls, int first, int count, int blocks, const BatchTiles &b,
+                                    const ReduceJob *jobs, double *partials, hipStream_t st);
+hipError_t launch_batch_observe_bf16(int ns, int walls, int first, int count, int blocks, const BatchTiles &b,
+                                     const ReduceJob *jobs, double *partials, hipStream_t st);
 int blocks_per_cu_f64(int ns, int walls, int tx);
 // Two time steps per launch (lb_step2.hpp): one wave per workgroup, strips of 54 columns,
 // nb = strips x segments workgroups, a.sy rows per segment.

@@ -340,51 +340,76 @@ hipError_t launch_step(int mode, int ns, int walls, int what, int tx, int nb, co
   return hipErrorInvalidValue;
 }
 
+// Tiles of 64 x 8 where they occupy every compute unit; below that the passes without sums take 16 x 8,
+// whose workgroups load in one round instead of two and are four times as many.
+hipError_t launch_observe(int mode, int ns, int walls, int what, int n_cu, const StepArgs &a, hipStream_t st) {
+  const bool wide = observe_blocks(a.lx, a.ly) >= n_cu;
+  switch (mode) {
+    case MODE_F64: return launch_observe_f64(ns, walls, what, wide, a, st);
+    case MODE_F32: return launch_observe_f32(ns, walls, what, wide, a, st);
+    case MODE_BF16:
+    case MODE_BF16SR: return launch_observe_bf16(ns, walls, what, wide, a, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_batch_observe(int mode, int ns, int walls, int first, int count, int blocks, const BatchTiles &b,
+                                const ReduceJob *jobs, double *partials, hipStream_t st) {
+  switch (mode) {
+    case MODE_F64: return launch_batch_observe_f64(ns, walls, first, count, blocks, b, jobs, partials, st);
+    case MODE_F32: return launch_batch_observe_f32(ns, walls, first, count, blocks, b, jobs, partials, st);
+    case MODE_BF16:
+    case MODE_BF16SR: return launch_batch_observe_bf16(ns, walls, first, count, blocks, b, jobs, partials, st);
+  }
+  return hipErrorInvalidValue;
+}
+
 __global__ void fill_kernel(double *p, double v, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
 }
 
-// Profile second pass, part 1: the per-row sums rows[y][slot] = sum over the 64-column
-// blocks b of prof[b][y][slot], in increasing b (one thread per row and slot).
-__global__ void profile_rows_kernel(const double *prof, int ncb, int ly, double *rows) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ly * PROF_N) return;
-  const size_t stride = (size_t)ly * PROF_N;
-  double v = 0.0;
-  for (int b = 0; b < ncb; ++b) v += prof[b * stride + i];
-  rows[i] = v;
-}
-
-// Part 2, one thread per row y (ubar) and per line k (sigma).  Line k lies between rows
-// k-1 and k; its stress is
+// Profile second pass.  A workgroup adds up the tile columns of 32 rows and the two below them, in
+// increasing column, one thread per row and slot, then one thread per row y (ubar, densities) and per
+// line k (sigma) finishes them.  Line k lies between rows k-1 and k; its stress is
 //   sigma(k) = (I1(k-1) + I2(k-2) - Kup(k-1) + Kdn(k)) / lx
 // (pair forces across the line on the rows below it, minus the x-momentum streaming up
 // across it), with rows wrapping on periodic lattices.  On channels, sigma(0) and sigma(ly)
 // are the walls' momentum exchange: 2 Kdn(0) / lx - wb0 and -(2 Kup(ly-1) / lx - wt0).
-__global__ void profile_finish_kernel(const double *rows, int lx, int ly, int walls, double wb0, double wt0,
-                                      double *out) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > ly) return;
-  auto row = [&](int y, int slot) { return rows[(size_t)y * PROF_N + slot]; };
+constexpr int kProfileLines = 32;
+__global__ __launch_bounds__(256) void profile_finish_kernel(const double *prof, int ncb, int lx, int ly, int walls, double wb0,
+                                                             double wt0, double *out) {
+  __shared__ double rows[kProfileLines + 2][PROF_N];
+  const int tid = threadIdx.x, k0 = blockIdx.x * kProfileLines;
+  static_assert((kProfileLines + 2) * PROF_N <= 256, "one thread per row and slot");
+  if (tid < (kProfileLines + 2) * PROF_N) {
+    const int r = tid / PROF_N, slot = tid - r * PROF_N, y = ((k0 + r - 2) % ly + ly) % ly;
+    const double *p = prof + (size_t)y * PROF_N + slot;
+    const size_t stride = (size_t)ly * PROF_N;
+    double v = 0.0;
+#pragma unroll 8
+    for (int b = 0; b < ncb; ++b) v += p[b * stride];
+    rows[r][slot] = v;
+  }
+  __syncthreads();
+  const int k = k0 + tid;
+  if (tid >= kProfileLines || k > ly) return;
+  const double *const here = rows[tid + 2], *const b1 = rows[tid + 1], *const b2 = rows[tid];
   const double ilx = 1.0 / lx;
   if (k < ly) {
-    out[k] = row(k, PROF_U) * ilx;
-    out[2 * ly + 1 + k] = row(k, PROF_RA) * ilx;
-    out[3 * ly + 1 + k] = row(k, PROF_RB) * ilx;
+    out[k] = here[PROF_U] * ilx;
+    out[2 * ly + 1 + k] = here[PROF_RA] * ilx;
+    out[3 * ly + 1 + k] = here[PROF_RB] * ilx;
   }
   double sig;
   if (walls && k == 0) {
-    sig = 2.0 * row(0, PROF_KDN) * ilx - wb0;
+    sig = 2.0 * here[PROF_KDN] * ilx - wb0;
   } else if (walls && k == ly) {
-    sig = -(2.0 * row(ly - 1, PROF_KUP) * ilx - wt0);
+    sig = -(2.0 * b1[PROF_KUP] * ilx - wt0);
   } else {
-    const int kk = k == ly ? 0 : k;  // periodic: line ly is line 0
-    const int ym1 = kk - 1 < 0 ? kk - 1 + ly : kk - 1;
-    const int ym2 = kk - 2 < 0 ? kk - 2 + ly : kk - 2;
-    double i = row(ym1, PROF_I1);
-    if (!walls || kk >= 2) i += row(ym2, PROF_I2);  // on channels a partner two rows down is a wall
-    sig = (i - row(ym1, PROF_KUP) + row(kk, PROF_KDN)) * ilx;
+    double i = b1[PROF_I1];
+    if (!walls || k >= 2) i += b2[PROF_I2];  // on channels a partner two rows down is a wall
+    sig = (i - b1[PROF_KUP] + here[PROF_KDN]) * ilx;
   }
   out[ly + k] = sig;
 }
@@ -436,12 +461,9 @@ __global__ void profile_stats_kernel(const double *smp, long long n, int ly, int
 }
 
 hipError_t launch_profile_finish(const double *prof, int ncb, int lx, int ly, int walls, double wb0, double wt0,
-                                 double *rows, double *out, hipStream_t st) {
-  hipLaunchKernelGGL(profile_rows_kernel, dim3((ly * PROF_N + 255) / 256), dim3(256), 0, st, prof, ncb, ly, rows);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(profile_finish_kernel, dim3((ly + 1 + 255) / 256), dim3(256), 0, st, rows, lx, ly, walls, wb0,
-                     wt0, out);
+                                 double *out, hipStream_t st) {
+  hipLaunchKernelGGL(profile_finish_kernel, dim3((ly + kProfileLines) / kProfileLines), dim3(256), 0, st, prof, ncb, lx, ly,
+                     walls, wb0, wt0, out);
   return hipGetLastError();
 }
 

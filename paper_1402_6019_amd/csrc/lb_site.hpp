@@ -20,17 +20,15 @@ __device__ __forceinline__ void site_psi(const SiteConsts<typename C::R> &p, con
   }
 }
 
-// Force, velocity shift and collision of a site of row y: f its pulled populations (decoded),
-// ps(dx, dy) the psi of a neighbour of the two belts, xr(dx, dy) the rho (or psi) of a neighbour
-// of the first.  Writes the densities and the post-collision deviations, without the exchange with
-// a moving wall.
+// Density, momentum and force of a site: f its pulled populations (decoded), ps(dx, dy) the psi of a
+// neighbour of the two belts, xr(dx, dy) the rho (or psi) of a neighbour of the first.
 template <class C, int NS, typename PS, typename XR>
-__device__ __forceinline__ void site_update(const SiteConsts<typename C::R> &p, const typename C::R (&f)[NS][9],
-                                            const PS &ps, const XR &xr, typename C::R (&rho)[NS],
-                                            typename C::R (&fsa)[NS][9]) {
+__device__ __forceinline__ void site_force(const SiteConsts<typename C::R> &p, const typename C::R (&f)[NS][9],
+                                           const PS &ps, const XR &xr, typename C::R (&drho)[NS], typename C::R (&rho)[NS],
+                                           typename C::R (&jx)[NS], typename C::R (&jy)[NS], typename C::R (&Fx)[NS],
+                                           typename C::R (&Fy)[NS]) {
   using R = typename C::R;
   using V = Vec<R, NS>;
-  R drho[NS], jx[NS], jy[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     drho[s] = sum9(f[s]);
@@ -38,7 +36,6 @@ __device__ __forceinline__ void site_update(const SiteConsts<typename C::R> &p, 
     jx[s] = (f[s][1] + f[s][5] + f[s][8]) - (f[s][3] + f[s][6] + f[s][7]);
     jy[s] = (f[s][2] + f[s][5] + f[s][6]) - (f[s][4] + f[s][7] + f[s][8]);
   }
-  R Fx[NS], Fy[NS];
   {
     const V pc = ps(0, 0);
     const V e1 = ps(1, 0), w1 = ps(-1, 0), n1 = ps(0, 1), s1 = ps(0, -1);
@@ -77,6 +74,17 @@ __device__ __forceinline__ void site_update(const SiteConsts<typename C::R> &p, 
       Fy[s] = fmadd(-c0.v[s], cy, Fy[s]);
     }
   }
+}
+
+// Velocity shift and collision of a site from those: the post-collision deviations, without the
+// exchange with a moving wall.
+template <class C, int NS>
+__device__ __forceinline__ void site_relax(const SiteConsts<typename C::R> &p, const typename C::R (&f)[NS][9],
+                                           const typename C::R (&drho)[NS], const typename C::R (&rho)[NS],
+                                           const typename C::R (&jx)[NS], const typename C::R (&jy)[NS],
+                                           const typename C::R (&Fx)[NS], const typename C::R (&Fy)[NS],
+                                           typename C::R (&fsa)[NS][9]) {
+  using R = typename C::R;
   R nux = jx[0] * p.om[0], nuy = jy[0] * p.om[0], den = rho[0] * p.om[0];
 #pragma unroll
   for (int s = 1; s < NS; ++s) {
@@ -107,6 +115,16 @@ __device__ __forceinline__ void site_update(const SiteConsts<typename C::R> &p, 
     fs[8] = relax(f[s][8], b36, r36, -(uy - ux));
     fs[0] = drho[s] - ((((fs[1] + fs[2]) + (fs[3] + fs[4])) + ((fs[5] + fs[6]) + (fs[7] + fs[8]))));
   }
+}
+
+// Both.
+template <class C, int NS, typename PS, typename XR>
+__device__ __forceinline__ void site_update(const SiteConsts<typename C::R> &p, const typename C::R (&f)[NS][9],
+                                            const PS &ps, const XR &xr, typename C::R (&rho)[NS],
+                                            typename C::R (&fsa)[NS][9]) {
+  typename C::R drho[NS], jx[NS], jy[NS], Fx[NS], Fy[NS];
+  site_force<C, NS>(p, f, ps, xr, drho, rho, jx, jy, Fx, Fy);
+  site_relax<C, NS>(p, f, drho, rho, jx, jy, Fx, Fy, fsa);
 }
 
 // The momentum a moving wall hands the populations it reflects, on the rows next to the walls

@@ -381,32 +381,26 @@ __device__ inline T wave_sum(T v) {
 // the FIFO until its own row is updated, so the loads' latency overlaps steps 3 to 5.
 
 // One tile: strip `strip` (tx = blockDim.x columns) and segment `seg` (a.sy rows) of the
-// lattice described by a, read from src and written to dst.  part: this tile's row of
-// reduction partials; out0: the output of a pass that stores nothing (WHAT_MOMENTS: rho;
-// WHAT_STRESS: the pressure tensor; WHAT_PROFILE: the [64-column block][row][PROF_N] sums);
-// out_u: the WHAT_MOMENTS velocity.
+// lattice described by a, read from src and written to dst.  part: this tile's row of running
+// sums (WHAT_STEP_ACCUM).
 template <int MODE, int NS, bool WALLS, int WHAT, int STP>
 __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const src, void *const dst, const int strip,
-                                         const int seg, double *const part, void *const out0,
-                                         void *const out_u, const int out_f32, const uint32_t tstep) {
+                                         const int seg, double *const part, const uint32_t tstep) {
   using C = Codec<MODE>;
   using R = typename C::R;
   using S = typename C::S;
   using L = typename C::L;
   using V = Vec<R, NS>;
-  constexpr bool STORE = (WHAT == WHAT_STEP || WHAT == WHAT_STEP_ACCUM);
-  constexpr bool REDUCE = (WHAT == WHAT_OBSERVE || WHAT == WHAT_STEP_ACCUM);
   // WHAT_STEP_ACCUM keeps only what stepping averages (wall stress) and the health count,
   // added to this workgroup's own row of running sums; the second pass runs when the host
   // reads them, not every step
   constexpr bool ACCUM = (WHAT == WHAT_STEP_ACCUM);
-  constexpr bool PROFILE = (WHAT == WHAT_PROFILE);
 
   const int TX = blockDim.x;
   const int W4 = TX + 4;
   V *psi_ring = reinterpret_cast<V *>(lb_smem);      // [6][W4]
   V *rho_ring = psi_ring + 6 * W4;                   // [6][W4] (two species only)
-  __shared__ double red_lds[4][RED_N];
+  __shared__ double red_lds[4][ACC_N];
 
   const int lx = a.lx, ly = a.ly;
   // Layout [y][l][pitch][species]: site_b bytes per site (both species), plane_b: byte
@@ -728,112 +722,6 @@ __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const sr
     const R iden = C::rcp(den);
     const R upx = nux * iden, upy = nuy * iden;
 
-    if (WHAT == WHAT_MOMENTS && col_ok) {
-      R sr = rho[0], mx = jx[0] + R(0.5) * Fx[0], my = jy[0] + R(0.5) * Fy[0];
-#pragma unroll
-      for (int s = 1; s < NS; ++s) {
-        sr += rho[s];
-        mx += jx[s] + R(0.5) * Fx[s];
-        my += jy[s] + R(0.5) * Fy[s];
-      }
-      const size_t site = (size_t)y * lx + xc;
-      const size_t nsite = (size_t)lx * ly;
-      if (out0) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          if (out_f32) static_cast<float *>(out0)[s * nsite + site] = float(rho[s]);
-          else static_cast<double *>(out0)[s * nsite + site] = double(rho[s]);
-        }
-      }
-      if (out_u) {
-        const R ux = mx / sr, uy = my / sr;
-        if (out_f32) {
-          static_cast<float *>(out_u)[site] = float(ux);
-          static_cast<float *>(out_u)[nsite + site] = float(uy);
-        } else {
-          static_cast<double *>(out_u)[site] = double(ux);
-          static_cast<double *>(out_u)[nsite + site] = double(uy);
-        }
-      }
-    }
-
-    if (WHAT == WHAT_STRESS && col_ok) {
-      // Pressure tensor of the lattice stress section, per site: sum over species of
-      // c_s^2 rho_s delta + sigma^(int)_s + (tau_s - 1/2)^2 F_s F_s / rho_s, plus the A-B pair
-      // stress.  sigma^(int) follows Appendix A shell by shell (K(q) = G_1 w(q) + G_2 p(q)):
-      //   shells 1, 2: K/2 psi(x) sum psi(x + c) c c
-      //   shells 4, 8: K/4 sum [psi(x) psi(x + c) + psi(x - c/2) psi(x + c/2)] c c
-      //   shell 5:     K/4 psi(x) sum psi(x + c) c c, plus K/4 (psi(x + c_a) psi(x + c_b) + ...) c c
-      //                over the first-belt pairs whose difference is c13, c14, c15 or c16
-      double sxx = 0.0, sxy = 0.0, syy = 0.0;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const R k1 = R(a.K[s][0]) * R(0.5), k2 = R(a.K[s][1]) * R(0.5), k4 = R(a.K[s][2]);
-        const R k5 = R(a.K[s][3]) * R(0.25), k8 = R(a.K[s][4]);
-        const R p0 = pc.v[s];
-        const R E = e1.v[s], W = w1.v[s], N = n1.v[s], S = s1.v[s];
-        const R NE = ne.v[s], NW = nw.v[s], SE = se.v[s], SW = sw.v[s];
-        const R diag = (NE + SW) + (NW + SE), dxy = (NE + SW) - (NW + SE);
-        const R d8 = (d8a.v[s] + d8A.v[s]) + (d8b.v[s] + d8B.v[s]), d8xy = (d8a.v[s] + d8A.v[s]) - (d8b.v[s] + d8B.v[s]);
-        const R mid8 = R(2) * (NE * SW + NW * SE), mid8xy = R(2) * (NE * SW - NW * SE);
-        const R qx = (qa.v[s] + qA.v[s]) + (qb.v[s] + qB.v[s]);  // |c_x| = 2
-        const R qy = (qc.v[s] + qC.v[s]) + (qd.v[s] + qD.v[s]);  // |c_y| = 2
-        const R qxy = ((qa.v[s] + qA.v[s]) + (qc.v[s] + qC.v[s])) - ((qb.v[s] + qB.v[s]) + (qd.v[s] + qD.v[s]));
-        const R e13 = NE * W + E * SW, e14 = NE * S + N * SW, e15 = N * SE + NW * S, e16 = NW * E + W * SE;
-        R xx = k1 * p0 * (E + W) + k2 * p0 * diag + k4 * (p0 * (e2.v[s] + w2.v[s]) + R(2) * (E * W)) +
-               k8 * (p0 * d8 + mid8) + k5 * (p0 * (R(4) * qx + qy) + (R(4) * (e13 + e16) + (e14 + e15)));
-        R yy = k1 * p0 * (N + S) + k2 * p0 * diag + k4 * (p0 * (n2.v[s] + s2.v[s]) + R(2) * (N * S)) +
-               k8 * (p0 * d8 + mid8) + k5 * (p0 * (qx + R(4) * qy) + ((e13 + e16) + R(4) * (e14 + e15)));
-        R xy = k2 * p0 * dxy + k8 * (p0 * d8xy + mid8xy) + k5 * R(2) * (p0 * qxy + ((e13 + e14) - (e15 + e16)));
-        // ideal gas and the discrete forcing correction
-        const R cr = (tau[s] - R(0.5)) * (tau[s] - R(0.5)) / rho[s];
-        xx += rho[s] * R(1.0 / 3.0) + cr * Fx[s] * Fx[s];
-        yy += rho[s] * R(1.0 / 3.0) + cr * Fy[s] * Fy[s];
-        xy += cr * Fx[s] * Fy[s];
-        sxx += double(xx);
-        sxy += double(xy);
-        syy += double(yy);
-      }
-      if (NS == 2) {
-        // A-B repulsion: (G_AB / 2) sum_l t(q) [r_A(x) r_B(x + c) + r_B(x) r_A(x + c)] c c
-        const V *base = a.cross_psi ? psi_ring : rho_ring;
-        const V *xr[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          int sl = lead_slot + 3 + dir * (k - 1);
-          sl = sl >= 6 ? sl - 6 : sl;
-          xr[k] = base + sl * W4 + tid + 2;
-        }
-        const V c0 = xr[1][0];
-        R xx = 0, xy = 0, yy = 0;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const int o = 1 - s;
-          const R ax = xr[1][1].v[o] + xr[1][-1].v[o], ay = xr[2][0].v[o] + xr[0][0].v[o];
-          const R dg = (xr[2][1].v[o] + xr[0][-1].v[o]) + (xr[2][-1].v[o] + xr[0][1].v[o]);
-          const R dgxy = (xr[2][1].v[o] + xr[0][-1].v[o]) - (xr[2][-1].v[o] + xr[0][1].v[o]);
-          xx += c0.v[s] * (T1 * ax + T2 * dg);
-          yy += c0.v[s] * (T1 * ay + T2 * dg);
-          xy += c0.v[s] * (T2 * dgxy);
-        }
-        sxx += double(R(0.5) * xx);
-        sxy += double(R(0.5) * xy);
-        syy += double(R(0.5) * yy);
-      }
-      const size_t site = (size_t)y * lx + xc;
-      const size_t nsite = (size_t)lx * ly;
-      if (out_f32) {
-        static_cast<float *>(out0)[site] = float(sxx);
-        static_cast<float *>(out0)[nsite + site] = float(sxy);
-        static_cast<float *>(out0)[2 * nsite + site] = float(syy);
-      } else {
-        static_cast<double *>(out0)[site] = sxx;
-        static_cast<double *>(out0)[nsite + site] = sxy;
-        static_cast<double *>(out0)[2 * nsite + site] = syy;
-      }
-    }
-
-    if (WHAT != WHAT_MOMENTS && WHAT != WHAT_STRESS) {
     double wb = 0.0, wt = 0.0;
     R fsa[NS][9];
 #pragma unroll
@@ -862,59 +750,14 @@ __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const sr
       // rest population closes the mass balance exactly: d*_0 = drho - sum_{l>0} d*_l
       fs[0] = drho[s] - ((((fs[1] + fs[2]) + (fs[3] + fs[4])) + ((fs[5] + fs[6]) + (fs[7] + fs[8]))));
 
-      if (REDUCE && WALLS && col_ok) {
+      if (ACCUM && WALLS && col_ok) {
         // momentum handed to the wall: c_x f* out minus c_x of the reflected population,
         // which a moving wall raises by 6 W_l rho_w (c_l . U) = +-rho_w U / 6
         if (y == 0) wb += 2.0 * (double(fs[8]) - double(fs[7])) - 2.0 * a.wall_mom[0][s];
         if (y == ly - 1) wt += 2.0 * (double(fs[5]) - double(fs[6])) - 2.0 * a.wall_mom[1][s];
       }
     }
-    if (PROFILE) {
-      // x-momentum crossing the lines above (c_y = +1) and below (c_y = -1) the row when
-      // these populations stream, before any wall term
-      double kup = 0.0, kdn = 0.0;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        kup += double(fsa[s][5] - fsa[s][6]);
-        kdn += double(fsa[s][8] - fsa[s][7]);
-      }
-      // pair forces on this site from partners above it, x components: eq. (FORCE) over the
-      // links with c_y = 1 (|c|^2 = 2, 5) and c_y = 2 (|c|^2 = 5, 8), and the A-B term over
-      // c = (+-1, 1); each +-c_x pair as one difference, as in the force itself
-      double i1 = 0.0, i2 = 0.0;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const R up1 = fmadd(K2[s], ne.v[s] - nw.v[s], K5[s] * (R(2) * (qa.v[s] - qB.v[s])));
-        const R up2 = fmadd(K5[s], qc.v[s] - qD.v[s], K8[s] * (d8a.v[s] - d8B.v[s]));
-        i1 += double(-pc.v[s] * (up1 + up2));
-        i2 += double(-pc.v[s] * up2);
-      }
-      if (NS == 2) {
-        const V *base = a.cross_psi ? psi_ring : rho_ring;
-        int sl0 = lead_slot + 3, sl1 = lead_slot + 3 + dir;
-        sl0 = sl0 >= 6 ? sl0 - 6 : sl0;
-        sl1 = sl1 >= 6 ? sl1 - 6 : (sl1 < 0 ? sl1 + 6 : sl1);
-        const V c0 = base[sl0 * W4 + tid + 2];
-        const V xne = base[sl1 * W4 + tid + 3], xnw = base[sl1 * W4 + tid + 1];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) i1 += double(-c0.v[s] * (T2 * (xne.v[1 - s] - xnw.v[1 - s])));
-      }
-      R sr = rho[0], mx = jx[0] + R(0.5) * Fx[0];
-#pragma unroll
-      for (int s = 1; s < NS; ++s) {
-        sr += rho[s];
-        mx += jx[s] + R(0.5) * Fx[s];
-      }
-      double pv[PROF_N] = {double(mx / sr), kup, kdn, i1, i2, double(rho[0]), NS == 2 ? double(rho[NS - 1]) : 0.0};
-      const int lane = tid & 63, wv = tid >> 6;
-      double *row = static_cast<double *>(out0) + ((size_t)(strip * (TX >> 6) + wv) * ly + y) * PROF_N;
-#pragma unroll
-      for (int k = 0; k < PROF_N; ++k) {
-        const double v = wave_sum(col_ok ? pv[k] : 0.0);
-        if (lane == 0) row[k] = v;
-      }
-    }
-    if (STORE && WALLS && a.moving) {
+    if (WALLS && a.moving) {
       // reflected populations of a moving wall: the stored outgoing population is only ever
       // pulled back into its opposite at the same site, so the wall's momentum goes in here:
       // f_5 = f*_7 + rho_w U_bot / 6, f_6 = f*_8 - rho_w U_bot / 6 off the bottom wall,
@@ -934,7 +777,7 @@ __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const sr
         }
       }
     }
-    if (STORE) {
+    {
       const Rsrc rd = make_rsrc(dst, ld_b);
       if constexpr (MODE == MODE_BF16SR) {
         // random bits from (site, plane, step): the same for every launch shape
@@ -962,29 +805,6 @@ __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const sr
       acc[RED_WTOP] += wt;
       acc[RED_BAD] += bad ? 1.0 : 0.0;
     }
-    if (REDUCE && !ACCUM && col_ok) {
-      R sr = rho[0], mx = jx[0] + R(0.5) * Fx[0];
-      bool bad = !(rho[0] > R(0) && rho[0] < R(INFINITY));
-#pragma unroll
-      for (int s = 1; s < NS; ++s) {
-        sr += rho[s];
-        mx += jx[s] + R(0.5) * Fx[s];
-        bad = bad || !(rho[s] > R(0) && rho[s] < R(INFINITY));
-      }
-      acc[RED_MASS0] += double(rho[0]);
-      if (NS == 2) acc[RED_MASS1] += double(rho[NS - 1]);
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        acc[RED_PX] += double(jx[s]);
-        acc[RED_PY] += double(jy[s]);
-      }
-      acc[RED_WBOT] += wb;
-      acc[RED_WTOP] += wt;
-      acc[RED_FLOW] += double(mx / sr);
-      acc[RED_BAD] += bad ? 1.0 : 0.0;
-    }
-    }  // WHAT != WHAT_MOMENTS
-
   };
 
   int lead_slot = 5;
@@ -1019,20 +839,6 @@ __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const sr
       for (int i = 0; i < nw; ++i) v += red_lds[i][tid];
       part[tid] += v;  // this workgroup's running sums (ACC_N per row)
     }
-  } else if (REDUCE) {
-    const int lane = tid & 63, wv = tid >> 6;
-#pragma unroll
-    for (int k = 0; k < RED_N; ++k) {
-      const double v = wave_sum(acc[k]);
-      if (lane == 0) red_lds[wv][k] = v;
-    }
-    __syncthreads();
-    if (tid < RED_N) {
-      double v = 0.0;
-      const int nw = (TX + 63) >> 6;
-      for (int i = 0; i < nw; ++i) v += red_lds[i][tid];
-      part[tid] = v;
-    }
   }
 }
 
@@ -1051,12 +857,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == MOD
   const int nstrip = (int)gridDim.x / a.nseg;
   const int seg = logical / nstrip;
   const int strip = logical - seg * nstrip;
-  double *const part = WHAT == WHAT_STEP_ACCUM ? a.accrows + (size_t)blockIdx.x * ACC_N
-                                               : a.partials + (size_t)blockIdx.x * RED_N;
-  void *const out0 =
-      WHAT == WHAT_STRESS ? a.out_sigma : (WHAT == WHAT_PROFILE ? static_cast<void *>(a.prof) : a.out_rho);
-  run_tile<MODE, NS, WALLS, WHAT, STP>(a, a.src, a.dst, strip, seg, part, out0, a.out_u, a.out_f32,
-                                       launch_step_index<MODE>(a.t_step, a.t_base));
+  double *const part = WHAT == WHAT_STEP_ACCUM ? a.accrows + (size_t)blockIdx.x * ACC_N : nullptr;
+  run_tile<MODE, NS, WALLS, WHAT, STP>(a, a.src, a.dst, strip, seg, part, launch_step_index<MODE>(a.t_step, a.t_base));
 }
 
 // Many independent lattices in one persistent launch.  The host lists every tile of every
@@ -1076,10 +878,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == MOD
     const int ti = (int)__builtin_amdgcn_readfirstlane((uint32_t)(b.tile0 + t));
     const TileDesc td = b.tiles[ti];
     const StepArgs &a = b.inst[td.inst];
-    double *const part = WHAT == WHAT_STEP_ACCUM ? b.accrows + (size_t)td.part * ACC_N
-                                                 : b.partials + (size_t)td.part * RED_N;
-    run_tile<MODE, NS, WALLS, WHAT, STP>(a, b.src + a.offset, b.dst + a.offset, td.strip, td.seg, part, b.out_rho,
-                                         b.out_u, b.out_f32, tstep);
+    double *const part = WHAT == WHAT_STEP_ACCUM ? b.accrows + (size_t)td.part * ACC_N : nullptr;
+    run_tile<MODE, NS, WALLS, WHAT, STP>(a, b.src + a.offset, b.dst + a.offset, td.strip, td.seg, part, tstep);
   }
 }
 
@@ -1103,18 +903,6 @@ static hipError_t launch_step_t(int what, int tx, int nb, const StepArgs &a, hip
                            st, a);
       else
         hipLaunchKernelGGL((step_kernel<MODE, NS, WALLS, WHAT_STEP_ACCUM>), dim3(nb), dim3(tx), lds, st, a);
-      break;
-    case WHAT_MOMENTS:
-      hipLaunchKernelGGL((step_kernel<MODE, NS, WALLS, WHAT_MOMENTS>), dim3(nb), dim3(tx), lds, st, a);
-      break;
-    case WHAT_OBSERVE:
-      hipLaunchKernelGGL((step_kernel<MODE, NS, WALLS, WHAT_OBSERVE>), dim3(nb), dim3(tx), lds, st, a);
-      break;
-    case WHAT_PROFILE:
-      hipLaunchKernelGGL((step_kernel<MODE, NS, WALLS, WHAT_PROFILE>), dim3(nb), dim3(tx), lds, st, a);
-      break;
-    case WHAT_STRESS:
-      hipLaunchKernelGGL((step_kernel<MODE, NS, WALLS, WHAT_STRESS>), dim3(nb), dim3(tx), lds, st, a);
       break;
     default: return hipErrorInvalidValue;
   }
@@ -1144,18 +932,6 @@ static hipError_t launch_batch_t(int what, int tx, int grid, const BatchArgs &b,
                            lds, st, b);
       else
         hipLaunchKernelGGL((batch_step_kernel<MODE, NS, WALLS, WHAT_STEP_ACCUM>), dim3(grid), dim3(tx), lds, st, b);
-      break;
-    case WHAT_MOMENTS:
-      hipLaunchKernelGGL((batch_step_kernel<MODE, NS, WALLS, WHAT_MOMENTS>), dim3(grid), dim3(tx), lds, st, b);
-      break;
-    case WHAT_OBSERVE:
-      hipLaunchKernelGGL((batch_step_kernel<MODE, NS, WALLS, WHAT_OBSERVE>), dim3(grid), dim3(tx), lds, st, b);
-      break;
-    case WHAT_PROFILE:
-      hipLaunchKernelGGL((batch_step_kernel<MODE, NS, WALLS, WHAT_PROFILE>), dim3(grid), dim3(tx), lds, st, b);
-      break;
-    case WHAT_STRESS:
-      hipLaunchKernelGGL((batch_step_kernel<MODE, NS, WALLS, WHAT_STRESS>), dim3(grid), dim3(tx), lds, st, b);
       break;
     default: return hipErrorInvalidValue;
   }
@@ -1223,9 +999,6 @@ static hipError_t launch_step_sr_t(int what, int tx, int nb, const StepArgs &a, 
         hipLaunchKernelGGL((step_kernel<M, NS, WALLS, WHAT_STEP_ACCUM, kStoreStreaming>), dim3(nb), dim3(tx), lds, st, a);
       else
         hipLaunchKernelGGL((step_kernel<M, NS, WALLS, WHAT_STEP_ACCUM>), dim3(nb), dim3(tx), lds, st, a);
-      break;
-    case WHAT_OBSERVE:
-      hipLaunchKernelGGL((step_kernel<M, NS, WALLS, WHAT_OBSERVE>), dim3(nb), dim3(tx), lds, st, a);
       break;
     default: return hipErrorInvalidValue;
   }

@@ -1,6 +1,7 @@
 // Step and batch launchers of the F64 storage mode: the instantiations of the fused
 // step kernels for this mode (one translation unit per mode, compiled in parallel).
 
+#include "lb_observe.hpp"
 #include "lb_step.hpp"
 #include "lb_step2.hpp"
 
@@ -12,6 +13,15 @@ hipError_t launch_step_f64(int ns, int walls, int what, int tx, int nb, const St
 
 hipError_t launch_batch_f64(int ns, int walls, int what, int tx, int grid, const BatchArgs &b, hipStream_t st) {
   return launch_batch_m<MODE_F64>(ns, walls, what, tx, grid, b, st);
+}
+
+hipError_t launch_observe_f64(int ns, int walls, int what, bool wide, const StepArgs &a, hipStream_t st) {
+  return launch_observe_m<MODE_F64>(ns, walls, what, wide, a, st);
+}
+
+hipError_t launch_batch_observe_f64(int ns, int walls, int first, int count, int blocks, const BatchTiles &b,
+                                   const ReduceJob *jobs, double *partials, hipStream_t st) {
+  return launch_batch_observe_m<MODE_F64>(ns, walls, first, count, blocks, b, jobs, partials, st);
 }
 
 int blocks_per_cu_f64(int ns, int walls, int tx) { return blocks_per_cu_m<MODE_F64>(ns, walls, tx); }

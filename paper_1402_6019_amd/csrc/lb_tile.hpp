@@ -44,6 +44,52 @@ constexpr size_t tile_lds_bytes() {
 // A coordinate wrapped onto [0, n); lattices narrower than a region may wrap more than once.
 __device__ __forceinline__ int wrap_any(int v, int n, bool narrow) { return narrow ? ((v % n) + n) % n : wrapi(v, n); }
 
+// Site tid + m NT of the list of a stage that updates a tile and a margin of H: those sites row by row,
+// then the two-site frame around them; relative to the tile's first site.
+template <int BX, int BY, int H, int NT>
+__device__ __forceinline__ void tile_site(int tid, int m, int &sx, int &sy) {
+  constexpr int UX = BX + 2 * H, EX = UX + 4, NU = UX * (BY + 2 * H), NE = EX * (BY + 2 * H + 4);
+  const int i = min(tid + m * NT, NE - 1);
+  const int r = i / UX;
+  sx = i - r * UX - H;
+  sy = r - H;
+  if ((m + 1) * NT > NU) {
+    // the frame: two rows below, two above, then two columns on either side
+    const int q = max(i - NU, 0), t = q - 4 * EX;
+    const int fr = q / EX, fy = fr < 2 ? fr - 2 : fr + (BY + 2 * H) - 2;
+    const int c = t & 3, fc = c < 2 ? c - 2 : c + UX - 2;
+    const int fx = t < 0 ? q - fr * EX - 2 : fc, fz = t < 0 ? fy : t >> 2;
+    const bool frame = m * NT >= NU || i >= NU;
+    sx = frame ? fx - H : sx;
+    sy = frame ? fz - H : sy;
+  }
+}
+
+// Byte offsets of the nine pulls of site (x, y): rows past a wall pull the row next to it (their values
+// are not used).  The plane goes into the uniform offset; a reflected pull, of the opposite plane two
+// planes up (off the lower wall) or down, has that difference in its lane offset.
+template <bool WALLS, typename A>
+__device__ __forceinline__ void pull_offsets(const A &a, uint32_t site_b, int x, int yg, uint32_t (&o)[9]) {
+  const int lx = a.lx, ly = a.ly;
+  const uint32_t plane_b = a.pitch_b, row_b = 9u * a.pitch_b;
+  const int y = WALLS ? min(max(yg, 0), ly - 1) : yg;
+  const bool lo = y == 0, hi = y == ly - 1;
+  const uint32_t ro = (uint32_t)y * row_b;
+  const uint32_t rm = lo ? (WALLS ? 2 * plane_b : (uint32_t)(ly - 1) * row_b) : ro - row_b;
+  const uint32_t rp = hi ? (WALLS ? ro - 2 * plane_b : 0u) : ro + row_b;
+  const uint32_t cc = (uint32_t)x * site_b, cm = (x == 0 ? (uint32_t)lx * site_b : cc) - site_b,
+                 cp = x == lx - 1 ? 0u : cc + site_b;
+  o[0] = ro + cc;
+  o[1] = ro + cm;
+  o[3] = ro + cp;
+  o[2] = rm + cc;
+  o[5] = rm + (WALLS && lo ? cc : cm);
+  o[6] = rm + (WALLS && lo ? cc : cp);
+  o[4] = rp + cc;
+  o[7] = rp + (WALLS && hi ? cc : cp);
+  o[8] = rp + (WALLS && hi ? cc : cm);
+}
+
 // N steps of the tile whose first site is (x0, y0), of the lattice described by a, from src to dst.
 // t0: time step of the first (stochastic rounding); red_mask: which steps reduce, into the
 // running sums accrow.
@@ -77,24 +123,6 @@ __device__ __forceinline__ void tile_steps(const TileArgs<typename Codec<MODE>::
     constexpr int k = decltype(kc)::value;
     constexpr int H = D::h(k), UX = D::ux(k), EX = D::ex(k), NU = D::nu(k), NE = D::ne(k);
     constexpr int M = (NE + NT - 1) / NT, MU = (NU + NT - 1) / NT;
-    // site tid + m NT of the stage's list, relative to the tile's first site (of round m, which
-    // reaches the frame or still the sites to update as the conditions on m say)
-    auto site = [&](int m, int &sx, int &sy) {
-      const int i = min(tid + m * NT, NE - 1);
-      const int r = i / UX;
-      sx = i - r * UX - H;
-      sy = r - H;
-      if ((m + 1) * NT > NU) {
-        // the frame: two rows below, two above, then two columns on either side
-        const int q = max(i - NU, 0), t = q - 4 * EX;
-        const int fr = q / EX, fy = fr < 2 ? fr - 2 : fr + (BY + 2 * H) - 2;
-        const int c = t & 3, fc = c < 2 ? c - 2 : c + UX - 2;
-        const int fx = t < 0 ? q - fr * EX - 2 : fc, fz = t < 0 ? fy : t >> 2;
-        const bool frame = m * NT >= NU || i >= NU;
-        sx = frame ? fx - H : sx;
-        sy = frame ? fz - H : sy;
-      }
-    };
     int pe[M], yg[M];  // the corner (-2, -2) of the site's neighbourhood in psi, and its row
     R f[M][NS][9];
     if constexpr (k == 1) {
@@ -106,30 +134,12 @@ __device__ __forceinline__ void tile_steps(const TileArgs<typename Codec<MODE>::
         // latency, gains nothing from it and loses 1.5% to the branch)
         if (BX * BY > 64 && (m + 1) * NT - NE >= 64 && (int)uni((uint32_t)tid & ~63u) + m * NT >= NE) continue;
         int sx, sy;
-        site(m, sx, sy);
+        tile_site<BX, BY, H, NT>(tid, m, sx, sy);
         pe[m] = (sy + H) * EX + sx + H;
         const int x = wrap_any(x0 + sx, lx, narrow_x);
         yg[m] = WALLS ? y0 + sy : wrap_any(y0 + sy, ly, narrow_y);
-        // rows past a wall pull the row next to it (their values are not used)
-        const int y = WALLS ? min(max(yg[m], 0), ly - 1) : yg[m];
-        const bool lo = y == 0, hi = y == ly - 1;
-        const uint32_t ro = (uint32_t)y * row_b;
-        const uint32_t rm = lo ? (WALLS ? 2 * plane_b : (uint32_t)(ly - 1) * row_b) : ro - row_b;
-        const uint32_t rp = hi ? (WALLS ? ro - 2 * plane_b : 0u) : ro + row_b;
-        const uint32_t cc = (uint32_t)x * site_b, cm = (x == 0 ? (uint32_t)lx * site_b : cc) - site_b,
-                       cp = x == lx - 1 ? 0u : cc + site_b;
-        // the plane goes into the uniform offset; a reflected pull, of the opposite plane two
-        // planes up (off the lower wall) or down, has that difference in its lane offset
         uint32_t o[9];
-        o[0] = ro + cc;
-        o[1] = ro + cm;
-        o[3] = ro + cp;
-        o[2] = rm + cc;
-        o[5] = rm + (WALLS && lo ? cc : cm);
-        o[6] = rm + (WALLS && lo ? cc : cp);
-        o[4] = rp + cc;
-        o[7] = rp + (WALLS && hi ? cc : cp);
-        o[8] = rp + (WALLS && hi ? cc : cm);
+        pull_offsets<WALLS>(a, site_b, x, yg[m], o);
 #pragma unroll
         for (int l = 0; l < 9; ++l) {
           if (NS == 2) C::bload2(rs, o[l], uni((uint32_t)l * plane_b), fl[m][0][l], fl[m][NS - 1][l]);
@@ -148,7 +158,7 @@ __device__ __forceinline__ void tile_steps(const TileArgs<typename Codec<MODE>::
       if ((m + 1) * NT > NE && tid + m * NT >= NE) continue;
       if constexpr (k > 1) {
         int sx, sy;
-        site(m, sx, sy);
+        tile_site<BX, BY, H, NT>(tid, m, sx, sy);
         pe[m] = (sy + H) * EX + sx + H;
         yg[m] = WALLS ? y0 + sy : 0;
         const bool lo = WALLS && yg[m] == 0, hi = WALLS && yg[m] == ly - 1;
