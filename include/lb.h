@@ -375,13 +375,14 @@ int lb_disjoining_pressure(const double *h, const double *gamma_f, int32_t n, do
  * W_bot/W_top as in lb_wall_stress for step t, Q(t) = (1/lx) sum_x u_x (u as in lb_moments),
  * t running over the T steps from the current state, which is held fixed.  Outputs (host):
  * *loss = L and grad[7] = dL/d(G_AA,1, G_BB,1, G_AA,2, G_BB,2, G_AB, g_x, g_y).
- * The forward pass keeps an FP64 checkpoint of the populations every `every` steps
- * (every <= 0: ceil(sqrt(T))); the reverse sweep recomputes each segment's states from its
- * checkpoint and runs the hand-written reverse step (FP64 for LB_F64 contexts or with
- * flags & LB_ADJ_FP64, FP32 otherwise).  With several segments the reverse steps run on a
- * second stream of the library's own, created and destroyed by the call, one segment behind
- * the recompute on the context's stream (two segment buffers in the workspace); the result
- * does not depend on the overlap.  every = 1 keeps instead what the reverse step reads
+ * The forward pass keeps a copy of the populations every `every` steps (every <= 0:
+ * ceil(sqrt(T))); the reverse sweep recomputes each segment's states from its copy and runs the
+ * hand-written reverse step (FP64 for LB_F64 contexts or with flags & LB_ADJ_FP64, FP32
+ * otherwise).  The last two segments are not recomputed: the forward pass leaves what the reverse
+ * step reads of their states in the two segment buffers of the workspace.  With several segments
+ * the reverse steps run on a second stream of the library's own, created and destroyed by the call,
+ * one segment behind the recompute on the context's stream; the result does not depend on the
+ * overlap.  every = 1 (and every >= T, one segment) keeps what the reverse step reads
  * of every state (moments and pseudopotential of every site, populations of the two rows
  * next to the walls): no recompute, at about T * 64 (FP64 reverse) or T * 32 (FP32) bytes per
  * site of workspace.  workspace: device buffer of

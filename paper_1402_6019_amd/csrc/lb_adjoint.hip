@@ -179,8 +179,7 @@ struct AdjDims {
 template <typename R, int NS, int BX, int BY, int NT>
 constexpr size_t adj_lds_bytes() {
   using D = AdjDims<BX, BY>;
-  constexpr size_t sites = (size_t)NS * (2 * D::NSTG + 4 * D::NL) * sizeof(R), sums = (size_t)ADJ_N * NT * sizeof(double);
-  return sites > sums ? sites : sums;
+  return (size_t)NS * (2 * D::NSTG + 4 * D::NL) * sizeof(R) + (size_t)ADJ_N * BX * BY * sizeof(double);
 }
 
 // One reverse step: lambda(t) from lambda(t+1) (a.lam_next) and the state of step t (a.fields, a.x), and
@@ -188,15 +187,19 @@ constexpr size_t adj_lds_bytes() {
 // The gather over A and B reads two sites past the tile, so the local part runs on the tile and a frame
 // of two and A and B never leave LDS: FP64 with two species moves 352 B per site (8 planes of fields, 18
 // of lambda each way) where a local and a gather pass moved 640.  Bound by FP64 and address
-// instructions at two waves per SIMD (236 registers), not by memory: 512 x 256 walled, FP64, two
-// species, beside the recompute stream: 23.0 us (4 TB/s) against 19.5 + 7.3 us for the two passes.  One
+// instructions at two waves per SIMD (244 registers), not by memory: 512 x 256 walled, FP64, two
+// species, beside the recompute stream: 23.0 us (2 TB/s) against 19.5 + 7.3 us for the two passes; alone
+// 20.3 us, vector units busy 37% of it (the frame's round occupies half of the waves; in 64 x 8 tiles
+// 19.9 us, in 16 x 16 26).  One
 // buffer range per array, planes in the uniform offset: a range per plane spilled scalar registers (728
 // of 2800 vector instructions only moved them; 25.9 us).
 template <typename R, int NS, bool WALLS, bool WIDE, int BX, int BY, int NT>
 __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
   using D = AdjDims<BX, BY>;
   constexpr int M = (D::NL + NT - 1) / NT, MT = (BX * BY + NT - 1) / NT;  // rounds of the region and of the tile
-  R *const sps = reinterpret_cast<R *>(lb_smem);  // psi of the state [NS][SY][SX]
+  constexpr int NU = BX * BY;
+  double *const sm = reinterpret_cast<double *>(lb_smem);  // the tile's sites' terms of the sums [ADJ_N][NU]
+  R *const sps = reinterpret_cast<R *>(sm + ADJ_N * NU);   // psi of the state [NS][SY][SX]
   R *const srh = sps + NS * D::NSTG;              // rho
   R *const sab = srh + NS * D::NSTG;              // A_s, B_s (x, y each) [NS][4][LY][LX]
   const int tid = threadIdx.x, lx = a.lx, ly = a.ly;
@@ -249,9 +252,6 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
   }
   __syncthreads();
 
-  double vals[ADJ_N];
-#pragma unroll
-  for (int k = 0; k < ADJ_N; ++k) vals[k] = 0.0;
   R lam[MT][NS][Q];  // the local part of lambda(t) at the tile's sites
 #pragma unroll
   for (int m = 0; m < M; ++m) {
@@ -267,6 +267,9 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
       for (int s = 0; s < NS; ++s)
 #pragma unroll
         for (int c = 0; c < 4; ++c) sab[(s * 4 + c) * D::NL + e] = R(0);
+      if (own)
+#pragma unroll
+        for (int k = 0; k < ADJ_N; ++k) sm[k * NU + i0] = 0.0;
       continue;
     }
     const int x = wrap(x0 + sx, lx), y = WALLS ? yr : wrap(yr, ly);
@@ -292,18 +295,6 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
       jx[s] = fields.load(4 + s, off);
       jy[s] = fields.load(6 + s, off);
     }
-    // and, on the two wall rows, their pre-collision populations (the wall stress's source)
-    R xwr[NS][Q];
-    if constexpr (WALLS) {
-      if (y == 0 || y == ly - 1) {
-        each_index<Q>([&](auto L) {
-          constexpr int l = decltype(L)::value, cy = CYS[l];
-          if constexpr (cy != 0)
-            for (int s = 0; s < NS; ++s) xwr[s][l] = R(a.x[((size_t)(s * Q + l) * 2 + (cy < 0 ? 0 : 1)) * lx + x]);
-        });
-      }
-    }
-
     const R *const pp = sps + (sy + 4) * D::SX + sx + 4, *const rr = srh + (sy + 4) * D::SX + sx + 4;
     auto psi_at = [&](int s, int dx, int dy) -> R { return pp[s * D::NSTG + dy * D::SX + dx]; };
     auto rho_at = [&](int s, int dx, int dy) -> R { return rr[s * D::NSTG + dy * D::SX + dx]; };
@@ -332,6 +323,7 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
       Fx[s] = -psi[s] * (R(a.g1[s]) * ax + R(a.g2[s]) * bx);
       Fy[s] = -psi[s] * (R(a.g1[s]) * ay + R(a.g2[s]) * by);
       xx[s] = 0; xy[s] = 0; self[s] = 0;
+      __builtin_amdgcn_sched_barrier(0);
     }
     if (NS == 2) {
       for (int s = 0; s < 2; ++s) {
@@ -349,6 +341,7 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
         self[s] = a.cross_psi ? psi[s] : rho[s];
         Fx[s] -= R(a.gab) * self[s] * cx;
         Fy[s] -= R(a.gab) * self[s] * cy;
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     for (int s = 0; s < NS; ++s) {
@@ -403,8 +396,9 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
             // wall stress: d/dy_l of cW (1/2)(1/lx) (2 c_lx y_l - 6 W_l rho_w c_lx^2 U); the
             // moving wall's share is constant
             if constexpr (cx != 0) al += cmul<cx>(cW) * ilx;
-            // post-collision population leaving the wall row
-            const R yl = (R(1) - om) * xwr[s][l] + om * feq;
+            // post-collision population leaving the wall row, from its pre-collision one
+            const R xl = R(a.x[((size_t)(s * Q + l) * 2 + (cy < 0 ? 0 : 1)) * lx + x]);
+            const R yl = (R(1) - om) * xl + om * feq;
             const R mw = R(3) * wl * R(a.rho_w[s]) * R(cx * cx) * R(cy < 0 ? a.u_wall[0] : a.u_wall[1]);
             if (live) loss_w += double(cW * (R(cx) * yl - mw));
           }
@@ -422,6 +416,7 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
       fby[s] = tau * by * ir;
       rb -= tau * (Fx[s] * bx + Fy[s] * by) * (ir * ir);
       rbar[s] = rb;
+      __builtin_amdgcn_sched_barrier(0);
     }
     for (int s = 0; s < NS; ++s) {
       const R om = R(a.omega[s]);
@@ -474,10 +469,10 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
       sab[(s * 4 + 2) * D::NL + e] = self[s] * fbx[s];
       sab[(s * 4 + 3) * D::NL + e] = self[s] * fby[s];
     }
-    if (live) {
+    if (own) {
       const double v[ADJ_N] = {dg1[0], dg1[1], dg2[0], dg2[1], dgab, dgx, dgy, loss_w, loss_q};
 #pragma unroll
-      for (int k = 0; k < ADJ_N; ++k) vals[k] += v[k];
+      for (int k = 0; k < ADJ_N; ++k) sm[k * NU + i0] = v[k];  // zeros past the lattice's end
     }
   }
   __syncthreads();
@@ -504,19 +499,14 @@ __global__ __launch_bounds__(NT) void adj_step_kernel(AdjArgs a) {
         lout.store(s * Q + l, off, lam[m][s][l] + corr[s]);
   }
 
-  // the tile's sums, through LDS: wave w sums the terms w, w + waves, ... over the threads, in a fixed
-  // order, and adds them to the tile's row (a shuffle tree of every term in every wave took as
-  // many LDS operations as the update)
-  __syncthreads();
-  double *const sm = reinterpret_cast<double *>(lb_smem);  // [ADJ_N][NT]
-#pragma unroll
-  for (int k = 0; k < ADJ_N; ++k) sm[k * NT + tid] = vals[k];
-  __syncthreads();
+  // the tile's sums: wave w sums the terms w, w + waves, ... over the sites, in a fixed order, and adds
+  // them to the tile's row (a shuffle tree of every term in every wave took as many LDS operations as
+  // the update)
   const int lane = tid & 63;
   for (int k = tid >> 6; k < ADJ_N; k += NT / 64) {
-    double v = sm[k * NT + lane];
+    double v = sm[k * NU + lane];
 #pragma unroll
-    for (int w = 1; w < NT / 64; ++w) v += sm[k * NT + w * 64 + lane];
+    for (int w = 1; w < NU / 64; ++w) v += sm[k * NU + w * 64 + lane];
     v = wave_sum(v);
     if (k == ADJ_LW || k == ADJ_LQ) v /= lx;
     if (lane == 0) a.partials[(size_t)blockIdx.x * ADJ_N + k] += v;

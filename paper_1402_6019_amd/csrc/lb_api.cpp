@@ -203,16 +203,16 @@ hipError_t launch_tile_steps(const lb_ctx *c, int shape, int n, int from, int wh
   return launch_tile(step_mode(c), c->lat.n_species, c->lat.walls, what, shape, n, a, o, st);
 }
 
-// n = 1 or 2 plain steps from buffer `from` that also write what the adjoint's reverse step reads of
-// the states stepped from (as launch_checkpoint_fields_from does): fields (FP64 if fp64) and the
-// FP64 populations of the rows next to the walls into xw, the second state's fb and xb bytes
-// further on.  Bitwise the same steps and the same fields as the separate passes.
-hipError_t launch_fields_steps(const lb_ctx *c, int n, int from, void *xw, size_t xb, void *fields, size_t fb, int fp64,
-                               hipStream_t st) {
+// n = 1 or 2 plain steps from population buffer src into dst that also write what the adjoint's reverse
+// step reads of the states stepped from: the fields rho, psi, j per species (FP64 if fp64) and the
+// canonical FP64 pre-collision populations of the rows next to the walls ([s][l][2][lx]) into xw, the
+// second state's fb and xb bytes further on.
+hipError_t launch_fields_steps(const lb_ctx *c, int n, const void *src, void *dst, void *xw, size_t xb, void *fields,
+                               size_t fb, int fp64, hipStream_t st) {
   StepArgs a;
   fill_step_args(c, a);
-  a.src = c->pop[from];
-  a.dst = c->pop[from ^ 1];
+  a.src = src;
+  a.dst = dst;
   a.out_rho = fields;
   a.out_u = xw;
   TileOpts o;
@@ -238,26 +238,6 @@ hipError_t launch_two_steps(const lb_ctx *c, int from, hipStream_t st, uint32_t 
   a.t_step = t_step;
   a.t_base = t_base;
   return launch_step2(step_mode(c), c->lat.n_species, c->lat.walls, nb, a, st);
-}
-
-// What the adjoint's reverse step reads of the state in buffer `from`: the canonical FP64
-// pre-collision populations of the rows next to the walls into dst ([s][l][2][lx]), and the
-// fields rho, psi, j per species (FP64 if fp64) into fields, on stream st.
-hipError_t launch_checkpoint_fields_from(const lb_ctx *c, int from, void *dst, void *fields, int fp64, hipStream_t st) {
-  LayoutArgs la{};
-  la.in = c->pop[from];
-  la.out = dst;
-  la.plane = c->plane;
-  la.lx = c->lat.lx;
-  la.ly = c->lat.ly;
-  la.pitch = c->pitch;
-  la.ns = c->lat.n_species;
-  la.rho_ref[0] = c->psi.rho_ref[0];
-  la.rho_ref[1] = c->psi.rho_ref[1];
-  la.fields = fields;
-  la.psi0 = c->psi.psi0;
-  la.irho0 = 1.0 / c->psi.rho0;
-  return launch_checkpoint_fields(c->lat.storage, c->lat.walls, fp64, la, st);
 }
 
 // Fold the running sums of the reducing steps since the last flush into d_acc.
@@ -911,8 +891,9 @@ struct AdjLayout {
   bool all = false;  // every == 1: what the reverse step reads of every state, kept by the forward pass
   int64_t per = 1;   // states per segment buffer
   int nbuf = 1;      // segment buffers
-  size_t s64 = 0, lamb = 0, nsite = 0, fb = 0, xw = 0;
-  size_t ckpt = 0, seg = 0, fin = 0, lam0 = 0, lam1 = 0, fields = 0, partials = 0, acc = 0;
+  int nck = 0;       // segments recomputed from a checkpoint (all but the last nbuf)
+  size_t popb = 0, lamb = 0, nsite = 0, fb = 0, xw = 0;
+  size_t ckpt = 0, seg = 0, lam0 = 0, lam1 = 0, fields = 0, partials = 0, acc = 0;
   size_t total = 0;
 };
 
@@ -929,22 +910,22 @@ AdjLayout adjoint_layout(const lb_ctx *c, int64_t T, int32_t every, int32_t flag
   const size_t rs = adjoint_fp64(c, flags) ? 8 : 4;
   const int ns = c->lat.n_species;
   L.all = L.every == 1;
-  // no checkpoints to restore from when every state is kept
-  if (L.all) L.ncp = 0;
+  // one segment of all states: nothing to recompute
+  if (L.all) L.ncp = 1;
   // per state: the FP64 populations of the two rows next to the walls, and the fields; with
   // several checkpoint segments, two segment buffers (one is recomputed while the reverse
   // sweep reads the other)
   L.per = L.all ? std::max<int64_t>(T, 1) : L.every;
   L.nbuf = L.ncp > 1 ? 2 : 1;
+  L.nck = L.ncp - L.nbuf;
   const int64_t nstate = L.per * L.nbuf;
-  L.s64 = align256((size_t)ns * 9 * L.nsite * 8);
+  L.popb = align256(lb_pop_bytes(&c->lat));
   L.xw = align256((size_t)ns * 9 * 2 * c->lat.lx * 8);
   L.lamb = align256((size_t)ns * 9 * L.nsite * rs);
   L.fb = align256(8 * L.nsite * rs);
   size_t o = 0;
-  L.ckpt = o; o += (size_t)L.ncp * L.s64;
+  L.ckpt = o; o += (size_t)L.nck * L.popb;
   L.seg = o; o += (size_t)nstate * L.xw;
-  L.fin = o; o += L.all ? 0 : align256(lb_pop_bytes(&c->lat));
   L.lam0 = o; o += L.lamb;
   L.lam1 = o; o += L.lamb;
   L.fields = o; o += (size_t)nstate * L.fb;  // one set per state of a segment (of the run when all)
@@ -1011,7 +992,6 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   int rc = poll_health(c, true);
   if (rc) return rc;
   char *ws = static_cast<char *>(workspace);
-  const int64_t t0 = c->t;
   const int keep_reduce = c->reduce_every;
   c->reduce_every = 0;
   auto done = [&](int code) {
@@ -1019,59 +999,53 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
     return code;
   };
   const int fp64 = adjoint_fp64(c, flags) ? 1 : 0;
+  // what the reverse step reads of state jj of segment buffer b
+  auto seg_x = [&](int b, int64_t jj) { return ws + L.seg + ((size_t)b * L.per + (size_t)jj) * L.xw; };
+  auto seg_f = [&](int b, int64_t jj) { return ws + L.fields + ((size_t)b * L.per + (size_t)jj) * L.fb; };
+  auto seg_len = [&](int k) { return L.all ? T : std::min<int64_t>(L.every, T - (int64_t)k * L.every); };
+  // The states of segment k into its buffer, two per launch, from src, ping-pong with other; returns where
+  // the state after the segment is.
+  auto states = [&](int k, void *src, void *other, hipError_t *er) -> void * {
+    const int b = k % L.nbuf;
+    const int64_t len = seg_len(k);
+    for (int64_t jj = 0; jj < len && *er == hipSuccess; jj += 2, std::swap(src, other))
+      *er = launch_fields_steps(c, (int)std::min<int64_t>(2, len - jj), src, other, seg_x(b, jj), L.xw, seg_f(b, jj), L.fb,
+                                fp64, c->stream);
+    return src;
+  };
+  // Forward pass: the last segments, one per buffer, leave what the reverse sweep reads as they are
+  // stepped; a segment before them leaves a copy of the populations it starts from.
   hipError_t e = hipSuccess;
-  if (L.all) {
-    // forward pass keeping what the reverse step reads of every state: no recompute later
-    for (int64_t t = 0; t < T && e == hipSuccess; t += 2) {
-      const int n = (int)std::min<int64_t>(2, T - t);
-      e = launch_fields_steps(c, n, c->cur, ws + L.seg + (size_t)t * L.xw, L.xw, ws + L.fields + (size_t)t * L.fb, L.fb,
-                              fp64, c->stream);
-      c->cur ^= 1;
-      c->t += n;
-    }
-    if (e != hipSuccess) return done(hip_fail(c, e, "adjoint forward pass"));
-  } else {
-    // forward pass with a checkpoint every L.every steps
-    for (int k = 0; k < L.ncp; ++k) {
-      if ((rc = lb_checkpoint(c, ws + L.ckpt + (size_t)k * L.s64))) return done(rc);
-      if ((rc = lb_step(c, std::min<int64_t>(L.every, T - (int64_t)k * L.every)))) return done(rc);
+  for (int k = 0; k < L.ncp && e == hipSuccess; ++k) {
+    if (k < L.nck) {
+      e = launch_stream_copy(ws + L.ckpt + (size_t)k * L.popb, c->pop[c->cur], lb_pop_bytes(&c->lat) / 16, 0, 4 * c->n_cu,
+                             c->stream);
+      if (e == hipSuccess && (rc = lb_step(c, seg_len(k)))) return done(rc);
+    } else {
+      c->cur = states(k, c->pop[c->cur], c->pop[c->cur ^ 1], &e) == c->pop[0] ? 0 : 1;
+      c->t += seg_len(k);
     }
   }
-  // the final state, bit for bit (the context continues from it; the checkpointed sweep
-  // overwrites the population buffers while recomputing)
+  if (e != hipSuccess) return done(hip_fail(c, e, "adjoint forward pass"));
+  // the final state stays in its buffer: a recompute alternates between the other one and the
+  // checkpoint it starts from, which nothing reads again
   const int cur_final = c->cur;
-  const size_t popb = lb_pop_bytes(&c->lat);
-  if (!L.all) e = hipMemcpyAsync(ws + L.fin, c->pop[cur_final], popb, hipMemcpyDeviceToDevice, c->stream);
+  if (!L.all) e = launch_fill(c->d_acc, 0.0, 4, c->stream);  // the running wall-stress average is reset
   if (e == hipSuccess) e = launch_zero(ws + L.lam1, L.lamb, c->stream);
   if (e == hipSuccess) e = launch_zero(ws + L.acc, ADJ_N * 8, c->stream);
   if (e == hipSuccess)
     e = launch_zero(ws + L.partials, (size_t)adj_blocks(c->lat.lx, c->lat.ly) * ADJ_N * 8, c->stream);
   if (e != hipSuccess) return done(hip_fail(c, e, "adjoint setup"));
-  // reverse sweep: over the whole run when every state was kept, else one checkpoint segment at
-  // a time
   AdjArgs a = adjoint_args(c, loss_weights[0], loss_weights[1], T);
   a.partials = reinterpret_cast<double *>(ws + L.partials);
   double *acc = reinterpret_cast<double *>(ws + L.acc);
   // lambda(t+1) is lam_buf[q], lambda(t) lam_buf[q ^ 1]
   char *lam_buf[2] = {ws + L.lam1, ws + L.lam0};
   int q = 0;
-  // what the reverse step reads of state jj of segment buffer b
-  auto seg_x = [&](int b, int jj) { return ws + L.seg + ((size_t)b * L.per + jj) * L.xw; };
-  auto seg_f = [&](int b, int jj) { return ws + L.fields + ((size_t)b * L.per + jj) * L.fb; };
-  // Every state of a segment but the last is stepped from, two per launch, which writes its fields
-  // on the way; the last one's fields come from a pass of their own.
-  auto recompute = [&](int from, int len, int b, hipStream_t st) -> hipError_t {
-    hipError_t er = hipSuccess;
-    int buf = from;
-    for (int jj = 0; jj + 1 < len && er == hipSuccess; jj += 2, buf ^= 1)
-      er = launch_fields_steps(c, std::min(2, len - 1 - jj), buf, seg_x(b, jj), L.xw, seg_f(b, jj), L.fb, fp64, st);
-    if (er == hipSuccess) er = launch_checkpoint_fields_from(c, buf, seg_x(b, len - 1), seg_f(b, len - 1), fp64, st);
-    return er;
-  };
-  auto reverse = [&](int q0, int len, int b, hipStream_t st) -> hipError_t {
+  auto reverse = [&](int q0, int64_t len, int b, hipStream_t st) -> hipError_t {
     hipError_t er = hipSuccess;
     int qq = q0;
-    for (int jj = len - 1; jj >= 0 && er == hipSuccess; --jj) {
+    for (int64_t jj = len - 1; jj >= 0 && er == hipSuccess; --jj) {
       a.x = reinterpret_cast<const double *>(seg_x(b, jj));
       a.fields = seg_f(b, jj);
       a.lam_next = lam_buf[qq];
@@ -1085,19 +1059,18 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   // recompute on the context's stream: segment k's reverse steps overlap segment k - 1's
   // recompute into the other buffer.  Events order the two (a recompute waits until the
   // reverse sweep that read its buffer has finished), so every kernel reads what it read
-  // with one stream, and the result is bitwise the same.  A full segment's recompute and its
-  // reverse sweep are the same launches for every full segment up to the buffer and the
-  // ping-pong parities: each is captured once per combination as a HIP graph and replayed; a
-  // shorter last segment runs eagerly.
-  GraphCache g_fwd[2], g_rev[2];
-  for (int b = 0; b < 2; ++b) g_fwd[b].steps = g_rev[b].steps = 1;
+  // with one stream, and the result is bitwise the same.  A full segment's reverse sweep is the
+  // same launches for every full segment up to the buffer and lambda's parity: it is captured
+  // once per combination as a HIP graph and replayed; a shorter last segment, and a single one,
+  // run eagerly.
+  GraphCache g_rev[2];
+  for (int b = 0; b < 2; ++b) g_rev[b].steps = 1;
   hipStream_t rst = c->stream;
   hipEvent_t ev_rec[2] = {nullptr, nullptr}, ev_rev[2] = {nullptr, nullptr};
   const bool two = L.nbuf == 2;
   auto release = [&]() {
     if (rst != c->stream) (void)hipStreamSynchronize(rst);
     for (int b = 0; b < 2; ++b) {
-      g_fwd[b].destroy();
       g_rev[b].destroy();
       if (ev_rec[b]) (void)hipEventDestroy(ev_rec[b]);
       if (ev_rev[b]) (void)hipEventDestroy(ev_rev[b]);
@@ -1121,40 +1094,21 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
     }
     if (e != hipSuccess) return graphs_done(hip_fail(c, e, "adjoint streams"));
   }
-  if (L.all) {
-    // every state was kept: one reverse sweep over the whole run
-    e = reverse(q, (int)T, 0, c->stream);
-    if (e != hipSuccess) return graphs_done(hip_fail(c, e, "adjoint sweep"));
-  }
-  auto seg_len = [&](int k) { return (int)std::min<int64_t>(L.every, T - (int64_t)k * L.every); };
-  // restore checkpoint k and recompute its segment into buffer k % nbuf (context's stream)
+  // recompute segment k from its checkpoint into buffer k % nbuf (context's stream)
   auto recompute_segment = [&](int k) -> int {
-    const int len = seg_len(k), b = k % L.nbuf;
-    int r = lb_restore(c, ws + L.ckpt + (size_t)k * L.s64);
-    if (r) return r;
-    hipError_t er = hipSuccess;
-    if (two && k + 2 < L.ncp) er = hipStreamWaitEvent(c->stream, ev_rev[b], 0);
-    const int from = c->cur;
-    if (er == hipSuccess) {
-      if (len == L.every) {
-        hipGraphExec_t gf = nullptr;
-        er = g_fwd[b].get(from, [&](int, hipStream_t st) { return recompute(from, len, b, st); }, &gf);
-        if (er == hipSuccess) er = hipGraphLaunch(gf, c->stream);
-      } else {
-        er = recompute(from, len, b, c->stream);
-      }
-    }
-    if (er == hipSuccess && two) er = hipEventRecord(ev_rec[b], c->stream);
+    hipError_t er = hipStreamWaitEvent(c->stream, ev_rev[k % L.nbuf], 0);
+    (void)states(k, ws + L.ckpt + (size_t)k * L.popb, c->pop[cur_final ^ 1], &er);
+    if (er == hipSuccess) er = hipEventRecord(ev_rec[k % L.nbuf], c->stream);
     if (er != hipSuccess) return hip_fail(c, er, "adjoint recompute");
-    c->cur = from ^ ((len / 2) & 1);  // len - 1 steps, two per launch
     return LB_OK;
   };
   // the reverse steps of segment k (second stream, after its recompute)
   auto reverse_segment = [&](int k) -> int {
-    const int len = seg_len(k), b = k % L.nbuf, q0 = q;
+    const int64_t len = seg_len(k);
+    const int b = k % L.nbuf, q0 = q;
     hipError_t er = two ? hipStreamWaitEvent(rst, ev_rec[b], 0) : hipSuccess;
     if (er == hipSuccess) {
-      if (len == L.every) {
+      if (two && len == L.every) {
         hipGraphExec_t gr = nullptr;
         er = g_rev[b].get(q0, [&](int, hipStream_t st) { return reverse(q0, len, b, st); }, &gr);
         if (er == hipSuccess) er = hipGraphLaunch(gr, rst);
@@ -1164,12 +1118,13 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
     }
     if (er == hipSuccess && two) er = hipEventRecord(ev_rev[b], rst);
     if (er != hipSuccess) return hip_fail(c, er, "adjoint sweep");
-    q ^= (len & 1);
+    q ^= (int)(len & 1);
     return LB_OK;
   };
-  if (L.ncp > 0 && (rc = recompute_segment(L.ncp - 1))) return graphs_done(rc);
+  for (int b = 0; two && b < 2 && e == hipSuccess; ++b) e = hipEventRecord(ev_rec[b], c->stream);
+  if (e != hipSuccess) return graphs_done(hip_fail(c, e, "adjoint streams"));
   for (int k = L.ncp - 1; k >= 0; --k) {
-    if (k > 0 && (rc = recompute_segment(k - 1))) return graphs_done(rc);
+    if (k - 1 < L.nck && k > 0 && (rc = recompute_segment(k - 1))) return graphs_done(rc);
     if ((rc = reverse_segment(k))) return graphs_done(rc);
   }
   e = launch_adjoint_reduce(a.partials, c->lat.lx, c->lat.ly, acc, rst);
@@ -1178,14 +1133,10 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   if (e == hipSuccess && two) e = hipStreamWaitEvent(c->stream, ev_rev[0], 0);
   if (e != hipSuccess) return graphs_done(hip_fail(c, e, "adjoint reduction"));
   release();
-  // back to the state after T steps
-  if (!L.all) e = hipMemcpyAsync(c->pop[cur_final], ws + L.fin, popb, hipMemcpyDeviceToDevice, c->stream);
   double h[ADJ_N];
-  if (e == hipSuccess) e = hipMemcpyAsync(h, acc, sizeof(h), hipMemcpyDeviceToHost, c->stream);
+  e = hipMemcpyAsync(h, acc, sizeof(h), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return done(hip_fail(c, e, "adjoint readback"));
-  c->cur = cur_final;
-  c->t = t0 + T;
   for (int k = 0; k < 7; ++k) grad[k] = h[k];
   if (loss) *loss = h[ADJ_LW] + h[ADJ_LQ];
   if (!std::isfinite(h[ADJ_LW] + h[ADJ_LQ])) return done(fail(c, LB_EUNSTABLE, "non-finite loss"));

@@ -229,11 +229,6 @@ struct LayoutArgs {
   long long plane;
   int lx, ly, pitch, ns;
   double rho_ref[2];
-  // checkpoint with fields (adjoint): out receives only the canonical populations of the rows
-  // next to the walls ([s][l][2][lx], FP64), fields rho, psi, jx, jy of each species of the
-  // state, [4][2][ly][lx] in the adjoint's precision
-  void *fields;
-  double psi0, irho0;
 };
 
 // Reverse step of the adjoint (lb_adjoint.hip).  Arrays are canonical [..][y][x]; R is
@@ -280,8 +275,6 @@ hipError_t launch_reduce(const double *partials, int nblocks, double *totals, do
                          double inv_lx, hipStream_t st);
 hipError_t launch_init(int mode, int walls, const LayoutArgs &a, hipStream_t st);
 hipError_t launch_checkpoint(int mode, int walls, const LayoutArgs &a, hipStream_t st);
-// The same, also writing the fields rho, psi, jx, jy (FP64 if fp64, else FP32) to a.fields.
-hipError_t launch_checkpoint_fields(int mode, int walls, int fp64, const LayoutArgs &a, hipStream_t st);
 hipError_t launch_restore(int mode, int walls, const LayoutArgs &a, hipStream_t st);
 
 hipError_t launch_fill(double *p, double v, int n, hipStream_t st);
