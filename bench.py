@@ -31,8 +31,9 @@ def kernel_source_hash():
     h = hashlib.sha256()
     # the step kernels' own source (lb_kernels.hip holds only their dispatch and the layout
     # and reduction kernels)
-    for f in ("lb_step.hpp", "lb_step2.hpp", "lb_step_f64.hip", "lb_step_f32.hip", "lb_step_bf16.hip",
-              "lb_internal.hpp", "lb_tables.hpp"):
+    for f in ("lb_site.hpp", "lb_tile.hpp", "lb_tile_f64.hip", "lb_tile_f32.hip", "lb_tile_bf16.hip",
+              "lb_tile_bf16sr.hip", "lb_step.hpp", "lb_step2.hpp", "lb_step_f64.hip", "lb_step_f32.hip",
+              "lb_step_bf16.hip", "lb_internal.hpp", "lb_tables.hpp"):
         with open(os.path.join(ROOT, "paper_1402_6019_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -47,13 +48,18 @@ def workload():
     return rho, info, kw
 
 
-# whether the last time_storage run of (storage, shape) advanced its steps two per launch
-PAIRS_SEEN = {}
+def step_kernel_name(storage, where, tile=None):
+    """The kernel that plain steps of a two-species lattice of a million sites or more run: tiles of
+    32 x 16 sites, two steps per launch, unless a launch shape is set (--tile)."""
+    what = {"f64": "F64", "f32": "F32", "bf16dev": "BF16 deviations"}[storage]
+    if tile:
+        return f"step_kernel<{what}, 2 species, {where}> of the launch shape given"
+    return f"tile_kernel<{what}, 2 species, {where}, 32 x 16>: two steps per launch"
 
 
 def time_storage(storage, rho, kw, steps, warmup, tile=None, shape=(LX, LY), rounding=None):
-    """Average duration of one step (= one fused-kernel launch) over `steps` launches, timed
-    with HIP events recorded on the stream the kernels run on."""
+    """Average duration of one step over `steps` steps (several per launch in the default kernels),
+    timed with HIP events recorded on the stream the kernels run on."""
     import torch
     from paper_1402_6019_amd import Sim
     sim = Sim(shape[0], shape[1], rho, storage=storage, tile=tile, **kw)
@@ -72,7 +78,6 @@ def time_storage(storage, rho, kw, steps, warmup, tile=None, shape=(LX, LY), rou
     wall = time.perf_counter() - t0
     ms = start.elapsed_time(stop) / steps
     tile_used = sim.get_tile()
-    PAIRS_SEEN[(storage, tuple(shape))] = sim.two_step_active
     sim.close()
     return ms, wall, tile_used
 
@@ -150,18 +155,13 @@ def channel_beyond_cache(steps):
     out = {"workload": f"confined emulsion channel {lx}x{ly}, walls + wetting, g = 1e-6, volume fraction 0.85, seed 3"}
     out["profiles_f32"] = channel_profiles(rho, kw, lx, ly)
     out["copy_ceiling_f32_footprint"] = stream_copy(9 * 2 * 4 * lx * ly, 100)  # one FP32 population buffer
-    # the kernel each mode runs at this footprint by default: FP32 two steps per launch, FP64
-    # single steps with streaming stores (both beyond the Infinity Cache), BF16 (2 x 75.5 MB,
-    # inside it) single steps with write-through stores
-    kernels = {"f32": "step2_kernel<F32, 2 species, channel>: two steps per launch, write-through stores",
-               "bf16dev": "step_kernel<BF16 deviations, 2 species, channel>, write-through stores",
-               "f64": "step_kernel<F64, 2 species, channel>, streaming stores"}
     for storage in ("f32", "bf16dev", "f64"):
         ms, wall, tile = time_storage(storage, rho, kw, steps, max(10, steps // 10), shape=(lx, ly))
         bpl = 2 * 9 * 2 * BYTES_PER_VALUE[storage]
         gbs = bpl * lx * ly / (ms * 1e-3) / 1e9
         out[storage] = {"ms_per_step": ms, "mlups": lx * ly / (ms * 1e-3) / 1e6, "gbs": gbs, "frac": gbs / HBM_PEAK_GBS,
-                        "footprint_mb": 2 * bpl / 2 * lx * ly / 1e6, "tile": list(tile), "kernel": kernels[storage]}
+                        "footprint_mb": 2 * bpl / 2 * lx * ly / 1e6, "tile": list(tile),
+                        "kernel": step_kernel_name(storage, "channel")}
     return out
 
 
@@ -523,7 +523,7 @@ def couette_cell(steps, sample_every=100):
     ms_run = start.elapsed_time(stop) / (nsamp * sample_every)
     sig = st["sigma"].cpu().numpy()
 
-    # two steps per launch (lb_set_two_step), timed over whole runs of steps
+    # the forced pairs (lb_set_two_step), timed over whole runs of steps
     def bulk(s, n):
         s.step(20)
         start.record(s.stream)
@@ -558,8 +558,8 @@ def couette_cell(steps, sample_every=100):
             "profile_every": sample_every, "ms_per_step_with_profiles": ms_run,
             "profile_overhead": ms_run / ms_step - 1.0, "samples": nsamp,
             "mean_wall_stress": [float(sig[0]), float(-sig[-1])],
-            "ragged_width": {"note": "ps per site of the 1040^2 cell against the same cell at 1024^2 (autotuned tile, "
-                                     "whole runs of steps), single steps and two steps per launch",
+            "ragged_width": {"note": "ps per site of the 1040^2 cell against the same cell at 1024^2 (autotuned, whole "
+                                     "runs of steps): single = the kernel the autotuner kept, two_step = forced pairs",
                              "ps_per_site_1040": {"single": ps(ms_step, lx), "two_step": ps(ms_two, lx)},
                              "ps_per_site_1024": {"single": ps(ref_single, 1024), "two_step": ps(ref_two, 1024)},
                              "best_1040_over_best_1024": min(ps(ms_step, lx), ps(ms_two, lx)) /
@@ -719,7 +719,7 @@ def adjoint_channel(T=4000, prerelax=2000, check_fd=True):
     keys = ("G1", "G2", "G_AB", "g_x")
     out = {"workload": f"confined emulsion channel {lx}x{ly}, G1 = -9.0, G2 = 8.1 both species, g = 1e-6, "
                        f"fraction 0.8, seed 5, {prerelax} FP64 steps of pre-relaxation, then T = {T}",
-           "storage": "FP32 forward (and recompute), FP64 checkpoints every ceil(sqrt(T)) steps, reverse sweep in "
+           "storage": "FP32 forward (and recompute), copies of the populations every ceil(sqrt(T)) steps, reverse sweep in "
                       "FP64 (grad) and in FP32 (grad_fp32_reverse)",
            "loss": loss, "grad": dict(zip(keys, grad)), "grad_fp32_reverse": dict(zip(keys, grad32)),
            "seconds_adjoint": t_adj, "seconds_adjoint_fp32_reverse": t_adj32, "seconds_forward_only": t_fwd,
@@ -1017,7 +1017,7 @@ def main():
     roof = {"bound": "hbm", "achieved": head["gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": head["gbs"] / HBM_PEAK_GBS,
             "traffic": traffic_from_profile(khash, "f32", head["tile"]),
-            "kernel": "step_kernel<F32, 2 species, periodic>", "bytes_per_lu": 144,
+            "kernel": step_kernel_name("f32", "periodic", tile), "bytes_per_lu": 144,
             "copy_ceiling_gbs": copy["gbs"], "frac_of_copy": head["gbs"] / copy["gbs"],
             "stream_copy_gbs": max(copy["stream_copy_gbs"], copy["stream_copy_nt_gbs"]),
             "frac_of_stream_copy": head["gbs"] / max(copy["stream_copy_gbs"], copy["stream_copy_nt_gbs"]),
@@ -1053,12 +1053,10 @@ def main():
                    "mass_fraction": info["mass_fraction"]},
         "roofline": roof,
         "fp64": {"mlups": res["f64"]["mlups"], "ms_per_step": res["f64"]["ms_per_step"],
-                 "kernel": ("step2_kernel<F64, 2 species, periodic>: two steps per launch, write-through stores"
-                            if PAIRS_SEEN.get(("f64", (LX, LY))) else
-                            "step_kernel<F64, 2 species, periodic>, streaming stores"),
+                 "kernel": step_kernel_name("f64", "periodic", tile),
                  "roofline": {"bound": "hbm", "achieved": res["f64"]["gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": res["f64"]["gbs"] / HBM_PEAK_GBS, "bytes_per_lu": 288,
-                              "steps_per_launch": 2 if PAIRS_SEEN.get(("f64", (LX, LY))) else 1,
+                              "steps_per_launch": 1 if tile else 2,
                               "traffic": traffic_from_profile(khash, "f64", res["f64"]["tile"])}},
         "bf16dev": {"mlups": res["bf16dev"]["mlups"], "ms_per_step": res["bf16dev"]["ms_per_step"],
                     "roofline": {"bound": "hbm", "achieved": res["bf16dev"]["gbs"], "peak": HBM_PEAK_GBS,

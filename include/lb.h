@@ -405,8 +405,8 @@ void lb_destroy(lb_ctx *ctx);
 
 /* ---------------------------------------------------------------------------------------
  * Batches: n independent lattices (e.g. channels of uneven size with their own couplings,
- * relaxation times and body forces) advanced together by one persistent kernel launch per
- * time step.  Each instance evolves exactly as it would in its own lb_init context (same
+ * relaxation times and body forces) advanced together, every launch over the tiles of all
+ * instances (several time steps per launch).  Each instance evolves exactly as it would in its own lb_init context (same
  * step, bitwise the same per-site arithmetic).  All instances share storage, n_species and
  * walls; sizes, couplings, tau and psi parameters are per instance.
  * Ownership and errors as for lb_ctx; lb_batch_last_error(NULL) reports lb_batch_init.

@@ -132,15 +132,16 @@ class Sim:
         self._chk(self._lib.lb_set_time(self._h, int(t)))
 
     def set_two_step(self, enable=True, rows=0):
-        """Advance plain steps two per launch (bitwise the same results): True, False or "auto"
-        (the default: pairs for walled FP32 and periodic FP64 lattices beyond the Infinity
-        Cache)."""
+        """How many steps a launch takes (bitwise the same results): "auto", the default, two or
+        three in tiles; False, one; True, pairs of plain steps in strips marched by single
+        waves."""
         mode = 2 if enable == "auto" else (1 if enable else 0)
         self._chk(self._lib.lb_set_two_step(self._h, mode, int(rows)))
 
     @property
     def two_step_active(self):
-        """Whether step() currently advances plain steps two per launch."""
+        """Whether the rule of set_two_step pairs this lattice's plain steps (it does not count the
+        steps per launch of the tile step)."""
         return self._lib.lb_two_step_active(self._h) == 1
 
     def step(self, n=1):
@@ -319,7 +320,7 @@ def fit_cooperative_length(z, f, H, zeta_range=None):
 
 
 class Batch:
-    """Many independent lattices stepped together by one persistent launch per time step.
+    """Many independent lattices stepped together, every launch over the tiles of all of them.
 
     instances: list of dicts with the keyword arguments of Sim (lx, ly, rho_init, and any of
     g1, g2, gab, body, rho_wall, tau, psi0, rho0, rho_ref, w, p, t, cross_psi, u_wall); storage,

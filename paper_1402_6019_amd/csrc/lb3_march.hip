@@ -12,8 +12,10 @@
 // Every address of a site but its plane's base stays the same through the march: nine lane offsets
 // per thread, the population's plane in the uniform offset and z in the buffer descriptor.
 // Per-site arithmetic and its order are those of lb3_kernels.hip (bitwise the same populations).
-// Two species, us per step before (two pulls) and now: 256^3 FP32 1540 and 1190 (5.2 TB/s of what it
-// has to move), 192 x 128 x 128 FP64 735 and 535; the moments of 256^3 4040 and 860 (that pass
+// Two species, us per step before (two pulls) and now: 256^3 FP32 1540 and 1250 (4.1 TB/s of
+// populations; vector units busy 35%, two waves per SIMD in step; the frame's loads, issued after the
+// stores, are waited for at the next plane, but spilled wherever they were issued earlier: 1494 and
+// more), 192 x 128 x 128 FP64 735 and 535; the moments of 256^3 4040 and 860 (that pass
 // spilled, see site3_update).
 
 #include <hip/hip_runtime.h>
