@@ -163,7 +163,8 @@ bool tiles_on(const lb_ctx *c) { return !c->shape_set && c->two_step != LB_TWO_S
 // Tile shape: the smallest whose tiles fit the compute units one each.  A launch lasts as long as
 // its busiest compute unit, so up to that point a larger tile only adds work, and beyond it a
 // smaller one only adds overlap: per step of 188 x 168 FP64 sites (one species) 16 x 8 tiles
-// took 2.6 us, 8 x 8 3.0 and 16 x 16 3.0; of a 512 x 512 FP32 channel 32 x 16 tiles 7.4 us,
+// took 2.6 us, 8 x 8 3.0 and 16 x 16 3.0; of 64 x 64 FP64 4 x 8 tiles 2.05 us, 8 x 8 2.11 (two species,
+// walls: 3.09 and 3.20); of a 512 x 512 FP32 channel 32 x 16 tiles 7.4 us,
 // 16 x 16 8.1.
 int tile_shape(const lb_ctx *c) {
   for (int k = 0; k < kTileShapes - 1; ++k)

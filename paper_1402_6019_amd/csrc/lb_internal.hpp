@@ -160,13 +160,13 @@ struct TileOpts {
 
 // Tile shapes of the tile step: sites per tile, and the most steps of one launch.  The last two are the
 // same tile, of one workgroup per compute unit (more threads, three steps) and of two.
-constexpr int kTileShapes = 5;
-constexpr int kTileX[kTileShapes] = {8, 16, 16, 32, 32}, kTileY[kTileShapes] = {8, 8, 16, 16, 16};
+constexpr int kTileShapes = 6;
+constexpr int kTileX[kTileShapes] = {4, 8, 16, 16, 32, 32}, kTileY[kTileShapes] = {8, 8, 8, 16, 16, 16};
 
 // Steps of one launch at most: three, in 32 x 16 tiles with one per compute unit (512 x 256, FP32,
 // walled: 4.40 us per step against 4.64 for two; beyond that the overlaps cost more than the launches:
 // 4096 x 512 62 and 44) unless the copy of f* outgrows LDS (two species in FP64).
-inline int tile_most_steps(int shape, bool fp64, int ns) { return shape == 4 || (shape == 3 && fp64 && ns == 2) ? 2 : 3; }
+inline int tile_most_steps(int shape, bool fp64, int ns) { return shape == 5 || (shape == 4 && fp64 && ns == 2) ? 2 : 3; }
 
 // Tiles of the observation passes (lb_observe.hpp) with sums, and of those without on large lattices.
 constexpr int kObserveX = 64, kObserveY = 8;

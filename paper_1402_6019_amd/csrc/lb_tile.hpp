@@ -356,27 +356,33 @@ static hipError_t launch_tile_k(const BatchTiles &b, const TileOpts &o, hipStrea
 template <int MODE, int NS, bool WALLS, int WHAT, typename A>
 static hipError_t launch_tile_w(int shape, int n, const A &a, const TileOpts &o, hipStream_t st) {
   constexpr int WT = kStoreWriteThrough, NTS = kStoreStreaming;
+  // two species in FP64 leave one workgroup per compute unit (155 KB of LDS), which then takes twelve
+  // waves: 2048 x 1024 106 -> 103 us per step, 4096 x 512 walled 110.6 -> 107.6; else two of eight
+  constexpr int LAST = MODE == MODE_F64 && NS == 2 ? 768 : 512;
   switch (shape * 4 + n) {
-    case 0 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 1, 256, WT>(a, o, st);
-    case 0 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 2, 384, WT>(a, o, st);
-    case 0 * 4 + 3: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 3, 512, WT>(a, o, st);
-    case 1 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 1, 256, WT>(a, o, st);
-    case 1 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 2, 512, WT>(a, o, st);
-    case 1 * 4 + 3: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 3, 512, WT>(a, o, st);
-    case 2 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 1, 448, WT>(a, o, st);
-    case 2 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 2, 512, WT>(a, o, st);
-    case 2 * 4 + 3: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 3, 576, WT>(a, o, st);
-    case 3 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 1, 512, WT>(a, o, st);
-    case 3 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 768, WT>(a, o, st);
-    case 3 * 4 + 3:
+    case 0 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 4, 8, 1, 128, WT>(a, o, st);
+    case 0 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 4, 8, 2, 256, WT>(a, o, st);
+    case 0 * 4 + 3: return launch_tile_k<MODE, NS, WALLS, WHAT, 4, 8, 3, 448, WT>(a, o, st);
+    case 1 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 1, 256, WT>(a, o, st);
+    case 1 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 2, 384, WT>(a, o, st);
+    case 1 * 4 + 3: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 3, 512, WT>(a, o, st);
+    case 2 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 1, 256, WT>(a, o, st);
+    case 2 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 2, 512, WT>(a, o, st);
+    case 2 * 4 + 3: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 3, 512, WT>(a, o, st);
+    case 3 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 1, 448, WT>(a, o, st);
+    case 3 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 2, 512, WT>(a, o, st);
+    case 3 * 4 + 3: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 3, 576, WT>(a, o, st);
+    case 4 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 1, 512, WT>(a, o, st);
+    case 4 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 768, WT>(a, o, st);
+    case 4 * 4 + 3:
       if constexpr (tile_lds_bytes<MODE, NS, 32, 16, 3>() <= 160 * 1024) return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 3, 768, WT>(a, o, st);
       break;
-    case 4 * 4 + 1:
+    case 5 * 4 + 1:
       return a.stream_stores ? launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 1, 512, NTS>(a, o, st)
                              : launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 1, 512, WT>(a, o, st);
-    case 4 * 4 + 2:
-      return a.stream_stores ? launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 512, NTS>(a, o, st)
-                             : launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 512, WT>(a, o, st);
+    case 5 * 4 + 2:
+      return a.stream_stores ? launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, LAST, NTS>(a, o, st)
+                             : launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, LAST, WT>(a, o, st);
   }
   return hipErrorInvalidValue;
 }
@@ -393,16 +399,18 @@ template <int MODE, int NS, bool WALLS, int WHAT>
 static hipError_t launch_tile_fields(int shape, int n, const StepArgs &a, const TileOpts &o, hipStream_t st) {
   constexpr int WT = kStoreWriteThrough;
   switch (shape * 4 + n) {
-    case 0 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 1, 256, WT>(a, o, st);
-    case 0 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 2, 384, WT>(a, o, st);
-    case 1 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 1, 256, WT>(a, o, st);
-    case 1 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 2, 512, WT>(a, o, st);
-    case 2 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 1, 448, WT>(a, o, st);
-    case 2 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 2, 512, WT>(a, o, st);
-    case 3 * 4 + 1:
-    case 4 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 1, 512, WT>(a, o, st);
-    case 3 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 768, WT>(a, o, st);
-    case 4 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 512, WT>(a, o, st);
+    case 0 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 4, 8, 1, 128, WT>(a, o, st);
+    case 0 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 4, 8, 2, 256, WT>(a, o, st);
+    case 1 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 1, 256, WT>(a, o, st);
+    case 1 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 8, 8, 2, 384, WT>(a, o, st);
+    case 2 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 1, 256, WT>(a, o, st);
+    case 2 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 8, 2, 512, WT>(a, o, st);
+    case 3 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 1, 448, WT>(a, o, st);
+    case 3 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 16, 16, 2, 512, WT>(a, o, st);
+    case 4 * 4 + 1:
+    case 5 * 4 + 1: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 1, 512, WT>(a, o, st);
+    case 4 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 768, WT>(a, o, st);
+    case 5 * 4 + 2: return launch_tile_k<MODE, NS, WALLS, WHAT, 32, 16, 2, 512, WT>(a, o, st);
   }
   return hipErrorInvalidValue;
 }

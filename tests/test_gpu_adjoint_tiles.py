@@ -28,3 +28,9 @@ def test_reverse_tiles_match_the_complex_step(lx, ly, ns, walls):
     got = np.array([g7[0] + g7[1], g7[2] + g7[3], g7[4], g7[5]])
     assert loss == pytest.approx(ref[0][0], rel=1e-10, abs=1e-15)
     np.testing.assert_allclose(got, d, rtol=1e-9, atol=1e-9 * np.abs(d[:3]).max())
+
+
+@pytest.mark.parametrize("ns,walls", [(1, False), (2, True)])
+def test_states_of_eight_wide_tiles(ns, walls):
+    """The recompute's 8 x 8 tiles, which the sizes above do not take."""
+    test_reverse_tiles_match_the_complex_step(100, 100, ns, walls)

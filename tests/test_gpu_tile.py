@@ -12,7 +12,7 @@ from cases import film_case, make_sim
 
 pytestmark = pytest.mark.gpu
 
-# lx, ly: 8x8 tiles (one and several wraps of a narrow lattice), 16x8, 16x16 and 32x16 tiles
+# lx, ly: 4x8 tiles (one and several wraps of a narrow lattice), 16x8, 16x16 and 32x16 tiles
 SIZES = [(5, 5), (9, 41), (160, 5), (64, 64), (61, 37), (131, 130), (301, 147), (517, 270)]
 
 
@@ -51,6 +51,16 @@ def test_tile_steps_are_bitwise_the_marched_steps(lx, ly, storage, ns, walls):
     steps = (1, 2, 3, 4, 5)
     print(lx, ly, storage, ns, walls, flush=True)
     for a, b in zip(populations(c, steps), populations(c, steps, tile=(64, 7))):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("lx,ly", [(100, 100), (127, 129)])
+@pytest.mark.parametrize("storage,ns,walls", [("f64", 1, False), ("f64", 2, True), ("f32", 2, True), ("bf16dev", 2, False)])
+def test_eight_wide_tiles(lx, ly, storage, ns, walls):
+    """8 x 8 tiles, ragged: lattices whose 4 x 8 tiles are more than the compute units."""
+    c = case(lx, ly, storage, ns, walls)
+    print(lx, ly, storage, ns, walls, flush=True)
+    for a, b in zip(populations(c, (1, 2, 3, 4, 5)), populations(c, (1, 2, 3, 4, 5), tile=(64, 7))):
         assert np.array_equal(a, b)
 
 
