@@ -171,8 +171,13 @@ int mode3(const lb3_ctx *c) { return c->lat.storage == LB_F64 ? MODE_F64 : MODE_
 
 int launch_what(lb3_ctx *c, int what, void *rho, void *u, int out_f32) {
   Lb3Args a = args3(c);
-  const bool split = !c->shape_set && c->d_psi;
-  if (!c->shape_set && !split) march_grid3(c, a);
+  // Totals always go through step3_kernel in the context's launch shape: a sum of terms that cancel (the
+  // momentum of a periodic lattice near rest: 1e-13 left of a sum of |j| of 1e4) is what its order of
+  // additions makes of it, so that order depends on no rule of which kernel steps.  It costs 107 of 7963 us
+  // per pass of five steps, moments and totals at 256^3 FP32, 13 of 1142 at 100 x 70 x 60 FP64.
+  const bool any_shape = c->shape_set || what == WHAT_OBSERVE;
+  const bool split = !any_shape && c->d_psi;
+  if (!any_shape && !split) march_grid3(c, a);
   a.psi = c->d_psi;
   const int nb = split ? split3_tiles(c->lat.lx, c->lat.ly, c->lat.lz, &a.nstrip, &a.nband) : a.nstrip * a.nband * a.nseg;
   a.src = c->pop[c->cur];
@@ -191,9 +196,9 @@ int launch_what(lb3_ctx *c, int what, void *rho, void *u, int out_f32) {
     }
     a.partials = c->d_partials;
   }
-  hipError_t e = c->shape_set ? launch_step3(mode3(c), c->lat.n_species, c->lat.walls, what, c->ty, nb, a, c->stream)
-                 : split      ? launch_split3(mode3(c), c->lat.n_species, c->lat.walls, what, nb, a, c->stream)
-                              : launch_march3(mode3(c), c->lat.n_species, c->lat.walls, what, nb, a, c->stream);
+  hipError_t e = any_shape ? launch_step3(mode3(c), c->lat.n_species, c->lat.walls, what, c->ty, nb, a, c->stream)
+                 : split   ? launch_split3(mode3(c), c->lat.n_species, c->lat.walls, what, nb, a, c->stream)
+                           : launch_march3(mode3(c), c->lat.n_species, c->lat.walls, what, nb, a, c->stream);
   if (e != hipSuccess) return hip_fail3(c, e, "3-D step launch");
   if (what == WHAT_OBSERVE) {
     e = launch_reduce3(c->d_partials, nb, c->d_totals, c->stream);

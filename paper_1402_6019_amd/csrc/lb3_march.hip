@@ -53,12 +53,10 @@ void march3_kernel(Lb3Args a) {
   using S = typename C::S;
   using V = Vec<R, NS>;
   constexpr bool STORE = WHAT == WHAT_STEP;
-  constexpr bool OBSERVE = WHAT == WHAT_OBSERVE;
   constexpr int TY = rows3<MODE>(), H = TY + 4, SLOT = W3 * H, NT = TX3 * TY, NHALO = SLOT - NT;
   constexpr int SLOTP = SLOT + 1;
   V *const psi_ring = reinterpret_cast<V *>(march3_smem);  // [RING3][H][W3]
   V *const rho_ring = psi_ring + RING3 * SLOTP;             // [RHO3][H][W3] (two species)
-  __shared__ double red_lds[NT / 64][RED3_N];
 
   const int lx = a.lx, ly = a.ly, lz = a.lz;
   constexpr uint32_t site_b = (uint32_t)(NS * sizeof(S));
@@ -142,10 +140,6 @@ void march3_kernel(Lb3Args a) {
   };
   auto zwrap = [&](int p) { return (int)uni((uint32_t)d3::wrap(d3::wrap(p, lz), lz)); };
 
-  double acc[RED3_N];
-#pragma unroll
-  for (int k = 0; k < RED3_N; ++k) acc[k] = 0.0;
-
   // FIFO: plane z lives in B[(z - zA) mod 4]; psi plane p in slot (p - zA + 2) mod 6, rho plane p
   // in slot (p - zA + 2) mod 5.
   R B[4][NS][19], hf[NS][19], ob[NS][2], hb[NS][2];
@@ -210,7 +204,7 @@ void march3_kernel(Lb3Args a) {
     auto xr = [&](int dx, int dy, int dz) { return psi_ring[(int)xo[dz + 1] + (ty + dy + 2) * W3 + tx + dx + 2]; };
     site3_update<C, NS, WHAT, STP>(
         a, p, f, [&](int dx, int dy, int dz) { return pl[dz + 2][(dy + 2) * W3 + dx + 2]; },
-        xr, x, y, z, site_ok, zrsrc(a.dst, z, STORE), site_ok ? own.row[1] + own.col[1] : kOff3, plane_b, acc);
+        xr, x, y, z, site_ok, zrsrc(a.dst, z, STORE), site_ok ? own.row[1] + own.col[1] : kOff3, plane_b);
     // the frame's loads last: in registers that the updated populations have left
     __builtin_amdgcn_sched_barrier(0);
     pull(halo, zwrap(z + 3), more, hf, hb);
@@ -220,21 +214,6 @@ void march3_kernel(Lb3Args a) {
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (z + k < zB) plane(z + k, B[k], B[(k + 2) & 3], B[(k + 3) & 3]);
-  }
-
-  if (OBSERVE) {
-    const int lane = tid & 63, wv = tid >> 6;
-#pragma unroll
-    for (int k = 0; k < RED3_N; ++k) {
-      const double v = wave_sum(acc[k]);
-      if (lane == 0) red_lds[wv][k] = v;
-    }
-    __syncthreads();
-    if (tid < RED3_N) {
-      double v = 0.0;
-      for (int i = 0; i < NT / 64; ++i) v += red_lds[i][tid];
-      a.partials[(size_t)blockIdx.x * RED3_N + tid] = v;
-    }
   }
 }
 
@@ -254,7 +233,6 @@ static hipError_t launch_march3_t(int what, int nb, const Lb3Args &a, hipStream_
       return a.stream_stores ? launch_march3_k<MODE, NS, WALLS, WHAT_STEP, kStoreStreaming>(nb, a, st)
                              : launch_march3_k<MODE, NS, WALLS, WHAT_STEP, kStoreWriteThrough>(nb, a, st);
     case WHAT_MOMENTS: return launch_march3_k<MODE, NS, WALLS, WHAT_MOMENTS, 0>(nb, a, st);
-    case WHAT_OBSERVE: return launch_march3_k<MODE, NS, WALLS, WHAT_OBSERVE, 0>(nb, a, st);
   }
   return hipErrorInvalidValue;
 }

@@ -103,12 +103,11 @@ struct Site3 {
 
 // Force and outputs of site (x, y, z) from its pulled populations f and its neighbours' psi(dx, dy,
 // dz) and xr(dx, dy, dz) (rho or psi): the post-collision populations to lane offset `at` of rd
-// (WHAT_STEP), the moments (WHAT_MOMENTS) or the sums acc (WHAT_OBSERVE) where site_ok.
+// (WHAT_STEP) or the moments (WHAT_MOMENTS) where site_ok.
 template <class C, int NS, int WHAT, int STP, typename PSI, typename XR>
 __device__ __forceinline__ void site3_update(const Lb3Args &a, const Site3<typename C::R, NS> &p,
                                              const typename C::R (&f)[NS][19], const PSI &psi, const XR &xr, int x, int y,
-                                             int z, bool site_ok, const Rsrc rd, uint32_t at, uint32_t plane_b,
-                                             double (&acc)[RED3_N]) {
+                                             int z, bool site_ok, const Rsrc rd, uint32_t at, uint32_t plane_b) {
   using R = typename C::R;
   using V = Vec<R, NS>;
   R drho[NS], rho[NS], jx[NS], jy[NS], jz[NS];
@@ -226,27 +225,6 @@ __device__ __forceinline__ void site3_update(const Lb3Args &a, const Site3<typen
         u[2 * nsite + site] = double(uz);
       }
     }
-  }
-
-  if (WHAT == WHAT_OBSERVE && site_ok) {
-    R srho = rho[0], mx = jx[0] + R(0.5) * Fx[0];
-    bool bad = !(rho[0] > R(0) && rho[0] < R(INFINITY));
-#pragma unroll
-    for (int s = 1; s < NS; ++s) {
-      srho += rho[s];
-      mx += jx[s] + R(0.5) * Fx[s];
-      bad = bad || !(rho[s] > R(0) && rho[s] < R(INFINITY));
-    }
-    acc[RED3_MASS0] += double(rho[0]);
-    if (NS == 2) acc[RED3_MASS1] += double(rho[NS - 1]);
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      acc[RED3_PX] += double(jx[s]);
-      acc[RED3_PY] += double(jy[s]);
-      acc[RED3_PZ] += double(jz[s]);
-    }
-    acc[RED3_FLOW] += double(mx / srho);
-    acc[RED3_BAD] += bad ? 1.0 : 0.0;
   }
 
   if (WHAT == WHAT_STEP) {

@@ -75,7 +75,6 @@ __global__ __launch_bounds__(SX *SY *SZ) void split3_kernel(Lb3Args a) {
   constexpr int NT = SX * SY * SZ;
   V *const psi_t = reinterpret_cast<V *>(split3_smem);  // [PZ][PY][PX]
   V *const rho_t = psi_t + PX * PY * PZ;                // [QZ][QY][QX] (two species)
-  __shared__ double red_lds[NT / 64][RED3_N];
   constexpr uint32_t site_b = (uint32_t)(NS * sizeof(S));
   const uint32_t plane_b = (uint32_t)a.pitch * site_b, row_b = 19u * plane_b;
   const uint64_t zplane_b = (uint64_t)row_b * (uint32_t)a.ly;
@@ -140,9 +139,6 @@ __global__ __launch_bounds__(SX *SY *SZ) void split3_kernel(Lb3Args a) {
   wall_fix3<WALLS>(q, fb, f);
   __syncthreads();
 
-  double acc[RED3_N];
-#pragma unroll
-  for (int k = 0; k < RED3_N; ++k) acc[k] = 0.0;
   const V *const pc = psi_t + ((tz + 2) * PY + ty + 2) * PX + tx + 2;
   // the cross term's field and its strides (uniform but for the lane)
   const int xy = a.cross_psi ? PX : QX, xz = a.cross_psi ? PX * PY : QX * QY;
@@ -151,22 +147,7 @@ __global__ __launch_bounds__(SX *SY *SZ) void split3_kernel(Lb3Args a) {
       a, p, f, [&](int dx, int dy, int dz) { return pc[(dz * PY + dy) * PX + dx]; },
       [&](int dx, int dy, int dz) { return xc[dz * xz + dy * xy + dx]; }, x, y, z, ok,
       make_rsrc(static_cast<char *>(a.dst) + (uint64_t)(uint32_t)min(z, lz - 1) * zplane_b, (uint32_t)zplane_b),
-      ok ? q.row[1] + q.col[1] : kOff3, plane_b, acc);
-
-  if (WHAT == WHAT_OBSERVE) {
-    const int lane = tid & 63, wv = tid >> 6;
-#pragma unroll
-    for (int k = 0; k < RED3_N; ++k) {
-      const double v = wave_sum(acc[k]);
-      if (lane == 0) red_lds[wv][k] = v;
-    }
-    __syncthreads();
-    if (tid < RED3_N) {
-      double v = 0.0;
-      for (int i = 0; i < NT / 64; ++i) v += red_lds[i][tid];
-      a.partials[(size_t)blockIdx.x * RED3_N + tid] = v;
-    }
-  }
+      ok ? q.row[1] + q.col[1] : kOff3, plane_b);
 }
 
 int split3_tiles(int lx, int ly, int lz, int *nstrip, int *nband) {
@@ -190,7 +171,6 @@ static hipError_t launch_split3_t(int what, int nb, const Lb3Args &a, hipStream_
   switch (what) {
     case WHAT_STEP: return launch_split3_k<MODE, NS, WALLS, WHAT_STEP>(nb, a, st);
     case WHAT_MOMENTS: return launch_split3_k<MODE, NS, WALLS, WHAT_MOMENTS>(nb, a, st);
-    case WHAT_OBSERVE: return launch_split3_k<MODE, NS, WALLS, WHAT_OBSERVE>(nb, a, st);
   }
   return hipErrorInvalidValue;
 }
