@@ -95,7 +95,8 @@ int count_tiles(const lb_batch *b, int tx, int sy) {
 int resident(const lb_batch *b, int tx) { return step_blocks_per_cu(b->storage, b->ns, b->walls, tx) * b->n_cu; }
 
 // Build the tile table (band-major within each instance), per-instance arguments and
-// reduction jobs for shape (tx, sy) and upload them.  Synchronises the stream.
+// reduction jobs for shape (tx, sy) and upload them.  A shape that is refused, or whose tables find no
+// memory, leaves the batch as it was.  Synchronises the stream.
 int build_tiles(lb_batch *b, int tx, int sy) {
   const int nt = count_tiles(b, tx, sy);
   if (nt < 0) return bfail(b, LB_EINVAL, "too many tiles");
@@ -129,15 +130,19 @@ int build_tiles(lb_batch *b, int tx, int sy) {
   hipError_t e = hipStreamSynchronize(b->stream);  // no launch may still read the old tables
   if (e != hipSuccess) return bhip(b, e, "tile table");
   if ((size_t)nt > b->tile_cap) {
+    TileDesc *d_tiles = nullptr;
+    double *d_accrows = nullptr;
+    if ((e = hipMalloc(&d_tiles, (size_t)nt * sizeof(TileDesc))) != hipSuccess ||
+        (e = hipMalloc(&d_accrows, (size_t)nt * ACC_N * sizeof(double))) != hipSuccess ||
+        (e = launch_fill(d_accrows, 0.0, nt * ACC_N, b->stream)) != hipSuccess) {
+      if (d_tiles) (void)hipFree(d_tiles);
+      if (d_accrows) (void)hipFree(d_accrows);
+      return bfail(b, LB_ENOMEM, std::string("tile table: ") + hipGetErrorString(e));
+    }
     if (b->d_tiles) (void)hipFree(b->d_tiles);
     if (b->d_accrows) (void)hipFree(b->d_accrows);
-    b->d_tiles = nullptr;
-    b->d_accrows = nullptr;
-    b->tile_cap = 0;
-    if ((e = hipMalloc(&b->d_tiles, (size_t)nt * sizeof(TileDesc))) != hipSuccess ||
-        (e = hipMalloc(&b->d_accrows, (size_t)nt * ACC_N * sizeof(double))) != hipSuccess ||
-        (e = launch_fill(b->d_accrows, 0.0, nt * ACC_N, b->stream)) != hipSuccess)
-      return bfail(b, LB_ENOMEM, std::string("tile table: ") + hipGetErrorString(e));
+    b->d_tiles = d_tiles;
+    b->d_accrows = d_accrows;
     b->tile_cap = nt;
   }
   if ((e = hipMemcpyAsync(b->d_tiles, tiles.data(), (size_t)nt * sizeof(TileDesc), hipMemcpyHostToDevice,
@@ -554,9 +559,12 @@ int lb_batch_set_tile(lb_batch *b, int32_t tx, int32_t sy, int32_t grid) {
   if (tx != 64 && tx != 128 && tx != 256) return bfail(b, LB_EINVAL, "tx must be 64, 128 or 256");
   if (sy < 1) return bfail(b, LB_EINVAL, "sy must be >= 1");
   if (grid < 0 || grid > kMaxBlocks) return bfail(b, LB_EINVAL, "grid must be in [0, 2^20]");
+  // only a shape that was built is taken: until then the graphs hold the launches of the present one
+  const int rc = build_tiles(b, tx, sy);
+  if (rc) return rc;
   b->grid = grid;
   b->shape_set = true;
-  return build_tiles(b, tx, sy);
+  return LB_OK;
 }
 
 int lb_batch_get_tile(const lb_batch *b, int32_t *tx, int32_t *sy, int32_t *grid) {
