@@ -225,9 +225,10 @@ int64_t lb_time(const lb_ctx *ctx);
 int lb_set_time(lb_ctx *ctx, int64_t t);
 
 /* Launch shape of the row-marching kernels: strip width tx in {64, 128, 256} columns (one
-   workgroup thread per column) and sy >= 1 rows per workgroup.  lb_step advances in rectangular
-   tiles, up to three steps per launch, until a shape is set here; from then on it marches rows in
-   that shape, one step per launch.  Any shape gives bitwise identical results.  Host call. */
+   workgroup thread per column) and sy >= 1 rows per workgroup.  Until a shape is set here lb_step
+   chooses by the lattice: rectangular tiles, up to three steps per launch, but on some lattices past
+   the Infinity Cache pairs of steps or marched rows (see lb_set_two_step); from then on it marches
+   rows in that shape, one step per launch.  Any shape gives bitwise identical results.  Host call. */
 int lb_set_tile(lb_ctx *ctx, int32_t tx, int32_t sy);
 int lb_get_tile(const lb_ctx *ctx, int32_t *tx, int32_t *sy);
 
@@ -257,9 +258,12 @@ int lb_set_rounding(lb_ctx *ctx, int32_t mode);
    of two single steps: results are bitwise identical to LB_TWO_STEP_OFF (also with stochastic
    BF16 rounding and under graph replay).  LB_TWO_STEP_OFF launches every step by itself.
    LB_TWO_STEP_AUTO (the default) takes the tile step, which advances two or three steps per
-   launch (one launch per step once lb_set_tile has set a shape, except for walled FP32 and
-   periodic FP64 lattices whose two buffers exceed the 256 MiB Infinity Cache, whose steps then go
-   in pairs).  LB_EINVAL for rows < 0.  Host call. */
+   launch, wherever nothing else measured faster; that is, past the Infinity Cache (256 MiB), these
+   pairs for the largest periodic FP64 lattices of two species and marched rows, one step per launch,
+   for the largest walled or reducing FP64 lattices of two species, the largest BF16 lattices and
+   single steps.  Once lb_set_tile has set a shape it marches, one launch per step, except for
+   walled FP32 and periodic FP64 lattices whose two buffers exceed the Infinity Cache, whose steps
+   then go in pairs.  LB_EINVAL for rows < 0.  Host call. */
 enum lb_two_step { LB_TWO_STEP_OFF = 0, LB_TWO_STEP_ON = 1, LB_TWO_STEP_AUTO = 2 };
 int lb_set_two_step(lb_ctx *ctx, int32_t enable, int32_t rows);
 

@@ -133,8 +133,8 @@ class Sim:
 
     def set_two_step(self, enable=True, rows=0):
         """How many steps a launch takes (bitwise the same results): "auto", the default, two or
-        three in tiles; False, one; True, pairs of plain steps in strips marched by single
-        waves."""
+        three in tiles, or what measured faster on the largest lattices; False, one; True, pairs of
+        plain steps in strips marched by single waves."""
         mode = 2 if enable == "auto" else (1 if enable else 0)
         self._chk(self._lib.lb_set_two_step(self._h, mode, int(rows)))
 

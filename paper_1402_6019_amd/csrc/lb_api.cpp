@@ -155,10 +155,55 @@ bool pairs_on(const lb_ctx *c) {
   return c->two_step == LB_TWO_STEP_ON;
 }
 
-// Whether plain and reducing steps run in tiles (lb_tile.hpp), several per launch; else in marched
-// rows of the launch shape that lb_set_tile or the autotuner set, or in the pairs that
-// lb_set_two_step forces.
-bool tiles_on(const lb_ctx *c) { return !c->shape_set && c->two_step != LB_TWO_STEP_ON; }
+// Whether the strips of the marched rows leave at most a tenth of their lanes past the lattice's edge.
+bool strips_fit(const lb_ctx *c) { return (c->lat.lx + c->tx - 1) / c->tx * c->tx * 10 <= c->lat.lx * 11; }
+
+// Whether a launch of a single step marches rows instead of taking tiles, whose overlap then buys
+// nothing.  In the caches tiles are faster all the same (1024 x 512 FP32 14.1 us against 17.3); beyond them
+// marching is, in rows of 1792 sites and more (us, tiles and marched: 2048^2 FP32 139 and 114, 4096 x 512
+// 66 and 58, 1800 x 2400 131 and 122, FP64 with two species 4096 x 512 122 and 113; but 1040 x 2100 FP32 70
+// and 76, 512 x 4096 FP64 110 and 125), not in BF16 (4096 x 512 29 and 41, 2048^2 78 and 83).  With
+// reductions also in narrower rows, whose strips fit, and in BF16: fewer workgroups leave fewer running
+// sums to fold (512 x 4096 FP32 78 and 73, 2048^2 BF16 101 and 92; 600 x 3000 FP32, three strips of
+// 256, 71 and 75).
+bool march_single(const lb_ctx *c, bool reducing) {
+  if (!streaming_stores(lb_pop_bytes(&c->lat))) return false;
+  return reducing ? c->lat.lx >= 1792 || strips_fit(c) : c->lat.storage != LB_BF16DEV && c->lat.lx >= 1792;
+}
+
+// How a call's steps are launched: in tiles (lb_tile.hpp), several per launch; in pairs of two (lb_step2.hpp);
+// or in marched rows, one per launch.
+enum class Path { Tiles, Pairs, March };
+
+// A launch shape that lb_set_tile or the autotuner set marches rows and lb_set_two_step can force pairs;
+// left to itself the library takes tiles, but for lattices past the caches on which they measured slower
+// (us per step):
+//   FP64, two species, periodic: pairs from 192 MiB per buffer in rows of 1792 sites and more (4096 x 512
+//     tiles 110, pairs 106; 2300 x 900 114 and 107; narrower, 700 x 2900, 101 and 104) and from 512 MiB in
+//     any (2048^2 223 and 198, 1200 x 4000 242 and 223): one workgroup per compute unit, whose loads at
+//     the start nothing covers, waits for memory that has further to come;
+//   FP64, two species, walls: marched rows from 512 MiB in rows of more than 3072 sites (4096 x 1024 tiles
+//     231, marched 217; 3000 x 1400 224 and 232); with reductions, walls or not, of more than 1536 (2048^2
+//     231 and 218; 1500 x 2800 232 and 246);
+//   BF16, two species: marched rows from 256 MiB (4096 x 2048 150 and 140, stochastic 175 and 166; half of
+//     that is even); with reductions, one species or two, once both buffers exceed the cache (2048^2 86 and
+//     79); where the strips fit (1040 x 4096 with reductions 86 and 94).
+Path step_path(const lb_ctx *c, bool reducing) {
+  if (c->shape_set || c->two_step == LB_TWO_STEP_ON) return !reducing && pairs_on(c) ? Path::Pairs : Path::March;
+  if (c->two_step == LB_TWO_STEP_OFF) return march_single(c, reducing) ? Path::March : Path::Tiles;
+  const size_t mib = lb_pop_bytes(&c->lat) >> 20;
+  const int lx = c->lat.lx;
+  if (c->lat.storage == LB_F64 && c->lat.n_species == 2) {
+    if (reducing) return mib > 512 && lx > 1536 ? Path::March : Path::Tiles;
+    if (c->lat.walls) return mib > 512 && lx > 3072 ? Path::March : Path::Tiles;
+    return mib > 512 || (mib > 192 && lx >= 1792) ? Path::Pairs : Path::Tiles;
+  }
+  if (c->lat.storage == LB_BF16DEV && strips_fit(c)) {
+    if (reducing) return streaming_stores(lb_pop_bytes(&c->lat)) ? Path::March : Path::Tiles;
+    if (c->lat.n_species == 2 && mib > 256) return Path::March;
+  }
+  return Path::Tiles;
+}
 
 // Tile shape: the smallest whose tiles fit the compute units one each.  A launch lasts as long as
 // its busiest compute unit, so up to that point a larger tile only adds work, and beyond it a
@@ -455,14 +500,14 @@ int lb_step(lb_ctx *c, int64_t n) {
   int rc = poll_health(c, false);
   if (rc) return rc;
   bool reduced = false;
-  // Without reductions, whole graphs of graph.steps launches (an even number: the state
-  // returns to the same buffer) are replayed; the rest is launched one by one.
+  const Path path = step_path(c, c->reduce_every > 0);
+  // Without reductions, whole graphs of graph.steps steps are replayed; the rest is launched one by one.
   if (c->graph.steps > 0 && c->reduce_every == 0) {
     while (n >= c->graph.steps) {
       hipGraphExec_t g = nullptr;
       const int from = c->cur;
       const double *tb = c->rounding == LB_ROUND_STOCHASTIC ? c->d_tbase : nullptr;
-      const bool tiles = tiles_on(c), pairs = !tiles && pairs_on(c);
+      const bool tiles = path == Path::Tiles, pairs = path == Path::Pairs;
       const int shape = tile_shape(c);
       int launches = 0;  // of one replay (the buffers swap once per launch)
       if (tiles)
@@ -495,13 +540,15 @@ int lb_step(lb_ctx *c, int64_t n) {
       n -= c->graph.steps;
     }
   }
-  if (tiles_on(c)) {
+  if (path == Path::Tiles) {
     const int shape = tile_shape(c);
     while (n > 0) {
       const int m = tile_steps(c, shape, n);
       uint32_t mask = 0;
       for (int k = 0; k < m && c->reduce_every > 0; ++k)
         if ((c->t + k) % c->reduce_every == 0) mask |= 1u << k;
+      // a last single step is marched below, unless the tiles' running sums would have to be folded for it
+      if (m == 1 && march_single(c, mask != 0) && !(mask && c->acc_pending)) break;
       if (mask && (rc = ensure_accrows(c, tile_blocks(c, shape)))) return rc;
       hipError_t e = launch_tile_steps(c, shape, m, c->cur, mask ? WHAT_STEP_ACCUM : WHAT_STEP, mask, c->stream,
                                        (uint32_t)c->t, nullptr);
@@ -516,7 +563,7 @@ int lb_step(lb_ctx *c, int64_t n) {
       n -= m;
     }
   }
-  if (pairs_on(c) && c->reduce_every == 0) {
+  if (path == Path::Pairs) {
     for (; n >= 2; n -= 2) {
       hipError_t e = launch_two_steps(c, c->cur, c->stream, (uint32_t)c->t, nullptr);
       if (e != hipSuccess) return hip_fail(c, e, "two-step kernel launch");
@@ -852,7 +899,7 @@ int lb_autotune(lb_ctx *c, int32_t trial_steps, int32_t *tx_out, int32_t *sy_out
   // the tile step competes too; where it wins, the shape found serves the passes that march
   const bool set0 = c->shape_set;
   c->shape_set = false;
-  if (!rc && tiles_on(c)) {
+  if (!rc && step_path(c, false) == Path::Tiles) {
     const int shape = tile_shape(c), n = tile_steps(c, shape, 1 << 20);
     const double ms = time_launches(c->stream, 2, trial_steps, [&]() {
       return launch_tile_steps(c, shape, n, c->cur, WHAT_STEP, 0, c->stream, (uint32_t)c->t, nullptr);
