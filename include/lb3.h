@@ -68,8 +68,9 @@ int lb3_init(lb3_ctx **out, const lb3_lattice *lat, const lb3_couplings *cpl, co
              const lb_psi_params *psi, const double *rho_init, void *pop_a, void *pop_b, size_t pop_bytes,
              void *hip_stream);
 
-/* Advance n >= 0 steps of eq. (LB) in 3-D: one fused launch per step, or two on small lattices,
-   whose context then holds a field of psi and rho (pull streaming with
+/* Advance n >= 0 steps of eq. (LB) in 3-D: one fused launch per step, or two on lattices of few
+   planes per compute unit whose population buffer fits the Infinity Cache (256 MiB); such a context
+   holds a field of psi and rho, n_species^2 values per site, allocated by lb3_init (pull streaming with
    bounce-back, moments, psi, the two-belt force of eq. (FORCE) over the cube, the A-B
    repulsion and the body force, the velocity shift, BGK collision with the rest-population
    closure, store).  Asynchronous. */

@@ -156,15 +156,17 @@ void march_grid3(const lb3_ctx *c, Lb3Args &a) {
   a.stream_stores = host::streaming_stores(lb3_pop_bytes(&c->lat));
 }
 
-// Whether the step goes in two passes (lb3_split.hip) instead of the march: where the march's
-// segments have at most eight planes, of which it pulls four more than it updates.  us per step,
-// split and march: FP32 64 x 48 x 40 19 and 26, 100 x 70 x 60 (segments of five) 54 and 61,
-// 128 x 128 x 64 (eight) 103 and 113, 128^3 (sixteen) 235 and 190; FP64 64 x 48 x 40 27 and 31,
-// 100 x 70 x 60 (nine) 110 and 98.
+// Whether the step goes in two passes (lb3_split.hip) instead of the march: where the march's segments have at
+// most eight planes, of which it pulls four more than it updates, and a population buffer fits the
+// Infinity Cache, which then serves the second pass's pull.  us per step, split and march: FP32 64 x 48 x 40
+// 19 and 26, 100 x 70 x 60 (segments of five) 54 and 61, 128 x 128 x 64 (eight) 103 and 113, 128^3 (sixteen)
+// 235 and 190; FP64 64 x 48 x 40 27 and 31, 100 x 70 x 60 (nine) 110 and 98; slabs, FP32 two species,
+// 128 x 128 x 8 20 and 32, 512 x 384 x 8 (228 MiB) 177 and 192, 512 x 512 x 8 (304 MiB) 235 and 215,
+// 1024 x 1024 x 5 (760 MiB) 722 and 578, FP64 1502 and 1055.
 bool split_rule(const lb3_ctx *c) {
   Lb3Args a{};
   march_grid3(c, a);
-  return a.sz <= 8;
+  return a.sz <= 8 && lb3_pop_bytes(&c->lat) <= host::kInfinityCacheBytes;
 }
 
 int mode3(const lb3_ctx *c) { return c->lat.storage == LB_F64 ? MODE_F64 : MODE_F32; }
@@ -275,13 +277,17 @@ int lb3_init(lb3_ctx **out, const lb3_lattice *lat, const lb3_couplings *cpl, co
   void *d_rho = nullptr;
   const size_t rho_bytes = (size_t)lat->n_species * nsite * sizeof(double);
   if ((e = hipMalloc(&c->d_totals, RED3_N * sizeof(double))) != hipSuccess ||
-      (split_rule(c) && (e = hipMalloc(&c->d_psi, nsite * lat->n_species * lat->n_species * elem3(lat->storage))) != hipSuccess) ||
       (e = hipMalloc(&d_rho, rho_bytes)) != hipSuccess ||
       (e = hipMemcpyAsync(d_rho, rho_init, rho_bytes, hipMemcpyHostToDevice, c->stream)) != hipSuccess) {
     g_init_error3 = std::string("allocation / copy: ") + hipGetErrorString(e);
     if (d_rho) (void)hipFree(d_rho);
     lb3_destroy(c);
     return LB_EDEVICE;
+  }
+  // no memory for the split step's field: the march needs none
+  if (split_rule(c) && hipMalloc(&c->d_psi, nsite * lat->n_species * lat->n_species * elem3(lat->storage)) != hipSuccess) {
+    c->d_psi = nullptr;
+    (void)hipGetLastError();
   }
   Lb3Layout la = layout3(c);
   la.in = d_rho;
