@@ -62,6 +62,7 @@ void march3_kernel(Lb3Args a) {
   constexpr uint32_t site_b = (uint32_t)(NS * sizeof(S));
   const uint32_t plane_b = (uint32_t)a.pitch * site_b, row_b = 19u * plane_b;
   const uint64_t zplane_b = (uint64_t)row_b * (uint32_t)ly;
+  const uint32_t off = (uint32_t)zplane_b;  // past the range (see pull3)
   auto zrsrc = [&](const void *p, int z, bool on) {
     return make_rsrc(static_cast<const char *>(p) + (uint64_t)(uint32_t)z * zplane_b, on ? (uint32_t)zplane_b : 0u);
   };
@@ -110,14 +111,14 @@ void march3_kernel(Lb3Args a) {
   if (!has_halo) {
     halo.lo = halo.hi = false;
     for (int k = 0; k < 3; ++k) {
-      halo.row[k] = kOff3;
+      halo.row[k] = off;
       halo.col[k] = 0u;
     }
   }
 
   auto pull = [&](const Pull3 &q, int z, bool on, R (&f)[NS][19], R (&fb)[NS][2]) {
     const Rsrc rz[3] = {zrsrc(a.src, d3::wrap(z + 1, lz), on), zrsrc(a.src, z, on), zrsrc(a.src, d3::wrap(z - 1, lz), on)};
-    pull3<C, NS, WALLS>(rz, q, plane_b, f, fb);
+    pull3<C, NS, WALLS>(rz, q, plane_b, off, f, fb);
   };
   // psi and rho of a pulled site into entry e of ring slots sp (psi) and sr (rho)
   auto ring_put = [&](R (&f)[NS][19], const R (&fb)[NS][2], const Pull3 &q, bool wall, int sp, int sr, int e) {
@@ -204,7 +205,7 @@ void march3_kernel(Lb3Args a) {
     auto xr = [&](int dx, int dy, int dz) { return psi_ring[(int)xo[dz + 1] + (ty + dy + 2) * W3 + tx + dx + 2]; };
     site3_update<C, NS, WHAT, STP>(
         a, p, f, [&](int dx, int dy, int dz) { return pl[dz + 2][(dy + 2) * W3 + dx + 2]; },
-        xr, x, y, z, site_ok, zrsrc(a.dst, z, STORE), site_ok ? own.row[1] + own.col[1] : kOff3, plane_b);
+        xr, x, y, z, site_ok, zrsrc(a.dst, z, STORE), site_ok ? own.row[1] + own.col[1] : off, plane_b);
     // the frame's loads last: in registers that the updated populations have left
     __builtin_amdgcn_sched_barrier(0);
     pull(halo, zwrap(z + 3), more, hf, hb);

@@ -9,9 +9,6 @@
 
 namespace lb355 {
 
-// Past every descriptor's range: loads give zeros, stores are dropped, neither moves bytes.
-constexpr uint32_t kOff3 = 0xfff00000u;
-
 // Where a site's pulls come from, relative to a z-plane: lane offsets of the source rows y - 1, y,
 // y + 1 (index cy: source row y - c_y) and columns, and whether the rows beside it are walls.
 struct Pull3 {
@@ -37,10 +34,11 @@ __device__ __forceinline__ Pull3 pull3_at(int x, int y, int lx, int ly, uint32_t
 // z + 1, z, z - 1.  Beside a wall the two links that leave it diagonally in z come from the site's
 // own plane instead of a neighbouring one, which a lane offset cannot say: they are loaded apart,
 // into fb (zeros without traffic for every other site), and wall_fix3 puts them in place once
-// loaded.
+// loaded.  off: a lane offset past the descriptors' range, where loads give zeros, stores are dropped and
+// neither moves bytes: the bytes of a z-plane, as no constant below 4 GiB is past every plane.
 template <class C, int NS, bool WALLS>
-__device__ __forceinline__ void pull3(const Rsrc (&rz)[3], const Pull3 &q, uint32_t plane_b, typename C::R (&f)[NS][19],
-                                      typename C::R (&fb)[NS][2]) {
+__device__ __forceinline__ void pull3(const Rsrc (&rz)[3], const Pull3 &q, uint32_t plane_b, uint32_t off,
+                                      typename C::R (&f)[NS][19], typename C::R (&fb)[NS][2]) {
   using R = typename C::R;
   auto load = [&](const Rsrc &r, uint32_t vo, uint32_t so, R &f0, R &f1) {
     if (NS == 2) C::bload2(r, vo, so, f0, f1);
@@ -58,8 +56,8 @@ __device__ __forceinline__ void pull3(const Rsrc (&rz)[3], const Pull3 &q, uint3
       load(rz[1 + cz], direct, uni((uint32_t)l * plane_b), f[0][l], f[NS - 1][l]);
   }
   if constexpr (WALLS) {  // links 15, 17 off the lower wall, 16, 18 off the upper one
-    load(rz[1], q.lo ? here + 16 * plane_b : (q.hi ? here + 15 * plane_b : kOff3), 0u, fb[0][0], fb[NS - 1][0]);
-    load(rz[1], q.lo ? here + 18 * plane_b : (q.hi ? here + 17 * plane_b : kOff3), 0u, fb[0][1], fb[NS - 1][1]);
+    load(rz[1], q.lo ? here + 16 * plane_b : (q.hi ? here + 15 * plane_b : off), 0u, fb[0][0], fb[NS - 1][0]);
+    load(rz[1], q.lo ? here + 18 * plane_b : (q.hi ? here + 17 * plane_b : off), 0u, fb[0][1], fb[NS - 1][1]);
   }
 }
 

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256) void psi3_kernel(Lb3Args a) {
     rz[k] = make_rsrc(static_cast<const char *>(a.src) + (uint64_t)(uint32_t)d3::wrap(z + 1 - k, a.lz) * zplane_b,
                       (uint32_t)zplane_b);
   R f[NS][19], fb[NS][2];
-  pull3<C, NS, WALLS>(rz, q, plane_b, f, fb);
+  pull3<C, NS, WALLS>(rz, q, plane_b, (uint32_t)zplane_b, f, fb);
   wall_fix3<WALLS>(q, fb, f);
   V ps, rh;
 #pragma unroll
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(SX *SY *SZ) void split3_kernel(Lb3Args a) {
     rz[k] = make_rsrc(static_cast<const char *>(a.src) + (uint64_t)(uint32_t)d3::wrap(min(z, lz - 1) + 1 - k, lz) * zplane_b,
                       (uint32_t)zplane_b);
   R f[NS][19], fb[NS][2];
-  pull3<C, NS, WALLS>(rz, q, plane_b, f, fb);
+  pull3<C, NS, WALLS>(rz, q, plane_b, (uint32_t)zplane_b, f, fb);
 
   // the field of the tile and its frames
   const bool narrow = lx < 2 * PX || ly < 2 * PY || lz < 2 * PZ;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(SX *SY *SZ) void split3_kernel(Lb3Args a) {
       a, p, f, [&](int dx, int dy, int dz) { return pc[(dz * PY + dy) * PX + dx]; },
       [&](int dx, int dy, int dz) { return xc[dz * xz + dy * xy + dx]; }, x, y, z, ok,
       make_rsrc(static_cast<char *>(a.dst) + (uint64_t)(uint32_t)min(z, lz - 1) * zplane_b, (uint32_t)zplane_b),
-      ok ? q.row[1] + q.col[1] : kOff3, plane_b);
+      ok ? q.row[1] + q.col[1] : (uint32_t)zplane_b, plane_b);
 }
 
 int split3_tiles(int lx, int ly, int lz, int *nstrip, int *nband) {

@@ -37,6 +37,22 @@ def test_slab_is_bitwise_the_set_shape(lx, ly, lz, storage, ns, walls):
         sim.close()
 
 
+def test_z_planes_of_nearly_4_gib():
+    """A plane that ends less than 1 MiB below 4 GiB: the lanes past a ragged strip's end neither read nor write."""
+    import torch
+    lx, ly, lz = 5, 882900, 5  # rows of 19 x 64 values
+    assert 2**32 - 2**20 < 19 * 64 * 4 * ly < 2**32
+    f = []
+    for tile in (None, (4, 8)):
+        sim = make(lx, ly, lz, "f32", 1, False, tile=tile)
+        print(tile, flush=True)
+        sim.step(2)
+        f.append(sim.checkpoint())
+        sim.close()
+        del sim
+    assert torch.equal(*f)
+
+
 def test_slab_past_the_cache_holds_no_field():
     import torch
     lx, ly, lz = 1024, 1024, 5  # 760 MiB per buffer; a field would take 84 MB
