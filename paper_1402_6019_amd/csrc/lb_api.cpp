@@ -940,8 +940,13 @@ struct AdjLayout {
   int64_t per = 1;   // states per segment buffer
   int nbuf = 1;      // segment buffers
   int nck = 0;       // segments recomputed from a checkpoint (all but the last nbuf)
-  size_t popb = 0, lamb = 0, nsite = 0, fb = 0, xw = 0;
-  size_t ckpt = 0, seg = 0, lam0 = 0, lam1 = 0, fields = 0, partials = 0, acc = 0;
+  // Checkpoints are copies of a population buffer; packed: without its rows' padding, where that makes them larger
+  // than FP64 copies of the sites (64 columns: three quarters of a row), and a segment starts from the buffer
+  // `spare` they unpack to.  Packing takes about 6 us per copy: 130 x 250 FP64, T = 144, 3250 us and 152 MB
+  // not packed, 3320 us and 116 MB packed.
+  bool packed = false;
+  size_t popb = 0, ckptb = 0, lamb = 0, nsite = 0, fb = 0, xw = 0;
+  size_t ckpt = 0, spare = 0, seg = 0, lam0 = 0, lam1 = 0, fields = 0, partials = 0, acc = 0;
   size_t total = 0;
 };
 
@@ -968,11 +973,15 @@ AdjLayout adjoint_layout(const lb_ctx *c, int64_t T, int32_t every, int32_t flag
   L.nck = L.ncp - L.nbuf;
   const int64_t nstate = L.per * L.nbuf;
   L.popb = align256(lb_pop_bytes(&c->lat));
+  L.ckptb = align256((size_t)ns * 9 * L.nsite * elem_size(c->lat.storage));
+  L.packed = L.popb > (size_t)ns * 9 * L.nsite * 8 && L.nck * L.ckptb + L.popb < L.nck * L.popb;
+  if (!L.packed) L.ckptb = L.popb;
   L.xw = align256((size_t)ns * 9 * 2 * c->lat.lx * 8);
   L.lamb = align256((size_t)ns * 9 * L.nsite * rs);
   L.fb = align256(8 * L.nsite * rs);
   size_t o = 0;
-  L.ckpt = o; o += (size_t)L.nck * L.popb;
+  L.ckpt = o; o += (size_t)L.nck * L.ckptb;
+  L.spare = o; o += L.packed ? L.popb : 0;
   L.seg = o; o += (size_t)nstate * L.xw;
   L.lam0 = o; o += L.lamb;
   L.lam1 = o; o += L.lamb;
@@ -1061,13 +1070,28 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
                                 fp64, c->stream);
     return src;
   };
+  // Checkpoint k from the current state, and the state it holds as a population buffer.
+  auto ckpt_at = [&](int k) { return ws + L.ckpt + (size_t)k * L.ckptb; };
+  const size_t site_b = c->lat.n_species * elem_size(c->lat.storage), row_b = c->lat.lx * site_b, pitch_b = c->pitch * site_b;
+  auto save_ckpt = [&](int k) {
+    if (!L.packed)
+      return launch_stream_copy(ckpt_at(k), c->pop[c->cur], lb_pop_bytes(&c->lat) / 16, 0, 4 * c->n_cu, c->stream);
+    return hipMemcpy2DAsync(ckpt_at(k), row_b, c->pop[c->cur], pitch_b, row_b, (size_t)9 * c->lat.ly, hipMemcpyDeviceToDevice,
+                            c->stream);
+  };
+  auto load_ckpt = [&](int k, hipError_t *er) -> void * {
+    if (!L.packed) return ckpt_at(k);
+    if (*er == hipSuccess)
+      *er = hipMemcpy2DAsync(ws + L.spare, pitch_b, ckpt_at(k), row_b, row_b, (size_t)9 * c->lat.ly, hipMemcpyDeviceToDevice,
+                             c->stream);
+    return ws + L.spare;
+  };
   // Forward pass: the last segments, one per buffer, leave what the reverse sweep reads as they are
   // stepped; a segment before them leaves a copy of the populations it starts from.
   hipError_t e = hipSuccess;
   for (int k = 0; k < L.ncp && e == hipSuccess; ++k) {
     if (k < L.nck) {
-      e = launch_stream_copy(ws + L.ckpt + (size_t)k * L.popb, c->pop[c->cur], lb_pop_bytes(&c->lat) / 16, 0, 4 * c->n_cu,
-                             c->stream);
+      e = save_ckpt(k);
       if (e == hipSuccess && (rc = lb_step(c, seg_len(k)))) return done(rc);
     } else {
       c->cur = states(k, c->pop[c->cur], c->pop[c->cur ^ 1], &e) == c->pop[0] ? 0 : 1;
@@ -1076,7 +1100,7 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   }
   if (e != hipSuccess) return done(hip_fail(c, e, "adjoint forward pass"));
   // the final state stays in its buffer: a recompute alternates between the other one and the
-  // checkpoint it starts from, which nothing reads again
+  // checkpoint it starts from (packed: the buffer it unpacks to), which nothing reads again
   const int cur_final = c->cur;
   if (!L.all) e = launch_fill(c->d_acc, 0.0, 4, c->stream);  // the running wall-stress average is reset
   if (e == hipSuccess) e = launch_zero(ws + L.lam1, L.lamb, c->stream);
@@ -1145,7 +1169,8 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   // recompute segment k from its checkpoint into buffer k % nbuf (context's stream)
   auto recompute_segment = [&](int k) -> int {
     hipError_t er = hipStreamWaitEvent(c->stream, ev_rev[k % L.nbuf], 0);
-    (void)states(k, ws + L.ckpt + (size_t)k * L.popb, c->pop[cur_final ^ 1], &er);
+    void *const from = load_ckpt(k, &er);
+    (void)states(k, from, c->pop[cur_final ^ 1], &er);
     if (er == hipSuccess) er = hipEventRecord(ev_rec[k % L.nbuf], c->stream);
     if (er != hipSuccess) return hip_fail(c, er, "adjoint recompute");
     return LB_OK;
