@@ -77,9 +77,10 @@ enum lb_rounding {
 
 /* Population store policy of the plain and reducing step kernels (lb_set_store_policy). */
 enum lb_store_policy {
-  LB_STORES_AUTO = 0,          /* by footprint: streaming once both buffers exceed 256 MiB */
+  LB_STORES_AUTO = 0,          /* by footprint and kernel, see lb_set_store_policy */
   LB_STORES_WRITE_THROUGH = 1, /* stores written through L2 and kept by the Infinity Cache */
-  LB_STORES_STREAMING = 2      /* non-temporal stores, lead-row loads issued without a branch */
+  LB_STORES_STREAMING = 2      /* non-temporal stores where the kernel has them (marched rows: lead-row
+                                  loads issued without a branch, too) */
 };
 
 typedef struct {
@@ -233,10 +234,12 @@ int lb_set_tile(lb_ctx *ctx, int32_t tx, int32_t sy);
 int lb_get_tile(const lb_ctx *ctx, int32_t *tx, int32_t *sy);
 
 /* Choose the step kernel's variant for the population traffic (enum lb_store_policy).  The
-   default, LB_STORES_AUTO, takes the streaming variant when both population buffers together
-   exceed the 256 MiB Infinity Cache and the write-through one otherwise; the other two values
-   force one.  All variants give bitwise identical results; only their speed differs.
-   Captured graphs are rebuilt.  Host call; LB_EINVAL for any other value. */
+   default, LB_STORES_AUTO, streams when both population buffers together exceed the 256 MiB
+   Infinity Cache, except in tiles of two or three FP32 or BF16 steps and in pairs of steps, which
+   write through at any size.  The other two values force one variant in marched rows, in pairs and in the
+   tiles of lattices of more than 512 sites per compute unit; smaller lattices, which the caches hold,
+   take tiles that have the write-through variant alone.  All variants give bitwise identical results;
+   only their speed differs.  Captured graphs are rebuilt.  Host call; LB_EINVAL for any other value. */
 int lb_set_store_policy(lb_ctx *ctx, int32_t policy);
 
 /* Rounding of the population stores of a BF16-deviation context (enum lb_rounding).  With
