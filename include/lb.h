@@ -270,9 +270,10 @@ int lb_set_rounding(lb_ctx *ctx, int32_t mode);
 enum lb_two_step { LB_TWO_STEP_OFF = 0, LB_TWO_STEP_ON = 1, LB_TWO_STEP_AUTO = 2 };
 int lb_set_two_step(lb_ctx *ctx, int32_t enable, int32_t rows);
 
-/* 1 if the two-step rule (lb_set_two_step and the reduction setting) pairs this lattice's plain
-   steps, 0 if not, -1 for a NULL context.  It does not count the steps per launch of the tile
-   step.  Pure host call. */
+/* 1 if the two-step rule pairs this lattice's plain steps once a launch shape is set: LB_TWO_STEP_ON,
+   or LB_TWO_STEP_AUTO for walled FP32 and periodic FP64 lattices whose two buffers exceed the Infinity
+   Cache, without reductions; 0 if not, -1 for a NULL context.  Until a shape is set, AUTO takes tiles
+   of two or three steps on most lattices, paired by this rule or not.  Pure host call. */
 int lb_two_step_active(const lb_ctx *ctx);
 
 /* Replay plain steps from captured HIP graphs: with steps > 0 (even) and no reductions

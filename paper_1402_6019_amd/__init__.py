@@ -140,8 +140,8 @@ class Sim:
 
     @property
     def two_step_active(self):
-        """Whether the rule of set_two_step pairs this lattice's plain steps (it does not count the
-        steps per launch of the tile step)."""
+        """Whether the rule of set_two_step pairs this lattice's plain steps once a launch shape is
+        set (until then most lattices take tiles of two or three steps instead)."""
         return self._lib.lb_two_step_active(self._h) == 1
 
     def step(self, n=1):

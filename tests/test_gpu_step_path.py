@@ -54,3 +54,24 @@ def test_default_path_is_bitwise_the_marched_rows(lx, ly, storage, ns, walls, ev
         assert np.abs(a - b).max() <= 1e-12 * np.abs(b).max()
     for sim in sims:
         sim.close()
+
+
+@pytest.mark.parametrize("lx,ly,storage,ns,walls", [(2100, 900, "f32", 2, True), (1040, 1030, "f64", 2, False),
+                                                    (1500, 1300, "f64", 1, False)])
+def test_automatic_pairs_in_a_set_shape(lx, ly, storage, ns, walls):
+    """With a launch shape set, the automatic rule pairs the steps of walled FP32 and periodic FP64 lattices beyond
+    the Infinity Cache: odd and even counts and graph replay, against the tiles and single marched steps."""
+    import torch
+    c = case(lx, ly, storage, ns, walls)
+    print(lx, ly, storage, ns, walls, flush=True)
+    f = []
+    for tile, two in ((None, "auto"), ((128, 30), "auto"), ((128, 30), False)):
+        sim = make_sim(c, tile=tile)
+        sim.set_two_step(two)
+        assert sim.two_step_active == (two == "auto")
+        sim.step(5)
+        sim.set_graph(6)
+        sim.step(14)
+        f.append(sim.checkpoint())
+        sim.close()
+    assert torch.equal(f[0], f[1]) and torch.equal(f[0], f[2])
