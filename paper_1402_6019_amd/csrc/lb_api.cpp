@@ -61,7 +61,7 @@ struct lb_ctx {
   bool check_pending = false;
   bool unstable = false;
   GraphCache graph;  // graph.steps > 0: plain steps are replayed from captured graphs
-  double *d_prof = nullptr;      // profile pass: [ncb][ly][PROF_N] block sums, then [ly][PROF_N] row sums
+  double *d_prof = nullptr;      // profile pass: sums of 64-column blocks [ncb][ly][PROF_N]
   size_t prof_cap = 0;           // doubles
   std::string err;
 };
@@ -655,7 +655,7 @@ int lb_totals(lb_ctx *c, double mass[2], double momentum[2], double *flow) {
   StepArgs a = observe_args(c);
   a.partials = c->d_partials;
   hipError_t e = run_observe(c, WHAT_OBSERVE, a);
-  if (e == hipSuccess) e = launch_reduce(c->d_partials, nb, c->d_totals, c->d_acc, 0, 1.0 / c->lat.lx, c->stream);
+  if (e == hipSuccess) e = launch_reduce(c->d_partials, nb, c->d_totals, 1.0 / c->lat.lx, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "totals kernel launch");
   double h[RED_N];
   e = hipMemcpyAsync(h, c->d_totals, sizeof(h), hipMemcpyDeviceToHost, c->stream);

@@ -51,7 +51,7 @@ struct lb_batch {
   ReduceJob *d_ojobs = nullptr;
   double *d_partials = nullptr;  // [observe_blocks of all instances][RED_N]
   double *d_accrows = nullptr;   // [tiles][ACC_N]: running sums of reducing steps (zero after a flush)
-  double *d_prof = nullptr;      // profile pass of one instance: block sums, then row sums
+  double *d_prof = nullptr;      // profile pass of one instance: sums of 64-column blocks
   size_t prof_cap = 0;           // doubles
   int64_t acc_pending = 0;       // reducing launches since the last flush
   double *d_totals = nullptr;    // [n][RED_N]
@@ -266,15 +266,14 @@ int launch_grid(const lb_batch *b, int ntiles) {
   return std::max(1, std::min(g, ntiles));
 }
 
-// One launch over tiles [first, first + count) from buffer `from` to the other one.
-hipError_t launch_tiles(const lb_batch *b, int what, int from, int first, int count, hipStream_t st,
+// One launch of marched rows over every tile from buffer `from` to the other one.
+hipError_t launch_tiles(const lb_batch *b, int what, int from, hipStream_t st,
                         uint32_t t_step = 0, const double *t_base = nullptr) {
   BatchArgs a;
   std::memset(&a, 0, sizeof(a));
   a.inst = b->d_args;
   a.tiles = b->d_tiles;
-  a.tile0 = first;
-  a.ntiles = count;
+  a.ntiles = (int)b->tiles.size();
   a.src = static_cast<const char *>(b->pop[from]);
   a.dst = static_cast<char *>(b->pop[from ^ 1]);
   a.accrows = b->d_accrows;
@@ -282,7 +281,7 @@ hipError_t launch_tiles(const lb_batch *b, int what, int from, int first, int co
   a.t_step = t_step;
   a.t_base = t_base;
   const int mode = b->storage == LB_BF16DEV && b->rounding == LB_ROUND_STOCHASTIC ? MODE_BF16SR : b->storage;
-  return launch_batch_step(mode, b->ns, b->walls, what, b->tx, launch_grid(b, count), a, st);
+  return launch_batch_step(mode, b->ns, b->walls, what, b->tx, launch_grid(b, a.ntiles), a, st);
 }
 
 // Arguments of a pass over the current state of instance i, as for one lattice.
@@ -453,7 +452,6 @@ int lb_batch_step(lb_batch *b, int64_t n) {
   if (n < 0) return bfail(b, LB_EINVAL, "n must be >= 0");
   int rc = poll(b, false);
   if (rc) return rc;
-  const int nt = (int)b->tiles.size();
   if (b->graph.steps > 0 && b->reduce_every == 0) {
     while (n >= b->graph.steps) {
       hipGraphExec_t g = nullptr;
@@ -476,7 +474,7 @@ int lb_batch_step(lb_batch *b, int64_t n) {
               }
               return er;
             }
-            return launch_tiles(b, WHAT_STEP, from ^ (k & 1), 0, nt, st, (uint32_t)k, tb);
+            return launch_tiles(b, WHAT_STEP, from ^ (k & 1), st, (uint32_t)k, tb);
           },
           &g);
       // the replay's steps are t + k: the base goes to device memory (a fill kernel, outside the graph)
@@ -505,7 +503,7 @@ int lb_batch_step(lb_batch *b, int64_t n) {
   }
   for (int64_t k = 0; k < n; ++k) {
     const bool red = b->reduce_every > 0 && (b->t % b->reduce_every) == 0;
-    hipError_t e = launch_tiles(b, red ? WHAT_STEP_ACCUM : WHAT_STEP, b->cur, 0, nt, b->stream, (uint32_t)b->t);
+    hipError_t e = launch_tiles(b, red ? WHAT_STEP_ACCUM : WHAT_STEP, b->cur, b->stream, (uint32_t)b->t);
     if (e != hipSuccess) return bhip(b, e, "batch step launch");
     reduced |= red;
     if (red) ++b->acc_pending;
@@ -598,9 +596,8 @@ int lb_batch_autotune(lb_batch *b, int32_t trial_steps, int32_t out[3], double *
       for (int persistent = 0; persistent < 2 && !rc; ++persistent) {
         b->grid = persistent ? resident(b, tx) : 0;
         if ((rc = build_tiles(b, tx, sy))) break;
-        const int nt = (int)b->tiles.size();
         const double ms =
-            time_launches(b->stream, 2, trial_steps, [&]() { return launch_tiles(b, WHAT_STEP, b->cur, 0, nt, b->stream); });
+            time_launches(b->stream, 2, trial_steps, [&]() { return launch_tiles(b, WHAT_STEP, b->cur, b->stream); });
         if (ms < 0.0) {
           rc = bhip(b, hipGetLastError(), "autotune trial");
           break;
@@ -712,7 +709,7 @@ int lb_batch_totals(lb_batch *b, double *out) {
   for (int i = 0, m = std::max(1, kMaxBlocks / blocks); i < b->n && e == hipSuccess; i += m)
     e = launch_batch_observe(b->storage, b->ns, b->walls, i, std::min(m, b->n - i), blocks, a, b->d_ojobs, b->d_partials,
                              b->stream);
-  if (e == hipSuccess) e = launch_batch_reduce(b->d_partials, b->d_ojobs, b->n, b->d_totals, b->d_acc, 0, b->stream);
+  if (e == hipSuccess) e = launch_batch_reduce(b->d_partials, b->d_ojobs, b->n, b->d_totals, b->stream);
   std::vector<double> h((size_t)b->n * RED_N);
   if (e == hipSuccess)
     e = hipMemcpyAsync(h.data(), b->d_totals, h.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream);

@@ -40,7 +40,7 @@ enum ProfSlot { PROF_U = 0, PROF_KUP, PROF_KDN, PROF_I1, PROF_I2, PROF_RA, PROF_
 
 // Partial-sum slots written per workgroup (and totals after the second pass).
 enum RedSlot {
-  RED_MASS0 = 0, RED_MASS1, RED_PX, RED_PY, RED_WBOT, RED_WTOP, RED_FLOW, RED_BAD, RED_N
+  RED_MASS0 = 0, RED_MASS1, RED_PX, RED_PY, RED_FLOW, RED_BAD, RED_N
 };
 
 // Kernel arguments of the fused step (passed by value through the kernarg segment).
@@ -65,8 +65,7 @@ struct StepArgs {
   long long offset;           // batch: byte offset of this instance in each population buffer
   double wall_mom[2][2];      // [bottom, top][species]: rho_w,s U / 6, added on reflection
   int moving;                 // some wall moves (wall_mom != 0)
-  int ncb;                    // profile: 64-column blocks per row in prof
-  double *prof;               // profile: [ncb][ly][PROF_N]
+  double *prof;               // profile: [64-column blocks][ly][PROF_N]
   int stream_stores;          // both population buffers exceed the Infinity Cache: non-temporal stores
   uint32_t t_step;            // MODE_BF16SR: time step of the launch, plus *t_base when t_base is set
   const double *t_base;       // (graph replays: the step at which the replay starts)
@@ -180,11 +179,11 @@ struct TileDesc {
   int part;   // row of reduction partials this tile writes
 };
 
-// Kernel arguments of the batched step: tiles [tile0, tile0 + ntiles) of the table.
+// Kernel arguments of the batched step: the ntiles tiles of the table.
 struct BatchArgs {
   const StepArgs *inst;  // [n] per-instance arguments (device)
   const TileDesc *tiles; // tile table (device)
-  int tile0, ntiles;
+  int ntiles;
   const char *src;       // population buffers holding every instance at StepArgs::offset
   char *dst;
   int stream_stores;     // non-temporal population stores (see StepArgs)
@@ -271,8 +270,7 @@ hipError_t launch_step(int mode, int ns, int walls, int what, int tx, int nblock
 // A pass over the current state (WHAT_MOMENTS, WHAT_OBSERVE, WHAT_PROFILE or WHAT_STRESS; a.src, the pass's
 // outputs in a) of one lattice; n_cu: compute units.  WHAT_OBSERVE writes observe_blocks rows of partials.
 hipError_t launch_observe(int mode, int ns, int walls, int what, int n_cu, const StepArgs &a, hipStream_t st);
-hipError_t launch_reduce(const double *partials, int nblocks, double *totals, double *acc, int accumulate,
-                         double inv_lx, hipStream_t st);
+hipError_t launch_reduce(const double *partials, int nblocks, double *totals, double inv_lx, hipStream_t st);
 hipError_t launch_init(int mode, int walls, const LayoutArgs &a, hipStream_t st);
 hipError_t launch_checkpoint(int mode, int walls, const LayoutArgs &a, hipStream_t st);
 hipError_t launch_restore(int mode, int walls, const LayoutArgs &a, hipStream_t st);
@@ -301,8 +299,7 @@ hipError_t launch_batch_step(int mode, int ns, int walls, int what, int tx, int 
 // observe_blocks rows of partials start at jobs[i].p0 (device).  blocks: the most of any instance.
 hipError_t launch_batch_observe(int mode, int ns, int walls, int first, int count, int blocks, const BatchTiles &b,
                                 const ReduceJob *jobs, double *partials, hipStream_t st);
-hipError_t launch_batch_reduce(const double *partials, const ReduceJob *jobs, int njobs, double *totals, double *acc,
-                               int accumulate, hipStream_t st);
+hipError_t launch_batch_reduce(const double *partials, const ReduceJob *jobs, int njobs, double *totals, hipStream_t st);
 
 size_t step_lds_bytes(int mode, int ns, int tx);
 

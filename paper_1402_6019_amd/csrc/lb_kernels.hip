@@ -14,8 +14,7 @@
 namespace lb355 {
 
 // Second reduction pass: fixed-order sum of the per-workgroup partials (deterministic).
-__device__ __forceinline__ void reduce_block(const double *partials, int nblocks, double *totals, double *acc,
-                                             int accumulate, double inv_lx) {
+__device__ __forceinline__ void reduce_block(const double *partials, int nblocks, double *totals, double inv_lx) {
   __shared__ double sm[256][RED_N];
   const int tid = threadIdx.x;
   double v[RED_N];
@@ -37,23 +36,14 @@ __device__ __forceinline__ void reduce_block(const double *partials, int nblocks
     double t[RED_N];
 #pragma unroll
     for (int k = 0; k < RED_N; ++k) t[k] = sm[0][k];
-    t[RED_WBOT] *= inv_lx;
-    t[RED_WTOP] *= inv_lx;
     t[RED_FLOW] *= inv_lx;
 #pragma unroll
     for (int k = 0; k < RED_N; ++k) totals[k] = t[k];
-    if (accumulate) {
-      acc[0] += t[RED_WBOT];
-      acc[1] += t[RED_WTOP];
-      acc[2] += 1.0;
-      acc[3] += t[RED_BAD];
-    }
   }
 }
 
-__global__ __launch_bounds__(256) void reduce_kernel(const double *partials, int nblocks, double *totals, double *acc,
-                                                     int accumulate, double inv_lx) {
-  reduce_block(partials, nblocks, totals, acc, accumulate, inv_lx);
+__global__ __launch_bounds__(256) void reduce_kernel(const double *partials, int nblocks, double *totals, double inv_lx) {
+  reduce_block(partials, nblocks, totals, inv_lx);
 }
 
 // Second pass of the stepping sums: rows [nrows][ACC_N] of running sums (one per workgroup of
@@ -100,11 +90,9 @@ __global__ __launch_bounds__(256) void batch_flush_kernel(double *rows, const Re
 }
 
 // One workgroup per instance of a batch: its tiles' partials are a contiguous range.
-__global__ __launch_bounds__(256) void batch_reduce_kernel(const double *partials, const ReduceJob *jobs,
-                                                           double *totals, double *acc, int accumulate) {
+__global__ __launch_bounds__(256) void batch_reduce_kernel(const double *partials, const ReduceJob *jobs, double *totals) {
   const ReduceJob j = jobs[blockIdx.x];
-  reduce_block(partials + (size_t)j.p0 * RED_N, j.n, totals + (size_t)blockIdx.x * RED_N,
-               acc + (size_t)blockIdx.x * 4, accumulate, j.inv_lx);
+  reduce_block(partials + (size_t)j.p0 * RED_N, j.n, totals + (size_t)blockIdx.x * RED_N, j.inv_lx);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -229,10 +217,9 @@ hipError_t launch_batch_step(int mode, int ns, int walls, int what, int tx, int 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_batch_reduce(const double *partials, const ReduceJob *jobs, int njobs, double *totals, double *acc,
-                               int accumulate, hipStream_t st) {
+hipError_t launch_batch_reduce(const double *partials, const ReduceJob *jobs, int njobs, double *totals, hipStream_t st) {
   if (njobs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(batch_reduce_kernel, dim3(njobs), dim3(256), 0, st, partials, jobs, totals, acc, accumulate);
+  hipLaunchKernelGGL(batch_reduce_kernel, dim3(njobs), dim3(256), 0, st, partials, jobs, totals);
   return hipGetLastError();
 }
 
@@ -461,9 +448,8 @@ hipError_t launch_fill(double *p, double v, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(const double *partials, int nblocks, double *totals, double *acc, int accumulate,
-                         double inv_lx, hipStream_t st) {
-  hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(256), 0, st, partials, nblocks, totals, acc, accumulate, inv_lx);
+hipError_t launch_reduce(const double *partials, int nblocks, double *totals, double inv_lx, hipStream_t st) {
+  hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(256), 0, st, partials, nblocks, totals, inv_lx);
   return hipGetLastError();
 }
 

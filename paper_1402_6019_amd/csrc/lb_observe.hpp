@@ -241,8 +241,6 @@ __device__ __forceinline__ void observe_tile(const TileArgs<typename Codec<MODE>
   }
 
   if constexpr (WHAT == WHAT_OBSERVE) {
-    R fsa[NS][9];
-    site_relax<C, NS>(p, f, drho, rho, jx, jy, Fx, Fy, fsa);
     double v[RED_N] = {};
     bool bad = false;
     v[RED_MASS0] = double(rho[0]);
@@ -252,9 +250,6 @@ __device__ __forceinline__ void observe_tile(const TileArgs<typename Codec<MODE>
       v[RED_PX] += double(jx[s]);
       v[RED_PY] += double(jy[s]);
       bad = bad || !(rho[s] > R(0) && rho[s] < R(INFINITY));
-      // momentum handed to the wall (see the step's reductions)
-      if (WALLS && y == 0) v[RED_WBOT] += 2.0 * (double(fsa[s][8]) - double(fsa[s][7])) - 2.0 * a.wall_mom[0][s];
-      if (WALLS && y == ly - 1) v[RED_WTOP] += 2.0 * (double(fsa[s][5]) - double(fsa[s][6])) - 2.0 * a.wall_mom[1][s];
     }
     v[RED_FLOW] = double(mx / sr);
     v[RED_BAD] = bad ? 1.0 : 0.0;

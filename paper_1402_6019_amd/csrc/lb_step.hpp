@@ -475,9 +475,9 @@ __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const sr
     hitem = halo_item(l, xh, lx, site_b, plane_b);
   }
 
-  double acc[RED_N];
+  double acc[ACC_N];
 #pragma unroll
-  for (int k = 0; k < RED_N; ++k) acc[k] = 0.0;
+  for (int k = 0; k < ACC_N; ++k) acc[k] = 0.0;
 
   // Stage 1, interior columns: psi_s and rho_s of lead row r into ring slot `slot` from the
   // pulled populations A of this thread's column.
@@ -801,9 +801,9 @@ __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const sr
       bool bad = !(rho[0] > R(0) && rho[0] < R(INFINITY));
 #pragma unroll
       for (int s = 1; s < NS; ++s) bad = bad || !(rho[s] > R(0) && rho[s] < R(INFINITY));
-      acc[RED_WBOT] += wb;
-      acc[RED_WTOP] += wt;
-      acc[RED_BAD] += bad ? 1.0 : 0.0;
+      acc[ACC_WBOT] += wb;
+      acc[ACC_WTOP] += wt;
+      acc[ACC_BAD] += bad ? 1.0 : 0.0;
     }
   };
 
@@ -826,10 +826,9 @@ __device__ __forceinline__ void run_tile(const StepArgs &a, const void *const sr
 
   if (ACCUM) {
     const int lane = tid & 63, wv = tid >> 6;
-    constexpr int slot[ACC_N] = {RED_WBOT, RED_WTOP, RED_BAD};
 #pragma unroll
     for (int k = 0; k < ACC_N; ++k) {
-      const double v = wave_sum(acc[slot[k]]);
+      const double v = wave_sum(acc[k]);
       if (lane == 0) red_lds[wv][k] = v;
     }
     __syncthreads();
@@ -875,7 +874,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == MOD
     const int t = base + mine;
     if (t >= b.ntiles) break;  // later rounds are shorter still
     if (base > 0) __syncthreads();  // the previous tile's last ring and staging reads are done
-    const int ti = (int)__builtin_amdgcn_readfirstlane((uint32_t)(b.tile0 + t));
+    const int ti = (int)__builtin_amdgcn_readfirstlane((uint32_t)t);
     const TileDesc td = b.tiles[ti];
     const StepArgs &a = b.inst[td.inst];
     double *const part = WHAT == WHAT_STEP_ACCUM ? b.accrows + (size_t)td.part * ACC_N : nullptr;

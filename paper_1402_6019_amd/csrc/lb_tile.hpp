@@ -290,7 +290,6 @@ __device__ __forceinline__ void tile_steps(const TileArgs<typename Codec<MODE>::
   stage(std::integral_constant<int, 1>{});
   if constexpr (N >= 2) stage(std::integral_constant<int, 2>{});
   if constexpr (N >= 3) stage(std::integral_constant<int, 3>{});
-  if constexpr (N >= 4) stage(std::integral_constant<int, 4>{});
 
   if constexpr (ACCUM) {
     // this workgroup's running sums: every wave's, then the waves in order
