@@ -531,28 +531,29 @@ __global__ void zero_kernel(uint32_t *p, size_t n) {
 
 // Tile of the reverse step: the largest that gives every compute unit one, as the frame it adds to
 // the local part shrinks with its size.
-static int adj_shape(int lx, int ly) {
+static int adj_shape(int lx, int ly, int n_cu) {
   auto tiles = [&](int bx, int by) { return (long long)((lx + bx - 1) / bx) * ((ly + by - 1) / by); };
-  return tiles(32, 16) >= 256 ? 2 : (tiles(16, 16) >= 256 ? 1 : 0);
+  return tiles(32, 16) >= n_cu ? 2 : (tiles(16, 16) >= n_cu ? 1 : 0);
 }
 
-int adj_blocks(int lx, int ly) {
-  const int k = adj_shape(lx, ly), bx = k == 2 ? 32 : 16, by = k == 0 ? 8 : 16;
+int adj_blocks(int lx, int ly, int n_cu) {
+  const int k = adj_shape(lx, ly, n_cu), bx = k == 2 ? 32 : 16, by = k == 0 ? 8 : 16;
   return ((lx + bx - 1) / bx) * ((ly + by - 1) / by);
 }
 
 template <typename R, int NS, bool WALLS, bool WIDE, int BX, int BY, int NT>
 static hipError_t adj_step_k(const AdjArgs &a, hipStream_t st) {
-  hipLaunchKernelGGL((adj_step_kernel<R, NS, WALLS, WIDE, BX, BY, NT>), dim3((unsigned)adj_blocks(a.lx, a.ly)), dim3(NT),
+  const int nb = ((a.lx + BX - 1) / BX) * ((a.ly + BY - 1) / BY);
+  hipLaunchKernelGGL((adj_step_kernel<R, NS, WALLS, WIDE, BX, BY, NT>), dim3(nb), dim3(NT),
                      (adj_lds_bytes<R, NS, BX, BY, NT>()), st, a);
   return hipGetLastError();
 }
 
 template <typename R, int NS, bool WALLS>
-static hipError_t adj_step_t(const AdjArgs &a, hipStream_t st) {
+static hipError_t adj_step_t(int n_cu, const AdjArgs &a, hipStream_t st) {
   if ((size_t)a.lx * a.ly * 9 * NS * sizeof(R) >= ((size_t)1 << 32))  // always the widest tile
     return adj_step_k<R, NS, WALLS, true, 32, 16, 512>(a, st);
-  switch (adj_shape(a.lx, a.ly)) {
+  switch (adj_shape(a.lx, a.ly, n_cu)) {
     case 0: return adj_step_k<R, NS, WALLS, false, 16, 8, 256>(a, st);
     case 1: return adj_step_k<R, NS, WALLS, false, 16, 16, 448>(a, st);
   }
@@ -560,17 +561,17 @@ static hipError_t adj_step_t(const AdjArgs &a, hipStream_t st) {
 }
 
 template <typename R>
-static hipError_t adj_step_r(int ns, int walls, const AdjArgs &a, hipStream_t st) {
-  if (ns == 1) return walls ? adj_step_t<R, 1, true>(a, st) : adj_step_t<R, 1, false>(a, st);
-  return walls ? adj_step_t<R, 2, true>(a, st) : adj_step_t<R, 2, false>(a, st);
+static hipError_t adj_step_r(int ns, int walls, int n_cu, const AdjArgs &a, hipStream_t st) {
+  if (ns == 1) return walls ? adj_step_t<R, 1, true>(n_cu, a, st) : adj_step_t<R, 1, false>(n_cu, a, st);
+  return walls ? adj_step_t<R, 2, true>(n_cu, a, st) : adj_step_t<R, 2, false>(n_cu, a, st);
 }
 
-hipError_t launch_adjoint_step(int fp64, int ns, int walls, const AdjArgs &a, hipStream_t st) {
-  return fp64 ? adj_step_r<double>(ns, walls, a, st) : adj_step_r<float>(ns, walls, a, st);
+hipError_t launch_adjoint_step(int fp64, int ns, int walls, int n_cu, const AdjArgs &a, hipStream_t st) {
+  return fp64 ? adj_step_r<double>(ns, walls, n_cu, a, st) : adj_step_r<float>(ns, walls, n_cu, a, st);
 }
 
-hipError_t launch_adjoint_reduce(const double *partials, int lx, int ly, double *acc, hipStream_t st) {
-  hipLaunchKernelGGL(adj_reduce_kernel, dim3(1), dim3(256), 0, st, partials, adj_blocks(lx, ly), acc);
+hipError_t launch_adjoint_reduce(const double *partials, int nblocks, double *acc, hipStream_t st) {
+  hipLaunchKernelGGL(adj_reduce_kernel, dim3(1), dim3(256), 0, st, partials, nblocks, acc);
   return hipGetLastError();
 }
 

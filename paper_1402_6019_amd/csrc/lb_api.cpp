@@ -986,7 +986,7 @@ AdjLayout adjoint_layout(const lb_ctx *c, int64_t T, int32_t every, int32_t flag
   L.lam0 = o; o += L.lamb;
   L.lam1 = o; o += L.lamb;
   L.fields = o; o += (size_t)nstate * L.fb;  // one set per state of a segment (of the run when all)
-  L.partials = o; o += align256((size_t)adj_blocks(c->lat.lx, c->lat.ly) * ADJ_N * 8);
+  L.partials = o; o += align256((size_t)adj_blocks(c->lat.lx, c->lat.ly, c->n_cu) * ADJ_N * 8);
   L.acc = o; o += align256(ADJ_N * 8);
   L.total = o;
   return L;
@@ -1106,7 +1106,7 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
   if (e == hipSuccess) e = launch_zero(ws + L.lam1, L.lamb, c->stream);
   if (e == hipSuccess) e = launch_zero(ws + L.acc, ADJ_N * 8, c->stream);
   if (e == hipSuccess)
-    e = launch_zero(ws + L.partials, (size_t)adj_blocks(c->lat.lx, c->lat.ly) * ADJ_N * 8, c->stream);
+    e = launch_zero(ws + L.partials, (size_t)adj_blocks(c->lat.lx, c->lat.ly, c->n_cu) * ADJ_N * 8, c->stream);
   if (e != hipSuccess) return done(hip_fail(c, e, "adjoint setup"));
   AdjArgs a = adjoint_args(c, loss_weights[0], loss_weights[1], T);
   a.partials = reinterpret_cast<double *>(ws + L.partials);
@@ -1122,7 +1122,7 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
       a.fields = seg_f(b, jj);
       a.lam_next = lam_buf[qq];
       a.lam = lam_buf[qq ^ 1];
-      er = launch_adjoint_step(fp64, c->lat.n_species, c->lat.walls, a, st);
+      er = launch_adjoint_step(fp64, c->lat.n_species, c->lat.walls, c->n_cu, a, st);
       qq ^= 1;
     }
     return er;
@@ -1200,7 +1200,7 @@ int lb_adjoint(lb_ctx *c, int64_t T, int32_t every, int32_t flags, const double 
     if (k - 1 < L.nck && k > 0 && (rc = recompute_segment(k - 1))) return graphs_done(rc);
     if ((rc = reverse_segment(k))) return graphs_done(rc);
   }
-  e = launch_adjoint_reduce(a.partials, c->lat.lx, c->lat.ly, acc, rst);
+  e = launch_adjoint_reduce(a.partials, adj_blocks(c->lat.lx, c->lat.ly, c->n_cu), acc, rst);
   // the context's stream continues after the reverse sweep
   if (e == hipSuccess && two) e = hipEventRecord(ev_rev[0], rst);
   if (e == hipSuccess && two) e = hipStreamWaitEvent(c->stream, ev_rev[0], 0);

@@ -256,11 +256,11 @@ struct AdjArgs {
 // Per-block partial sums of the adjoint: parameter sensitivities and the loss.
 enum AdjSlot { ADJ_G1A = 0, ADJ_G1B, ADJ_G2A, ADJ_G2B, ADJ_GAB, ADJ_GX, ADJ_GY, ADJ_LW, ADJ_LQ, ADJ_N };
 
-int adj_blocks(int lx, int ly);
+int adj_blocks(int lx, int ly, int n_cu);  // n_cu: compute units
 // One reverse step; adds this step's per-block sensitivities to a.partials.
-hipError_t launch_adjoint_step(int fp64, int ns, int walls, const AdjArgs &a, hipStream_t st);
+hipError_t launch_adjoint_step(int fp64, int ns, int walls, int n_cu, const AdjArgs &a, hipStream_t st);
 // acc[k] += sum over blocks of partials[block][k] (fixed order).
-hipError_t launch_adjoint_reduce(const double *partials, int lx, int ly, double *acc, hipStream_t st);
+hipError_t launch_adjoint_reduce(const double *partials, int nblocks, double *acc, hipStream_t st);
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
 
 // Host-side launchers (lb_kernels.hip).  Return hipSuccess or the launch error.
