@@ -481,10 +481,11 @@ def auxiliary_passes(rho, kw, reps=200):
 def couette_cell(steps, sample_every=100):
     """Planar Couette cell of the emulsion section at its 1040 x 1040 domain: confined
     emulsion (volume fraction 0.8, seed 6), walls wetted by B sliding with -U_w and +U_w
-    (U_w = 0.01), FP32.  Times the plain step, the profile pass (lb_profile: a step's read of
-    the state without the store, plus a small second pass) and a run that takes a profile
-    every `sample_every` steps followed by the statistics pass.  The launch shape is the
-    autotuner's (1040 columns do not fill whole 256-wide strips)."""
+    (U_w = 0.01), FP32.  Times the plain step in whole runs (several steps per launch) and called one
+    by one, the profile pass (lb_profile: a step's read of the state without the store, plus a small
+    second pass) and a run that takes a profile every `sample_every` steps followed by the statistics
+    pass, which is compared with the whole runs.  The launch shape is the autotuner's (1040 columns do
+    not fill whole 256-wide strips)."""
     import torch
     import lbgen
     from paper_1402_6019_amd import Sim
@@ -509,7 +510,16 @@ def couette_cell(steps, sample_every=100):
         torch.cuda.synchronize()
         return start.elapsed_time(stop) / reps
 
-    ms_step = timed(lambda: sim.step(1), steps)
+    def bulk(s, n):
+        s.step(20)
+        start.record(s.stream)
+        s.step(n)
+        stop.record(s.stream)
+        torch.cuda.synchronize()
+        return start.elapsed_time(stop) / n
+
+    ms_step = bulk(sim, steps)
+    ms_called = timed(lambda: sim.step(1), steps)
     nprof = 50
     buf = torch.empty((nprof, 4 * ly + 1), dtype=torch.float64, device="cuda")
     it = iter(range(nprof))
@@ -523,15 +533,7 @@ def couette_cell(steps, sample_every=100):
     ms_run = start.elapsed_time(stop) / (nsamp * sample_every)
     sig = st["sigma"].cpu().numpy()
 
-    # the forced pairs (lb_set_two_step), timed over whole runs of steps
-    def bulk(s, n):
-        s.step(20)
-        start.record(s.stream)
-        s.step(n)
-        stop.record(s.stream)
-        torch.cuda.synchronize()
-        return start.elapsed_time(stop) / n
-
+    # the forced pairs (lb_set_two_step)
     sim.set_two_step(True)
     ms_two = bulk(sim, steps)
     sim.close()
@@ -552,11 +554,12 @@ def couette_cell(steps, sample_every=100):
     return {"workload": f"Couette cell {lx}x{ly}, confined emulsion, volume fraction 0.8, seed 6, walls +-{uw}, FP32",
             "mass_fraction": info["mass_fraction"], "tile": list(tile), "default_tile": list(default_tile),
             "ms_per_step": ms_step, "mlups": lx * ly / (ms_step * 1e-3) / 1e6,
-            "gbs": 144 * lx * ly / (ms_step * 1e-3) / 1e9,
+            "gbs": 144 * lx * ly / (ms_step * 1e-3) / 1e9, "ms_per_step_called_one_by_one": ms_called,
             "ms_per_step_two_step": ms_two, "gbs_two_step": 144 * lx * ly / (ms_two * 1e-3) / 1e9,
             "ms_per_profile": ms_prof, "profile_read_gbs": read_bytes / (ms_prof * 1e-3) / 1e9,
             "profile_every": sample_every, "ms_per_step_with_profiles": ms_run,
-            "profile_overhead": ms_run / ms_step - 1.0, "samples": nsamp,
+            "profile_overhead": ms_run / ms_step - 1.0,  # both in runs of many steps per call
+            "samples": nsamp,
             "mean_wall_stress": [float(sig[0]), float(-sig[-1])],
             "ragged_width": {"note": "ps per site of the 1040^2 cell against the same cell at 1024^2 (autotuned, whole "
                                      "runs of steps): single = the kernel the autotuner kept, two_step = forced pairs",
@@ -1018,11 +1021,15 @@ def main():
             "frac": head["gbs"] / HBM_PEAK_GBS,
             "traffic": traffic_from_profile(khash, "f32", head["tile"]),
             "kernel": step_kernel_name("f32", "periodic", tile), "bytes_per_lu": 144,
+            "steps_per_launch": 1 if tile else 2,
             "copy_ceiling_gbs": copy["gbs"], "frac_of_copy": head["gbs"] / copy["gbs"],
             "stream_copy_gbs": max(copy["stream_copy_gbs"], copy["stream_copy_nt_gbs"]),
             "frac_of_stream_copy": head["gbs"] / max(copy["stream_copy_gbs"], copy["stream_copy_nt_gbs"]),
             "served_by": "infinity_cache",
-            "note": "footprint 2 x 75.5 MB fits in the 256 MB Infinity Cache, so this rate is served by that "
+            "note": "achieved and frac count the bytes of one crossing of the lattice per step, which a launch of "
+                    "several steps makes once: its memory traffic (traffic, bytes per launch) runs at about half "
+                    "that rate, and the kernel is bound by vector issue. "
+                    "Footprint 2 x 75.5 MB fits in the 256 MB Infinity Cache, so this rate is served by that "
                     "cache, not by HBM; hbm_served gives the same kernel on the 4096 x 512 channel, whose "
                     "302 MB footprint exceeds it"}
     beyond = None if args.core else leg("beyond_infinity_cache", channel_beyond_cache, max(50, args.steps // 4))
