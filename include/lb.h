@@ -199,8 +199,9 @@ int lb_wall_stress(lb_ctx *ctx, double out[2], int32_t reset);
    Kinetic Theory for non-ideal fluids"; the emulsion section keeps each species' mass fixed by
    its initial condition); also the flow rate (1/lx) sum u_x of the confined flows (section
    "Numerical simulations of confined pressure-driven flows", u as in lb_moments) if
-   flow != NULL.  Sums are FP64 in a fixed order whatever the storage mode.  Launches one
-   reduction pass.  Synchronises; returns LB_EUNSTABLE on a bad density. */
+   flow != NULL.  Sums are FP64 in an order that depends on the lattice alone, whatever the storage mode
+   and the launch shape; the momentum has digits down to about 1e-16 of sum |j|, so what is left of it on
+   a periodic lattice at rest is rounding of that order.  Launches one reduction pass.  Synchronises; returns LB_EUNSTABLE on a bad density. */
 int lb_totals(lb_ctx *ctx, double mass[2], double momentum[2], double *flow);
 
 /* Write the current pre-collision populations f(t) in the canonical FP64 layout to dst

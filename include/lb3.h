@@ -84,8 +84,9 @@ int lb3_moments(lb3_ctx *ctx, void *rho, void *u, int32_t dtype);
 
 /* FP64 totals of the current state (host): species masses, total momentum sum_s j_s (3
    components), the collision invariants of eq. (LB); and, if flow != NULL, the flow rate
-   sum u_x / (lx lz) with u as in lb3_moments.  Synchronises; LB_EUNSTABLE on a non-finite or
-   non-positive density. */
+   sum u_x / (lx lz) with u as in lb3_moments.  FP64 sums in the order of the launch shape that
+   lb3_get_tile reports, whichever kernel steps; the momentum has digits down to about 1e-16 of
+   sum |j|.  Synchronises; LB_EUNSTABLE on a non-finite or non-positive density. */
 int lb3_totals(lb3_ctx *ctx, double mass[2], double momentum[3], double *flow);
 
 /* Canonical FP64 pre-collision populations f_l(x, t) of eq. (LB) (layout above) to dst / from

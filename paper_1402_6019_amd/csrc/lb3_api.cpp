@@ -175,8 +175,9 @@ int launch_what(lb3_ctx *c, int what, void *rho, void *u, int out_f32) {
   Lb3Args a = args3(c);
   // Totals always go through step3_kernel in the context's launch shape: a sum of terms that cancel (the
   // momentum of a periodic lattice near rest: 1e-13 left of a sum of |j| of 1e4) is what its order of
-  // additions makes of it, so that order depends on no rule of which kernel steps.  It costs 107 of 7963 us
-  // per pass of five steps, moments and totals at 256^3 FP32, 13 of 1142 at 100 x 70 x 60 FP64.
+  // additions makes of it, so that order depends on no rule of which kernel steps.  A pass of steps, moments and
+  // totals takes 8080 us at 256^3 FP32 (five steps) and 1145 at 100 x 70 x 60 FP64 (ten) this way, 7963 and 1142
+  // with the totals in the march.
   const bool any_shape = c->shape_set || what == WHAT_OBSERVE;
   const bool split = !any_shape && c->d_psi;
   if (!any_shape && !split) march_grid3(c, a);

@@ -1,7 +1,7 @@
 // Host runtime of the batched calls of include/lb.h: many independent lattices of uneven
 // sizes and couplings (one kernel template: same storage, species count and wall mode),
-// stepped together by one persistent launch per time step, optionally replayed from a
-// captured HIP graph, with the tile shape picked by an autotuner.
+// stepped together, every launch over the tiles of all of them (two or three time steps per launch,
+// or one in marched rows where a launch shape is set), optionally replayed from a captured HIP graph.
 
 #include <hip/hip_runtime.h>
 
