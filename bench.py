@@ -524,13 +524,18 @@ def couette_cell(steps, sample_every=100):
     buf = torch.empty((nprof, 4 * ly + 1), dtype=torch.float64, device="cuda")
     it = iter(range(nprof))
     ms_prof = timed(lambda: sim.profile(buf[next(it)]), nprof)
+    # the same runs of sample_every steps without and with a profile after each, in turn: the best of three
     nsamp = max(2, steps // sample_every)
-    start.record(sim.stream)
-    samples = sim.sample_profiles(nsamp, sample_every)
-    st = sim.profile_stats(samples)
-    stop.record(sim.stream)
-    torch.cuda.synchronize()
-    ms_run = start.elapsed_time(stop) / (nsamp * sample_every)
+    ms_runs, ms_profiled = [], []
+    for _ in range(3):
+        ms_runs.append(timed(lambda: sim.step(sample_every), nsamp) / sample_every)
+        start.record(sim.stream)
+        samples = sim.sample_profiles(nsamp, sample_every)
+        st = sim.profile_stats(samples)
+        stop.record(sim.stream)
+        torch.cuda.synchronize()
+        ms_profiled.append(start.elapsed_time(stop) / (nsamp * sample_every))
+    ms_run = min(ms_profiled)
     sig = st["sigma"].cpu().numpy()
 
     # the forced pairs (lb_set_two_step)
@@ -558,7 +563,7 @@ def couette_cell(steps, sample_every=100):
             "ms_per_step_two_step": ms_two, "gbs_two_step": 144 * lx * ly / (ms_two * 1e-3) / 1e9,
             "ms_per_profile": ms_prof, "profile_read_gbs": read_bytes / (ms_prof * 1e-3) / 1e9,
             "profile_every": sample_every, "ms_per_step_with_profiles": ms_run,
-            "profile_overhead": ms_run / ms_step - 1.0,  # both in runs of many steps per call
+            "profile_overhead": ms_run / min(ms_runs) - 1.0,
             "samples": nsamp,
             "mean_wall_stress": [float(sig[0]), float(-sig[-1])],
             "ragged_width": {"note": "ps per site of the 1040^2 cell against the same cell at 1024^2 (autotuned, whole "
