@@ -27,7 +27,7 @@ LB_ORACLE_LIB_DIR="$OUT" OMP_NUM_THREADS=2 \
 echo "== host runtime (hipcc, -Xarch_host sanitizers)"
 CL_RT="$(ls /opt/rocm/llvm/lib/clang/*/lib/linux/libclang_rt.asan-x86_64.so | head -1)"
 FL="--offload-arch=gfx950 -O1 -std=c++17 -fPIC -Xclang -target-feature -Xclang -packed-fp32-ops -ffp-contract=off -I$ROOT/include"
-SRCS="lb_step_f64.hip lb_step_f32.hip lb_step_bf16.hip lb_kernels.hip lb_adjoint.hip lb_static.hip lb3_kernels.hip lb_api.cpp lb_batch.cpp lb_rheology.cpp lb3_api.cpp"
+SRCS="$(cd "$ROOT" && python3 -c "from paper_1402_6019_amd.build import SOURCES; print(*SOURCES)")"
 for f in $SRCS; do
   /opt/rocm/bin/hipcc $FL -Xarch_host -fsanitize=address -Xarch_host -fsanitize=undefined \
       -Xarch_host -fno-sanitize-recover=undefined -Xarch_host -fno-omit-frame-pointer \
